@@ -243,31 +243,33 @@ int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
                void* y, int64_t ldy, int y_dtype, void* stream);
 
 /*
- * Workspace bytes that let nvfp4_gemm_with_workspace run an M x N x K call
- * in its K-halves form on the current device; 0 when the shape does not use
- * it (then any workspace, or none, gives the nvfp4_gemm launches) or the
- * arguments are invalid.  The form applies when the last round of 256 x 256
- * output tiles (one per compute unit) would be at most half full, those
- * tiles make whole tile columns, and K % 512 == 0 (e.g. 8192 x 5120 x 17408:
- * 2 * 8192 * 1024 * 4 bytes).
+ * Workspace bytes that let nvfp4_gemm_with_workspace split the K range of an
+ * M x N x K call over several workgroups per output tile on the current
+ * device; 0 when the shape does not use it (then any workspace, or none,
+ * gives the nvfp4_gemm launches) or the arguments are invalid.  Two forms:
+ *   - K halves of the last round: the last round of 256 x 256 output tiles
+ *     (one per compute unit) would be at most half full, those tiles make
+ *     whole tile columns, and K % 512 == 0 (e.g. 8192 x 5120 x 17408:
+ *     2 * 8192 * 1024 * 4 bytes);
+ *   - K parts: the whole output has too few tiles to fill the compute units
+ *     (e.g. 200 x 5120 x 17408); at most 128 MB.
  */
 size_t nvfp4_gemm_workspace(int64_t M, int64_t N, int64_t K);
 
 /*
  * nvfp4_gemm with a caller workspace (same arguments, same result contract
- * up to the summation order).  For shapes where nvfp4_gemm_workspace is
- * non-zero, the output tiles of the partially filled last round are computed
- * as two K halves on twice as many compute units: each half writes its
- * segment-scaled FP32 partial sums to the workspace ([2][M][tail columns]),
- * and a second pass writes y = half0 + half1 (one FP32 addition; bf16 output
- * is that sum rounded to nearest even).  Three launches on `stream` instead
- * of two; the workspace is overwritten and must not be used by another call
- * in flight.
- *   workspace        device memory, 16-byte aligned, or NULL when
- *                    nvfp4_gemm_workspace(M, N, K) is 0.
+ * up to the summation order).  Each K half or K part of an output tile writes
+ * its segment-scaled FP32 partial sums to the workspace ([parts][M][columns]),
+ * and a last pass writes their sum (FP32 additions in part order; bf16 output
+ * is that sum rounded to nearest even).  The workspace is overwritten and must
+ * not be used by another call in flight.
+ *   workspace        device memory, 16-byte aligned, or NULL.
  *   workspace_bytes  its size.
- * Errors: as nvfp4_gemm; NVFP4_EWORKSPACE if the workspace is smaller than
- * nvfp4_gemm_workspace(M, N, K); NVFP4_EINVAL for a misaligned workspace.
+ * Errors: as nvfp4_gemm; NVFP4_EINVAL for a misaligned workspace;
+ * NVFP4_EWORKSPACE if the shape has a K-halves form and the workspace is
+ * smaller than that needs.  A workspace smaller than the K-parts form needs is
+ * not an error: the call then takes the K-halves form if there is one, else
+ * the nvfp4_gemm launches.
  */
 int nvfp4_gemm_with_workspace(const uint8_t* a_codes, const uint8_t* a_scales,
                               const float* a_g_enc, int64_t M, int64_t K,

@@ -257,7 +257,7 @@ int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const float* a_g
   st = check_device();
   if (st != NVFP4_OK) return st;
   hipError_t e = nvfp4::launch_gemm(a_codes, a_scales, a_g_enc, M, K, w_packed, N, seg_offsets, n_seg,
-                                    w_g_enc_seg, y, ldy, y_dtype == NVFP4_F32, nullptr, 0,
+                                    w_g_enc_seg, y, ldy, y_dtype == NVFP4_F32, nullptr, nvfp4::kNoWorkspace,
                                     static_cast<hipStream_t>(stream));
   return e == hipSuccess ? NVFP4_OK : fail_hip(e);
 }
@@ -279,11 +279,10 @@ int nvfp4_gemm_with_workspace(const uint8_t* a_codes, const uint8_t* a_scales, c
   if (workspace != nullptr && !aligned16(workspace)) return NVFP4_EINVAL;
   st = check_device();
   if (st != NVFP4_OK) return st;
-  const size_t need = M > 0 ? nvfp4::gemm_workspace_bytes(M, N, K) : 0;
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return NVFP4_EWORKSPACE;
   hipError_t e = nvfp4::launch_gemm(a_codes, a_scales, a_g_enc, M, K, w_packed, N, seg_offsets, n_seg,
-                                    w_g_enc_seg, y, ldy, y_dtype == NVFP4_F32, need > 0 ? workspace : nullptr,
-                                    workspace_bytes, static_cast<hipStream_t>(stream));
+                                    w_g_enc_seg, y, ldy, y_dtype == NVFP4_F32, workspace,
+                                    workspace == nullptr ? 0 : workspace_bytes, static_cast<hipStream_t>(stream));
+  if (e == nvfp4::kWorkspaceTooSmall) return NVFP4_EWORKSPACE;
   return e == hipSuccess ? NVFP4_OK : fail_hip(e);
 }
 

@@ -24,34 +24,112 @@ static uint32_t cu_count() {
   return (uint32_t)g_cu_count[dev];
 }
 
+// Estimated time of one tile shape on n_cu compute units, in us, for the
+// choice between tile shapes and numbers of K parts.  A workgroup alone on a
+// CU and two that share it take the same time per chunk and workgroup
+// (measured: 240 workgroups of 91 chunks and 480 of 45 both 50 us), so the
+// busiest CU's work is ceil(workgroups / CUs) runs of chunks whatever the
+// occupancy.
+struct TileCost {
+  int kind, super_kind;
+  uint32_t bm, bn;
+  float chunk_us, chunk_us_super;   // one 64-deep chunk of a tile
+  float fixed_us;                   // first loads, epilogue, launch
+};
+// Measured at 200 x 5120 x 17408, 1000 x 8192 x 5120 and 300 x 5120 x 4352.
+constexpr TileCost kTileCosts[] = {
+    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.60f, 1.46f, 7.0f},
+    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.51f, 0.46f, 5.0f},
+    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.51f, 0.46f, 5.0f},
+};
+// The summing pass: a launch, and every partial sum written and read once
+// (they stay in the last-level cache).
+constexpr float kSumLaunchUs = 2.5f, kPartBytesPerUs = 8.0e6f;
+// Bound on the partial sums of one call.
+constexpr uint64_t kMaxPartBytes = 128ull << 20;
+constexpr uint32_t kMaxParts = 32;
+constexpr uint32_t kMinPartChunks = 4;   // one group of chunks with super-stages
+
+// Below this K the K-halves / tall-tile form of the last round is kept as
+// it is: the cost of a tile is then mostly its first loads and epilogue.
+constexpr int64_t kTailMinK = 2048;
+
+// The cheapest single launch over all columns: tile shape and K parts.
+static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws, float* cost) {
+  const bool super = K % 256 == 0;
+  const uint32_t unit = super ? 4 : 1, units = (uint32_t)(K / 64) / unit;
+  GemmPlan best{};
+  *cost = 0.0f;
+  for (const TileCost& t : kTileCosts) {
+    const bool square = t.kind == GemmPlan::kLdsSquare;
+    const uint64_t tiles = (uint64_t)((M + t.bm - 1) / t.bm) * (uint64_t)((N + t.bn - 1) / t.bn);
+    for (uint32_t parts = 1; parts <= kMaxParts; ++parts) {
+      const uint64_t part_bytes = (uint64_t)parts * (uint64_t)M * parts_row((uint32_t)N) * sizeof(float);
+      if (parts > 1 && (!with_ws || units * unit < parts * kMinPartChunks || part_bytes > kMaxPartBytes ||
+                        (square && !super)))
+        break;
+      const uint64_t rounds = (tiles * parts + n_cu - 1) / n_cu;
+      const uint32_t chunks = (units + parts - 1) / parts * unit;
+      const float c = (float)rounds * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us +
+                      (parts > 1 ? kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs : 0.0f);
+      if (best.first == GemmPlan::kNone || c < *cost) {
+        best.first = super ? t.super_kind : t.kind;
+        best.k_parts = parts;
+        *cost = c;
+      }
+    }
+  }
+  best.n_split = (uint32_t)N;
+  return best;
+}
+
+// Square tiles fill whole rounds of one workgroup per CU.  When the last
+// round would be at most half full and its tiles make whole tile columns,
+// those columns run as a second launch: with a workspace and K % 512 == 0, the
+// same square tiles as two K halves on twice the CUs (FP32 partial sums, then
+// a summing pass: about 0.55 of a round plus the pass); otherwise as 256 x 128
+// tiles (two per CU), about 0.7 of a round.  Scale super-stages need
+// K % 256 == 0 (whole groups of 4 chunks).
+static GemmPlan plan_square(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws) {
+  GemmPlan g{};
+  g.first = (K % 256) == 0 ? GemmPlan::kLdsSuper : GemmPlan::kLdsSquare;
+  g.n_split = (uint32_t)N;
+  g.k_parts = 1;
+  const uint32_t tiles_m = (uint32_t)((M + kSquareTile - 1) / kSquareTile);
+  const uint32_t tiles_n = (uint32_t)((N + kSquareTile - 1) / kSquareTile);
+  const uint32_t rem = n_cu ? (tiles_m * tiles_n) % n_cu : 0;
+  if (rem != 0 && rem <= n_cu / 2 && rem % tiles_m == 0 && rem / tiles_m < tiles_n) {
+    g.n_split = (tiles_n - rem / tiles_m) * kSquareTile;
+    g.second = (with_ws && K % 512 == 0) ? GemmPlan::kLdsSuperHalves : GemmPlan::kLdsTall;
+  }
+  return g;
+}
+
 // The kernels one nvfp4_gemm call launches for a shape (n_cu: compute units
 // of the device).
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws) {
+  const bool aligned = (K % 64) == 0;
   GemmPlan g{};
   g.n_split = (uint32_t)N;
-  const bool aligned = (K % 64) == 0;
-  if (M == 0) {
-    g.first = GemmPlan::kNone;
-  } else if (aligned && N <= 96) {
+  g.k_parts = 1;
+  if (M == 0) return g;
+  if (aligned && N <= 96) {
     g.first = GemmPlan::kSplitkNarrow;
   } else if (aligned && M <= 32) {
     g.first = M <= 8 ? GemmPlan::kSplitkDecodeFew : GemmPlan::kSplitkDecode;
   } else if (aligned) {
-    // Square tiles fill whole rounds of one workgroup per CU.  When the last
-    // round would be at most half full and its tiles make whole tile
-    // columns, those columns run as a second launch: with a workspace and
-    // K % 512 == 0, the same square tiles as two K halves on twice the CUs
-    // (FP32 partial sums, then a summing pass: about 0.55 of a round plus
-    // the pass); otherwise as 256 x 128 tiles (two per CU), about 0.7 of a
-    // round.  Scale super-stages need K % 256 == 0 (whole groups of 4
-    // chunks).
-    g.first = (K % 256) == 0 ? GemmPlan::kLdsSuper : GemmPlan::kLdsSquare;
-    const uint32_t tiles_m = (uint32_t)((M + kSquareTile - 1) / kSquareTile);
-    const uint32_t tiles_n = (uint32_t)((N + kSquareTile - 1) / kSquareTile);
-    const uint32_t rem = n_cu ? (tiles_m * tiles_n) % n_cu : 0;
-    if (rem != 0 && rem <= n_cu / 2 && rem % tiles_m == 0 && rem / tiles_m < tiles_n) {
-      g.n_split = (tiles_n - rem / tiles_m) * kSquareTile;
-      g.second = (with_ws && K % 512 == 0) ? GemmPlan::kLdsSuperHalves : GemmPlan::kLdsTall;
+    g = plan_square(M, N, K, n_cu, with_ws);
+    const bool tail = g.second != GemmPlan::kNone;
+    if (n_cu != 0 && (!tail || K >= kTailMinK)) {
+      // The cheapest tile shape and number of K parts, where that beats the
+      // second launch of the last round (0.6 or 0.75 of a round).
+      float cost;
+      const GemmPlan t = plan_tiles(M, N, K, n_cu, with_ws, &cost);
+      const TileCost& sq = kTileCosts[0];
+      const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
+      const float rounds = (float)(tiles / n_cu) + (g.second == GemmPlan::kLdsSuperHalves ? 0.6f : 0.75f);
+      const float chunk_us = (K % 256) == 0 ? sq.chunk_us_super : sq.chunk_us;
+      if (!tail || cost < rounds * (float)(K / 64) * chunk_us + sq.fixed_us) g = t;
     }
   } else {
     g.first = GemmPlan::kReg;
@@ -60,17 +138,33 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
 }
 
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N) {
-  if (g.second != GemmPlan::kLdsSuperHalves) return 0;
-  return (size_t)2 * (size_t)M * (size_t)halves_row((uint32_t)N - g.n_split) * sizeof(float);
+  if (g.second == GemmPlan::kLdsSuperHalves)
+    return (size_t)2 * (size_t)M * (size_t)parts_row((uint32_t)N - g.n_split) * sizeof(float);
+  if (g.k_parts > 1) return (size_t)g.k_parts * (size_t)M * (size_t)parts_row((uint32_t)N) * sizeof(float);
+  return 0;
 }
 
-const char* gemm_kernel_name(int kind) {
+const char* gemm_kernel_name(int kind, bool parts) {
   switch (kind) {
     case GemmPlan::kLdsSquare: return "gemm_lds_kernel<LdsSquare> (256x256 tiles)";
-    case GemmPlan::kLdsSuper: return "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, scale super-stages)";
+    case GemmPlan::kLdsSuper:
+      return parts ? "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, scale super-stages, K parts) + sum_parts_kernel"
+                   : "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, scale super-stages)";
+    case GemmPlan::kLdsMid:
+      return parts ? "gemm_lds_kernel<LdsMid> (128x128 tiles, K parts) + sum_parts_kernel"
+                   : "gemm_lds_kernel<LdsMid> (128x128 tiles)";
+    case GemmPlan::kLdsMidSuper:
+      return parts ? "gemm_lds_kernel<LdsMidSuper> (128x128 tiles, scale super-stages, K parts) + sum_parts_kernel"
+                   : "gemm_lds_kernel<LdsMidSuper> (128x128 tiles, scale super-stages)";
+    case GemmPlan::kLdsLow:
+      return parts ? "gemm_lds_kernel<LdsLow> (64x256 tiles, K parts) + sum_parts_kernel"
+                   : "gemm_lds_kernel<LdsLow> (64x256 tiles)";
+    case GemmPlan::kLdsLowSuper:
+      return parts ? "gemm_lds_kernel<LdsLowSuper> (64x256 tiles, scale super-stages, K parts) + sum_parts_kernel"
+                   : "gemm_lds_kernel<LdsLowSuper> (64x256 tiles, scale super-stages)";
     case GemmPlan::kLdsTall: return "gemm_lds_kernel<LdsTall> (256x128 tiles)";
     case GemmPlan::kLdsSuperHalves:
-      return "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, two K halves, FP32 partials) + sum_halves_kernel";
+      return "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, two K halves, FP32 partials) + sum_parts_kernel";
     case GemmPlan::kSplitkNarrow: return "gemm_splitk_kernel<4,2,3,3> (64x96 tiles, split-K)";
     case GemmPlan::kSplitkDecode: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";
     case GemmPlan::kSplitkDecodeFew: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
@@ -84,7 +178,7 @@ const char* gemm_kernel_for(int64_t M, int64_t N, int64_t K, int part, bool with
   if (n_cu == 0) return nullptr;
   const GemmPlan g = plan_gemm(M, N, K, n_cu, with_ws);
   const int kind = part == 0 ? g.first : g.second;
-  return kind == GemmPlan::kNone ? nullptr : gemm_kernel_name(kind);
+  return kind == GemmPlan::kNone ? nullptr : gemm_kernel_name(kind, part == 0 && g.k_parts > 1);
 }
 
 static hipError_t run_one(int kind, const GemmOperands& o, const GemmParams& p, uint32_t n_begin, uint32_t n_end,
@@ -94,6 +188,10 @@ static hipError_t run_one(int kind, const GemmOperands& o, const GemmParams& p, 
     case GemmPlan::kLdsSuper:
       return out_f32 ? launch_lds_super_f32(o, p, n_begin, n_end, stream)
                      : launch_lds_super_bf16(o, p, n_begin, n_end, stream);
+    case GemmPlan::kLdsMid:
+    case GemmPlan::kLdsMidSuper: return launch_lds_mid(o, p, kind == GemmPlan::kLdsMidSuper, 1, nullptr, out_f32, stream);
+    case GemmPlan::kLdsLow:
+    case GemmPlan::kLdsLowSuper: return launch_lds_low(o, p, kind == GemmPlan::kLdsLowSuper, 1, nullptr, out_f32, stream);
     case GemmPlan::kLdsTall: return launch_lds_tall(o, p, n_begin, n_end, out_f32, stream);
     case GemmPlan::kSplitkNarrow: return launch_splitk_narrow(o, p, out_f32, false, stream);
     case GemmPlan::kSplitkDecode:
@@ -119,16 +217,34 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
   p.y_stream = !out_f32 && (uint64_t)M * (uint64_t)N * 2u >= kMallBytes ? 1u : 0u;
   const GemmOperands o{a_codes, a_scales, a_g, static_cast<const uint8_t*>(w_packed), w_g, y};
   GemmPlan g = plan_gemm(M, N, K, cu_count(), workspace != nullptr);
-  if (g.second == GemmPlan::kLdsSuperHalves && workspace_bytes < plan_workspace_bytes(g, M, N))
+  if (workspace_bytes != kNoWorkspace && workspace_bytes < plan_workspace_bytes(plan_gemm(M, N, K, cu_count(), true), M, N)) {
     g = plan_gemm(M, N, K, cu_count(), false);
+    if (K % 64 == 0 && N > 96 && M > 32) {
+      const GemmPlan h = plan_square(M, N, K, cu_count(), true);
+      if (workspace_bytes < plan_workspace_bytes(h, M, N)) return kWorkspaceTooSmall;
+      if (h.second == GemmPlan::kLdsSuperHalves) g = h;
+    }
+  }
   const bool aligned = (K % 64) == 0;
+  float* parts = static_cast<float*>(workspace);
+  if (g.k_parts > 1) {
+    hipError_t e;
+    if (g.first == GemmPlan::kLdsSuper)
+      e = launch_lds_super_parts(o, p, 0, (uint32_t)N, g.k_parts, parts, stream);
+    else if (g.first == GemmPlan::kLdsMid || g.first == GemmPlan::kLdsMidSuper)
+      e = launch_lds_mid(o, p, g.first == GemmPlan::kLdsMidSuper, g.k_parts, parts, true, stream);
+    else
+      e = launch_lds_low(o, p, g.first == GemmPlan::kLdsLowSuper, g.k_parts, parts, true, stream);
+    if (e != hipSuccess) return e;
+    return launch_sum_parts(parts, g.k_parts, (uint32_t)M, (uint32_t)N, y, (uint32_t)ldy, 0, out_f32, stream);
+  }
   hipError_t e = run_one(g.first, o, p, 0, g.n_split, out_f32, aligned, stream);
   if (e != hipSuccess || g.second == GemmPlan::kNone) return e;
   if (g.second == GemmPlan::kLdsSuperHalves) {
-    float* parts = static_cast<float*>(workspace);
-    e = launch_lds_super_halves(o, p, g.n_split, (uint32_t)N, parts, stream);
+    e = launch_lds_super_parts(o, p, g.n_split, (uint32_t)N, 2, parts, stream);
     if (e != hipSuccess) return e;
-    return launch_sum_halves(parts, (uint32_t)M, (uint32_t)N - g.n_split, y, (uint32_t)ldy, g.n_split, out_f32, stream);
+    return launch_sum_parts(parts, 2, (uint32_t)M, (uint32_t)N - g.n_split, y, (uint32_t)ldy, g.n_split, out_f32,
+                            stream);
   }
   return run_one(g.second, o, p, g.n_split, (uint32_t)N, out_f32, aligned, stream);
 }

@@ -90,9 +90,9 @@ struct GemmParams {
   // go to HBM while the GEMM leaves HBM idle instead of being written back
   // when the next kernel's reads evict them).
   uint32_t y_stream;
-  // K split across workgroups (LDS kernel, FP32 output only): k_parts = 2
-  // runs every tile twice, workgroup 2t + j on chunks [j * chunks, (j + 1) *
-  // chunks) writing its partial sums at y + j * part_stride floats.
+  // K split across workgroups (LDS kernel, FP32 output only): every tile runs
+  // k_parts times, each on its own run of chunks, part j writing its partial
+  // sums at y + j * part_stride floats.
   uint32_t k_parts, part_stride;
   // GDN gate epilogue (split-K kernel only): H b-columns, then H a-columns.
   const float* gate_a_log;
@@ -166,19 +166,29 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// Tile (tm, tn) of workgroup blockIdx.x: XCD-contiguous remap (workgroup i
-// runs on XCD i % 8), then M-grouped order (kGroupM tiles of M per group).
-template <int kGroupM>
-__device__ __forceinline__ void tile_of(const GemmParams& p, uint32_t& tm, uint32_t& tn,
-                                        uint32_t pid0 = blockIdx.x) {
-  const uint32_t total = p.tiles_m * p.tiles_n;
+// Work item of workgroup blockIdx.x of `total`: workgroup i runs on XCD i % 8,
+// and each XCD takes a contiguous range of items.
+__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t total) {
+  const uint32_t pid0 = blockIdx.x;
   const uint32_t xcd = pid0 % kNumXcd, per = total / kNumXcd, extra = total % kNumXcd;
-  const uint32_t pid = xcd * per + (xcd < extra ? xcd : extra) + pid0 / kNumXcd;
+  return xcd * per + (xcd < extra ? xcd : extra) + pid0 / kNumXcd;
+}
+
+// Tile (tm, tn) at position pid of the M-grouped order (kGroupM tiles of M
+// per group).
+template <int kGroupM>
+__device__ __forceinline__ void tile_at(const GemmParams& p, uint32_t pid, uint32_t& tm, uint32_t& tn) {
   const uint32_t in_group = kGroupM * p.tiles_n;
   const uint32_t first_m = (pid / in_group) * kGroupM;
   const uint32_t gm = (p.tiles_m - first_m) < (uint32_t)kGroupM ? (p.tiles_m - first_m) : (uint32_t)kGroupM;
   tm = first_m + (pid % in_group) % gm;
   tn = (pid % in_group) / gm;
+}
+
+// Tile of workgroup blockIdx.x.
+template <int kGroupM>
+__device__ __forceinline__ void tile_of(const GemmParams& p, uint32_t& tm, uint32_t& tn) {
+  tile_at<kGroupM>(p, xcd_contiguous(p.tiles_m * p.tiles_n), tm, tn);
 }
 
 // Epilogue: y = acc / (G_A * G_W[s]) for the segment s of each column, BF16
@@ -409,18 +419,19 @@ constexpr uint64_t kMallBytes = 256ull << 20;
 constexpr uint32_t kSquareTile = 256;
 
 // The kernels one nvfp4_gemm call launches: `first` over output columns
-// [0, n_split), then `second` (if any) over [n_split, N).
+// [0, n_split), in k_parts runs of K (with k_parts > 1: FP32 partial sums,
+// then sum_parts), then `second` (if any) over [n_split, N).
 struct GemmPlan {
   enum Kind { kNone = 0, kLdsSquare, kLdsSuper, kLdsTall, kSplitkNarrow, kSplitkDecode, kReg, kLdsSuperHalves,
-              kSplitkDecodeFew };
+              kSplitkDecodeFew, kLdsMid, kLdsMidSuper, kLdsLow, kLdsLowSuper };
   int first, second;
-  uint32_t n_split;
+  uint32_t n_split, k_parts;
 };
-// with_ws: the caller provides gemm_workspace_bytes of workspace (the last
-// round's tile columns may then run as two K halves on twice the CUs).
+// with_ws: the caller provides gemm_workspace_bytes of workspace (tiles may
+// then run as several K parts).
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws);
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N);
-const char* gemm_kernel_name(int kind);
+const char* gemm_kernel_name(int kind, bool parts);
 
 // Launchers of the kernel families (each in its own translation unit).
 // Prefill tiles over output columns [n_begin, n_end) (n_begin a multiple of 32).
@@ -430,14 +441,19 @@ hipError_t launch_lds_super_bf16(const GemmOperands& o, GemmParams p, uint32_t n
                                  hipStream_t stream);
 hipError_t launch_lds_super_f32(const GemmOperands& o, GemmParams p, uint32_t n_begin, uint32_t n_end,
                                 hipStream_t stream);
-// The same kernel over columns [n_begin, n_end) with the K range split in
-// two halves (p.chunks % 8 == 0): FP32 partial sums (segment-scaled) to
-// parts[2][M][halves_row(n_end - n_begin)]; sum_halves then forms Y.
-inline uint32_t halves_row(uint32_t width) { return (width + 3u) & ~3u; }
-hipError_t launch_lds_super_halves(const GemmOperands& o, GemmParams p, uint32_t n_begin, uint32_t n_end,
-                                   float* parts, hipStream_t stream);
-hipError_t launch_sum_halves(const float* parts, uint32_t M, uint32_t width, void* y, uint32_t ldy, uint32_t col0,
-                             bool out_f32, hipStream_t stream);
+// K parts of every tile (see launch_lds_parts in gemm_lds.h), and the pass
+// that sums them.
+inline uint32_t parts_row(uint32_t width) { return (width + 3u) & ~3u; }
+hipError_t launch_lds_super_parts(const GemmOperands& o, const GemmParams& p, uint32_t n_begin, uint32_t n_end,
+                                  uint32_t k_parts, float* parts, hipStream_t stream);
+hipError_t launch_sum_parts(const float* parts, uint32_t k_parts, uint32_t M, uint32_t width, void* y, uint32_t ldy,
+                            uint32_t col0, bool out_f32, hipStream_t stream);
+// 128 x 128 and 64 x 256 tiles over all columns, with scale super-stages
+// (K % 256 == 0) or without; k_parts > 1: partial sums to `parts`.
+hipError_t launch_lds_mid(const GemmOperands& o, const GemmParams& p, bool super, uint32_t k_parts, float* parts,
+                          bool out_f32, hipStream_t stream);
+hipError_t launch_lds_low(const GemmOperands& o, const GemmParams& p, bool super, uint32_t k_parts, float* parts,
+                          bool out_f32, hipStream_t stream);
 hipError_t launch_lds_tall(const GemmOperands& o, GemmParams p, uint32_t n_begin, uint32_t n_end, bool out_f32,
                            hipStream_t stream);
 // Split-K: 64 x 96 tiles (N <= 96, optional GDN gate epilogue); M <= 32:

@@ -21,8 +21,11 @@ struct LdsCfg {
   static constexpr int kWaves = WM * WN, kThreads = kWaves * 64;
   static constexpr int BM = WM * FM * 32, BN = WN * FN * 32;
   static constexpr int NFA = WM * FM, NFB = WN * FN;         // fragments per workgroup
-  // Each wave moves the same number of A and B fragments (codes + scales).
-  static constexpr int kAPerWave = NFA / kWaves, kBPerWave = NFB / kWaves;
+  // Each wave moves the same number of A and B fragments (codes + scales);
+  // with fewer fragments than waves, several waves move the same one (the
+  // same bytes to the same place).
+  static constexpr int kAPerWave = NFA >= kWaves ? NFA / kWaves : 1;
+  static constexpr int kBPerWave = NFB >= kWaves ? NFB / kWaves : 1;
   // Scales: one dword of 4 block scales per fragment row and chunk.  With an
   // even count per wave, one DMA moves the scales of two fragments (64
   // distinct rows, 128 B per fragment slot); with an odd count, one DMA per
@@ -48,10 +51,17 @@ struct LdsCfg {
   // columns, rows padded by 16 bytes.
   static constexpr int kEpiPitch = FN * 32 * 2 + 16;
   static constexpr int kEpiBytes = kWaves * 32 * kEpiPitch;
+  // Where that area would cost a workgroup per CU, the staging uses the ring
+  // instead (after a barrier, which the other workgroups cover).
+  static constexpr bool kEpiInRing = kOcc * (kLdsBytes + kEpiBytes) > 160 * 1024;
+  static constexpr int kEpiBase = kEpiInRing ? 0 : kLdsBytes;
+  static constexpr int kLdsTotal = kEpiInRing ? kLdsBytes : kLdsBytes + kEpiBytes;   // bf16 output
+  static_assert(!kEpiInRing || kEpiBytes <= kLdsBytes, "staging fits the ring");
   // DMA loads per chunk and wave (without the super-stage loads).
   static constexpr int kLoadsPerWave = kAPerWave + kBPerWave + (kSuper ? 0 : kSDmaA + kSDmaB);
   static constexpr int kSuperLoads = 2;          // per 4 chunks: one A pair, one W pair
-  static_assert(!kSuper || (kAPerWave == 2 && kBPerWave == 2 && kStages == 4), "super-stage layout");
+  static_assert(!kSuper || (kAPerWave <= 2 && kBPerWave <= 2 && NFA % 2 == 0 && NFB % 2 == 0 && kStages == 4),
+                "super-stage layout");
   static constexpr int kGroupM = 4;
   static constexpr int kMfma = 4 * FM * FN;                   // MFMAs per chunk and wave
   static constexpr int kValuPerMfma = kValu_;                 // schedule: VALU slots after each MFMA
@@ -64,9 +74,9 @@ struct LdsCfg {
   static constexpr int kWaitSuper0 = lds::vmcnt_imm(2 * kLoadsPerWave);                // c % 4 in {0, 3}
   static constexpr int kWaitSuper1 = lds::vmcnt_imm(2 * kLoadsPerWave + kSuperLoads);  // c % 4 in {1, 2}
   static_assert(kStages >= 2 && (kStages - 1) * kLoadsPerWave < 64, "ring depth");
-  static_assert(NFA % kWaves == 0 && NFB % kWaves == 0 && kAPerWave > 0 && kBPerWave > 0, "load split");
+  static_assert((NFA % kWaves == 0 || kWaves % NFA == 0) && (NFB % kWaves == 0 || kWaves % NFB == 0), "load split");
   static_assert(kLdsReads <= kMfma / 2 && kLoadsPerWave <= kMfma, "schedule slots");
-  static_assert(kOcc * (kLdsBytes + kEpiBytes) <= 160 * 1024, "LDS per CU");
+  static_assert(kOcc * kLdsTotal <= 160 * 1024, "LDS per CU");
 };
 
 // The launched shape: 256 x 256 workgroups of 2 x 2 waves, each wave a
@@ -82,6 +92,17 @@ typedef LdsCfg<2, 2, 4, 4, 1, 5, 4, true> LdsSquareSuper;
 // tail of a launch whose last round of square tiles would be at most half
 // full (see launch_gemm).
 typedef LdsCfg<2, 2, 4, 2, 2, 5, 4> LdsTall;
+// Small tiles, two workgroups per CU, for outputs with too few 256 x 256
+// tiles (see plan_gemm): 128 x 128 workgroups of 2 x 2 waves, and 64 x 256
+// workgroups of 1 x 4 waves for up to 64 rows and ragged row counts; both
+// have 2 x 2 fragments per wave (8 decode VALU per MFMA, which with two
+// waves per SIMD costs 21 ns per MFMA against 16.3 ns for the MFMA alone).
+// 128 x 256 (2 x 4 fragments per wave, 6 VALU per MFMA) measured the same
+// per MFMA and balances worse.
+typedef LdsCfg<2, 2, 2, 2, 2, 9, 4> LdsMid;
+typedef LdsCfg<2, 2, 2, 2, 2, 9, 4, true> LdsMidSuper;
+typedef LdsCfg<1, 4, 2, 2, 2, 9, 4> LdsLow;
+typedef LdsCfg<1, 4, 2, 2, 2, 9, 4, true> LdsLowSuper;
 static_assert(LdsSquare::BM == kSquareTile && LdsSquare::BN == kSquareTile && LdsSquareSuper::BN == kSquareTile,
               "square tile of the dispatch");
 
@@ -228,13 +249,23 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const uint32_t lane = threadIdx.x & 63, wave = wave_index();
   const uint32_t r = lane & 31, h = lane >> 5;
-  // K split (FP32 partial sums): workgroup 2t + part takes chunks
-  // [part * chunks, (part + 1) * chunks) of tile t; the descriptors' bases
-  // move to the first of them, the row strides stay those of the whole K.
-  const uint32_t part = p.k_parts > 1 ? (blockIdx.x & 1u) : 0u;
-  const uint32_t kc0 = part * p.chunks;
-  uint32_t tm, tn;
-  tile_of<C::kGroupM>(p, tm, tn, p.k_parts > 1 ? blockIdx.x >> 1 : blockIdx.x);
+  // K split (FP32 partial sums): part j of a tile takes the j-th of k_parts
+  // nearly equal runs of whole groups of kUnit chunks; the descriptors' bases
+  // move to its first chunk, the row strides stay those of the whole K.
+  // Consecutive workgroups of an XCD take different tiles of one part (they
+  // read the same K range of A and W, and so share them in the XCD's L2).
+  constexpr uint32_t kUnit = C::kSuper ? 4 : 1;
+  uint32_t part = 0, kc0 = 0, chunks = p.chunks, tm, tn;
+  if (kF32Out && p.k_parts > 1) {
+    const uint32_t tiles = p.tiles_m * p.tiles_n, units = p.chunks / kUnit;
+    const uint32_t pid = xcd_contiguous(tiles * p.k_parts);
+    part = pid / tiles;
+    kc0 = part * units / p.k_parts * kUnit;
+    chunks = (part + 1) * units / p.k_parts * kUnit - kc0;
+    tile_at<C::kGroupM>(p, pid - part * tiles, tm, tn);
+  } else {
+    tile_of<C::kGroupM>(p, tm, tn);
+  }
   const uint32_t wm = wave / WN, wn = wave % WN;
 
   // Per-lane offsets are fixed; the chunk advances the descriptors' base
@@ -243,7 +274,7 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   // Scale DMA j: lane (h, r) loads the scale dword of row r of fragment
   // j * 2 + h of the wave's pair (paired), or of fragment j (single).
   uint32_t a_off[kAPerWave], as_off[C::kSDmaA], b_off[kBPerWave], bs_off[C::kSDmaB];
-  const uint32_t fa0 = kAPerWave * wave, fb0 = kBPerWave * wave;   // first fragment this wave loads
+  const uint32_t fa0 = kAPerWave * wave % C::NFA, fb0 = kBPerWave * wave % C::NFB;   // first fragment this wave loads
   const uint32_t nt0 = (p.n_off >> 5) + tn * (BN / 32);             // first weight tile of the tile
 #pragma unroll
   for (int i = 0; i < kAPerWave; ++i) {
@@ -277,7 +308,7 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   // last chunk so that every address stays inside its tensor.
   auto issue = [&](uint32_t kc) {
     uint8_t* st = smem + (kc % kStages) * kStageBytes;
-    const uint32_t kq = kc < p.chunks ? kc : p.chunks - 1;
+    const uint32_t kq = kc < chunks ? kc : chunks - 1;
 #pragma unroll
     for (int i = 0; i < kAPerWave; ++i) dma16(ra, st + kA + (fa0 + i) * 1024, a_off[i], kq * 32u);
     if constexpr (!C::kSuper) {
@@ -294,24 +325,25 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
     }
   };
   // Super-stage sg (the scales of chunks 4 sg .. 4 sg + 3) into buffer
-  // sg % 2: lane (h, r) loads row r of the wave's A fragment fa0 + h (16
-  // bytes: 4 chunks of one row) and 16 bytes (rows 4 (r % 8) .., chunk r / 8)
-  // of the 512-byte group of weight tile fb0 + h.  Groups past the end of K
-  // re-load the last one.
+  // sg % 2: lane (h, r) loads row r of A fragment fap + h of the wave's pair
+  // (16 bytes: 4 chunks of one row) and 16 bytes (rows 4 (r % 8) .., chunk
+  // r / 8) of the 512-byte group of weight tile fbp + h.  Groups past the end
+  // of K re-load the last one.
+  const uint32_t fap = fa0 & ~1u, fbp = fb0 & ~1u;
   const uint32_t a_sup_off = [&]() {
-    const uint32_t row = tm * BM + (fa0 + h) * 32 + r;
+    const uint32_t row = tm * BM + (fap + h) * 32 + r;
     return row < p.M ? row * (p.K >> 4) : kOOB;
   }();
   const uint32_t b_sup_off = [&]() {
-    const uint32_t nt = nt0 + fb0 + h;
+    const uint32_t nt = nt0 + fbp + h;
     return nt < p.w_tiles ? nt * p.w_kc * 128u + r * 16u : kOOB;
   }();
   auto issue_super = [&](uint32_t sg) {
     uint8_t* sb = smem + C::kSuperBase + (sg & 1u) * C::kSuperBytes;
-    const uint32_t last = (p.chunks >> 2) - 1;
+    const uint32_t last = (chunks >> 2) - 1;
     const uint32_t sq = sg < last ? sg : last;
-    dma16(rs, sb + fa0 * 512, a_sup_off, sq * 16u);
-    dma16(rbs, sb + C::kSuperB + fb0 * 512, b_sup_off, sq * 512u);
+    dma16(rs, sb + fap * 512, a_sup_off, sq * 16u);
+    dma16(rbs, sb + C::kSuperB + fbp * 512, b_sup_off, sq * 512u);
   };
 
   struct Regs {
@@ -457,15 +489,15 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   scales(cur);
   decode_step(cur, 0, 0);
   if constexpr (C::kSuper) {
-    // p.chunks % 4 == 0 (K % 256 == 0).
-    for (uint32_t c = 0; c < p.chunks; c += 4) {
+    // chunks % 4 == 0 (K % 256 == 0, parts of whole groups).
+    for (uint32_t c = 0; c < chunks; c += 4) {
       step(c, cur, nxt, Pos0{});
       step(c + 1, nxt, cur, Pos1{});
       step(c + 2, cur, nxt, Pos2{});
       step(c + 3, nxt, cur, Pos3{});
     }
   } else {
-    for (uint32_t c = 0; c < p.chunks; ++c) {
+    for (uint32_t c = 0; c < chunks; ++c) {
       step(c, cur, nxt, Pos0{});
       cur = nxt;
     }
@@ -475,8 +507,9 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   void* yo = kF32Out ? static_cast<void*>(static_cast<float*>(y) + (size_t)part * p.part_stride) : y;
   if constexpr (kTransposed) {
     constexpr int kPitch = C::kEpiPitch;
+    if constexpr (C::kEpiInRing) __syncthreads();            // every wave has left the ring
     store_tile_t<FM, FN, kPitch>(acc, p, ep, a_g, w_g, yo, m0_wave, n0_wave, lane,
-                                 smem + C::kLdsBytes + wave * 32 * kPitch);
+                                 smem + C::kEpiBase + wave * 32 * kPitch);
   } else {
     store_tile<FM, FN, kF32Out>(acc, p, a_g, w_g, yo, m0_wave, n0_wave, r, h);
   }
@@ -490,10 +523,27 @@ static hipError_t launch_lds_as(const GemmOperands& o, GemmParams p, uint32_t n_
   p.tiles_m = (p.M + C::BM - 1) / C::BM;
   p.tiles_n = (n_end - n_begin + C::BN - 1) / C::BN;
   const dim3 grid(p.tiles_m * p.tiles_n * p.k_parts), block(C::kThreads);
-  const uint32_t lds = C::kLdsBytes + (kF32Out ? 0 : C::kEpiBytes);
+  const uint32_t lds = kF32Out ? C::kLdsBytes : C::kLdsTotal;
   hipLaunchKernelGGL((gemm_lds_kernel<C, kF32Out>), grid, block, lds, stream, o.a_codes, o.a_scales, o.a_g,
                      o.w_packed, o.w_g, o.y, p);
   return hipGetLastError();
+}
+
+// Output columns [n_begin, n_end) as k_parts runs of K per tile (whole groups
+// of 4 chunks with super-stages): segment-scaled FP32 partial sums into
+// parts[k_parts][M][parts_row(n_end - n_begin)], for sum_parts_kernel.
+template <class C>
+static hipError_t launch_lds_parts(const GemmOperands& o, GemmParams p, uint32_t n_begin, uint32_t n_end,
+                                   uint32_t k_parts, float* parts, hipStream_t stream) {
+  const uint32_t ldp = parts_row(n_end - n_begin);
+  p.k_parts = k_parts;
+  p.part_stride = p.M * ldp;
+  p.ldy = ldp;
+  GemmOperands q = o;
+  // The kernel stores column c at y[row * ldy + c]: shift the base so that
+  // column n_begin lands at parts[row * ldp].
+  q.y = reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(parts) - (uintptr_t)n_begin * sizeof(float));
+  return launch_lds_as<C, true>(q, p, n_begin, n_end, stream);
 }
 
 template <class C>

@@ -51,9 +51,15 @@ hipError_t launch_harmonize_weight(void* packed, int64_t N, int64_t K, const int
                                    int n_seg, const float* g_enc_seg, float* g_shared,
                                    hipStream_t stream);
 
-// nvfp4_gemm and nvfp4_gemm_with_workspace: workspace may be null (then
-// workspace_bytes is ignored); a workspace of gemm_workspace_bytes(M, N, K)
-// bytes or more enables the K-halves form of a partial last round.
+// nvfp4_gemm (workspace null, workspace_bytes kNoWorkspace) and
+// nvfp4_gemm_with_workspace (workspace_bytes 0 with a null workspace).  A
+// workspace of gemm_workspace_bytes(M, N, K) bytes or more enables the K
+// parts of the shape's plan.  With less, the call falls back: to the K-halves
+// form of a partial last round where that applies (which requires its
+// workspace: kWorkspaceTooSmall if that is missing too), else to tiles over
+// the whole of K.
+constexpr size_t kNoWorkspace = (size_t)-1;
+constexpr hipError_t kWorkspaceTooSmall = hipErrorTbd;   // a marker that no HIP call returns
 hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const float* a_g,
                        int64_t M, int64_t K, const void* w_packed, int64_t N,
                        const int64_t* seg_offsets, int n_seg, const float* w_g, void* y,

@@ -1,0 +1,78 @@
+"""GPU parity of the GEMM's small tiles (128 x 128, 64 x 256) and of tiles
+split over several K parts, at the edges of the tiles and of the parts, against
+the CPU oracle; tolerance as in tests/gpu_common.py (FP32 sums, any order)."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import gemm as OG
+from oracle import quant as OQ
+from paper_2609_04098_amd import linear as L
+from paper_2609_04098_amd import nvfp4 as C
+from paper_2609_04098_amd import synth
+from tests.gpu_common import bf16_rne_of, check_gemm, log, to_dev_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(m, n, k, offs, ldy):
+    rng = np.random.default_rng(m * 13 + n * 5 + k)
+    x = rng.standard_normal((m, k))
+    x[:, rng.choice(k, max(1, k // 200), replace=False)] *= 100.0
+    xb = synth.f64_to_bf16_bits(x)
+    wb = synth.f64_to_bf16_bits(rng.standard_normal((n, k)) * 0.02)
+    aq = L.quantize_act(to_dev_bf16(xb))
+    pw = L.pack_weight(to_dev_bf16(wb), offs)
+    need = C.nvfp4_gemm_workspace(m, n, k)
+    guard = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    out = {}
+    for dtype in (torch.float32, torch.bfloat16):
+        big = torch.full((m + 1, ldy), -7.0, dtype=dtype, device="cuda")
+        y = big[:m, :n]
+        L.gemm(aq, pw, out=y, workspace=guard[:need] if need else None)
+        torch.cuda.synchronize()
+        assert bool((big[:m, n:] == -7.0).all()) and bool((big[m] == -7.0).all())
+        out[dtype] = y.contiguous()
+    assert bool((guard[need:] == 0x5A).all()), "written past the workspace"
+    y_nows = L.gemm_no_workspace(aq, pw, out_dtype=torch.float32)
+    xp, xs, gx = OQ.quantize_tensor(xb)
+    wp, ws, gw = OQ.quantize_segments(wb, offs)
+    y_ref = OG.gemm_f64(xp, xs, gx, wp, ws, gw, offs)
+    r_ref = OG.abs_bound(xp, xs, gx, wp, ws, gw, offs)
+    check_gemm(out[torch.float32].cpu().numpy().astype(np.float64), y_ref, r_ref, "%dx%dx%d" % (m, n, k))
+    check_gemm(y_nows.cpu().numpy().astype(np.float64), y_ref, r_ref, "%dx%dx%d no workspace" % (m, n, k))
+    np.testing.assert_array_equal(out[torch.bfloat16].view(torch.int16).cpu().numpy().view(np.uint16),
+                                  bf16_rne_of(out[torch.float32]))
+    return need, aq, pw
+
+
+@pytest.mark.parametrize("m,n,k,offs,ldy", [
+    (33, 97, 64, [0, 97], 97),                       # one chunk, one partial tile
+    (64, 256, 320, [0, 256], 256),                   # one 64 x 256 tile, K % 256 != 0
+    (65, 257, 576, [0, 100, 257], 264),              # one past a tile in both directions, 9 chunks
+    (128, 128, 1024, [0, 128], 128),                 # one 128 x 128 tile
+    (129, 385, 2048, [0, 128, 385], 392),            # ragged tiles, 8 groups of chunks in several K parts
+    (200, 515, 4352, [0, 256, 515], 515),            # 17 groups of chunks: parts of different length, odd row stride
+    (200, 320, 4416, [0, 320], 320),                 # 69 chunks, K % 256 != 0: parts of single chunks
+    (100, 2600, 5120, [0, 1300, 2600], 2600),        # segment boundary inside a tile
+    (40, 1000, 17408, [0, 1000], 1000),              # long K, many parts
+    (600, 1100, 1280, [0, 1100], 1104),              # more rows than columns of tiles
+])
+def test_gemm_tiles_and_k_parts(m, n, k, offs, ldy):
+    need, _, _ = _case(m, n, k, offs, ldy)
+    log("%dx%dx%d: %s, workspace %d" % (m, n, k, L.gemm_kernels(m, n, k), need))
+
+
+def test_gemm_k_parts_without_their_workspace():
+    """A workspace short of the K parts' (or none) gives the nvfp4_gemm result."""
+    need, aq, pw = _case(70, 300, 8192, [0, 300], 300)
+    assert need > 0
+    y0 = L.gemm_no_workspace(aq, pw, out_dtype=torch.float32)
+    y1 = torch.empty_like(y0)
+    L.gemm(aq, pw, out=y1, workspace=torch.empty(need - 16, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(y0, y1)
+    y2 = torch.empty_like(y0)
+    C.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y2, C.NVFP4_F32,
+                                None, None, M=aq.m, K=aq.k)
+    assert torch.equal(y0, y2)
