@@ -13,8 +13,7 @@ std::once_flag g_cu_once[kMaxDevices];
 int g_cu_count[kMaxDevices];
 }  // namespace
 
-// Compute units of the current device (cached per device, thread-safe).
-static uint32_t cu_count() {
+uint32_t cu_count() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
   std::call_once(g_cu_once[dev], [dev]() {
@@ -35,20 +34,34 @@ struct TileCost {
   uint32_t bm, bn;
   float chunk_us, chunk_us_super;   // one 64-deep chunk of a tile
   float fixed_us;                   // first loads, epilogue, launch
+  uint32_t max_parts;               // K parts the launcher offers (with super-stages; square: only with them)
 };
-// Measured at 200 x 5120 x 17408, 1000 x 8192 x 5120 and 300 x 5120 x 4352.
+// Fitted, on one box, to M = 50 .. 1000 against N = 4352 .. 34816 at K = 5120,
+// to N = 5120 at K = 2176 .. 17408, and for the square tile to larger M.  The
+// split-K tiles (four waves share a tile's reduction and meet in LDS) have
+// the cheaper small tile, the LDS tiles the cheaper large one and K parts.
 constexpr TileCost kTileCosts[] = {
-    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.60f, 1.46f, 7.0f},
-    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.51f, 0.46f, 5.0f},
-    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.51f, 0.46f, 5.0f},
+    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.60f, 1.46f, 7.5f, 32},
+    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.51f, 0.45f, 7.0f, 32},
+    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.51f, 0.45f, 7.0f, 32},
+    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.19f, 0.19f, 8.0f, 1},
+    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.155f, 0.155f, 6.0f, 1},
+    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.09f, 0.09f, 5.0f, 1},
+    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1},
 };
 // The summing pass: a launch, and every partial sum written and read once
 // (they stay in the last-level cache).
 constexpr float kSumLaunchUs = 2.5f, kPartBytesPerUs = 8.0e6f;
 // Bound on the partial sums of one call.
 constexpr uint64_t kMaxPartBytes = 128ull << 20;
-constexpr uint32_t kMaxParts = 32;
 constexpr uint32_t kMinPartChunks = 4;   // one group of chunks with super-stages
+
+// The split-K tiles are offered where their costs were fitted: a batch of up
+// to 1024 rows, at most 5 rounds of tiles (100 x 34816 x 5120 with 32 x 64
+// tiles, 9 rounds, took 75 us for an estimate of 70; the LDS tiles, which share
+// each operand between their waves, are the better ones there).
+constexpr int64_t kSplitkMaxRows = 1024;
+constexpr uint64_t kSplitkMaxRounds = 5;
 
 // Below this K the K-halves / tall-tile form of the last round is kept as
 // it is: the cost of a tile is then mostly its first loads and epilogue.
@@ -63,7 +76,8 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
   for (const TileCost& t : kTileCosts) {
     const bool square = t.kind == GemmPlan::kLdsSquare;
     const uint64_t tiles = (uint64_t)((M + t.bm - 1) / t.bm) * (uint64_t)((N + t.bn - 1) / t.bn);
-    for (uint32_t parts = 1; parts <= kMaxParts; ++parts) {
+    if (t.kind == t.super_kind && (M > kSplitkMaxRows || tiles > kSplitkMaxRounds * n_cu)) continue;   // split-K tile
+    for (uint32_t parts = 1; parts <= t.max_parts; ++parts) {
       const uint64_t part_bytes = (uint64_t)parts * (uint64_t)M * parts_row((uint32_t)N) * sizeof(float);
       if (parts > 1 && (!with_ws || units * unit < parts * kMinPartChunks || part_bytes > kMaxPartBytes ||
                         (square && !super)))
@@ -116,7 +130,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
   if (aligned && N <= 96) {
     g.first = GemmPlan::kSplitkNarrow;
   } else if (aligned && M <= 32) {
-    g.first = M <= 8 ? GemmPlan::kSplitkDecodeFew : GemmPlan::kSplitkDecode;
+    g.first = GemmPlan::kSplitkDecode;
   } else if (aligned) {
     g = plan_square(M, N, K, n_cu, with_ws);
     const bool tail = g.second != GemmPlan::kNone;
@@ -165,11 +179,32 @@ const char* gemm_kernel_name(int kind, bool parts) {
     case GemmPlan::kLdsTall: return "gemm_lds_kernel<LdsTall> (256x128 tiles)";
     case GemmPlan::kLdsSuperHalves:
       return "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, two K halves, FP32 partials) + sum_parts_kernel";
-    case GemmPlan::kSplitkNarrow: return "gemm_splitk_kernel<4,2,3,3> (64x96 tiles, split-K)";
-    case GemmPlan::kSplitkDecode: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";
-    case GemmPlan::kSplitkDecodeFew: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
+    case GemmPlan::kSplitk32x32: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
+    case GemmPlan::kSplitk32x64: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";
+    case GemmPlan::kSplitk64x64: return "gemm_splitk_kernel<4,2,2,3> (64x64 tiles, split-K)";
+    case GemmPlan::kSplitk64x96: return "gemm_splitk_kernel<4,2,3,3> (64x96 tiles, split-K)";
     case GemmPlan::kReg: return "gemm_reg_kernel<2,2,4,4> (256x256 tiles, register path)";
     default: return "none";
+  }
+}
+
+static const char* decode_kernel_name(DecodeShape d) {
+  switch (d) {
+    case DecodeShape::k4Private: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
+    case DecodeShape::k8Private: return "gemm_splitk_kernel<8,1,1,3> (32x32 tiles, split-K, per-wave rings)";
+    case DecodeShape::k16Private: return "gemm_splitk_kernel<16,1,1,3> (32x32 tiles, split-K, per-wave rings)";
+    case DecodeShape::k4Shared: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, shared activation ring)";
+    case DecodeShape::k8Shared: return "gemm_splitk_kernel<8,1,1,4> (32x32 tiles, split-K, shared activation ring)";
+    default: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";
+  }
+}
+
+static const char* narrow_kernel_name(int fragments) {
+  switch (fragments) {
+    case 1: return "gemm_splitk_kernel<8,1,1,3> (32x32 tiles, split-K, shared activation ring)";
+    case 2: return "gemm_splitk_kernel<8,1,2,3> (32x64 tiles, split-K, shared activation ring)";
+    case 3: return "gemm_splitk_kernel<8,1,3,3> (32x96 tiles, split-K, shared activation ring)";
+    default: return "gemm_splitk_kernel<4,2,3,3> (64x96 tiles, split-K)";
   }
 }
 
@@ -178,6 +213,8 @@ const char* gemm_kernel_for(int64_t M, int64_t N, int64_t K, int part, bool with
   if (n_cu == 0) return nullptr;
   const GemmPlan g = plan_gemm(M, N, K, n_cu, with_ws);
   const int kind = part == 0 ? g.first : g.second;
+  if (kind == GemmPlan::kSplitkDecode) return decode_kernel_name(decode_shape(M, N, K, n_cu));
+  if (kind == GemmPlan::kSplitkNarrow) return narrow_kernel_name(narrow_fragments(M, N, n_cu));
   return kind == GemmPlan::kNone ? nullptr : gemm_kernel_name(kind, part == 0 && g.k_parts > 1);
 }
 
@@ -194,8 +231,11 @@ static hipError_t run_one(int kind, const GemmOperands& o, const GemmParams& p, 
     case GemmPlan::kLdsLowSuper: return launch_lds_low(o, p, kind == GemmPlan::kLdsLowSuper, 1, nullptr, out_f32, stream);
     case GemmPlan::kLdsTall: return launch_lds_tall(o, p, n_begin, n_end, out_f32, stream);
     case GemmPlan::kSplitkNarrow: return launch_splitk_narrow(o, p, out_f32, false, stream);
-    case GemmPlan::kSplitkDecode:
-    case GemmPlan::kSplitkDecodeFew: return launch_splitk_decode(o, p, out_f32, stream);
+    case GemmPlan::kSplitk32x32:
+    case GemmPlan::kSplitk32x64:
+    case GemmPlan::kSplitk64x64:
+    case GemmPlan::kSplitk64x96: return launch_splitk_tile(o, p, kind, out_f32, stream);
+    case GemmPlan::kSplitkDecode: return launch_splitk_decode(o, p, out_f32, stream);
     case GemmPlan::kReg: return launch_reg_square(o, p, out_f32, aligned, stream);
     default: return hipSuccess;
   }

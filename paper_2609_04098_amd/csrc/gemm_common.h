@@ -287,11 +287,11 @@ __device__ __forceinline__ void segment_alpha(const GemmParams& p, float ga, con
 
 // Split-K epilogue: the KS waves' partial sums meet in LDS, kGroup fragments
 // at a time (part: kGroup x KS x 64 floatx16), and are summed in wave order
-// (deterministic).  Plain outputs: fragment f is summed and stored by wave
-// f % KS.  With the GDN gate transform (kGate), whose transcendentals
-// dominate the epilogue, every wave takes 16 / KS of each lane's 16
-// accumulator entries of every fragment instead, so that all waves share
-// that arithmetic.  Each value is scaled by its column's alpha.  LDS at part
+// (deterministic).  Plain outputs of 4 waves: fragment f is summed and stored
+// by wave f % KS.  With the GDN gate transform (kGate), whose transcendentals
+// dominate the epilogue, and with more waves, every wave takes 16 / KS of each
+// lane's 16 accumulator entries of every fragment instead, so that all waves
+// share that work.  Each value is scaled by its column's alpha.  LDS at part
 // must be free (a caller that used it for other data synchronizes first).
 template <int KS, int FM, int FN, int kGroup, bool kF32Out, bool kGate>
 __device__ __forceinline__ void splitk_epilogue(const floatx16 (&acc)[FM][FN], floatx16* part, const GemmParams& p,
@@ -299,6 +299,7 @@ __device__ __forceinline__ void splitk_epilogue(const floatx16 (&acc)[FM][FN], f
                                                 uint32_t m0, uint32_t n0, uint32_t wave, uint32_t lane) {
   static_assert(16 % KS == 0, "entries per wave");
   constexpr int kPer = 16 / KS, kFrags = FM * FN;
+  constexpr bool kSpread = kGate || KS > 4;
   const uint32_t r = lane & 31, h = lane >> 5;
   const float* partf = reinterpret_cast<const float*>(part);
   auto store = [&](float v, uint32_t row, uint32_t col) {
@@ -324,7 +325,7 @@ __device__ __forceinline__ void splitk_epilogue(const floatx16 (&acc)[FM][FN], f
       const int fa = f / FN, fb = f % FN;
       const uint32_t col = n0 + fb * 32 + r;
       const floatx16* pj = part + j * KS * 64;
-      if (kGate) {
+      if (kSpread) {
         const float* pf = partf + j * KS * 64 * 16;
 #pragma unroll
         for (int e = 0; e < kPer; ++e) {
@@ -371,12 +372,12 @@ struct SplitkAGroup {
   static constexpr int kLoadsPerWave = 2 * kSlicesPerWave;
 };
 
-// LDS of the split-K kernel: KS private weight rings, then the shared
-// activation ring (streamed activation) or nothing (the fused quantizer puts
+// LDS of the split-K kernel: KS private weight rings, then one shared
+// activation ring per 4 waves (streamed activation) or nothing (the fused quantizer puts
 // its activation after the rings).
 template <int KS, int FM, int FN, int kStages, bool kAShared>
 constexpr int splitk_ring_bytes() {
-  return KS * kStages * SplitkStage<0, FN>::kBytes + (kAShared ? kStages * SplitkAGroup<FM>::kBytes : 0);
+  return KS * kStages * SplitkStage<0, FN>::kBytes + (kAShared ? KS / 4 * kStages * SplitkAGroup<FM>::kBytes : 0);
 }
 
 // Operands of one GEMM call (device pointers), as passed to the launchers.
@@ -423,7 +424,8 @@ constexpr uint32_t kSquareTile = 256;
 // then sum_parts), then `second` (if any) over [n_split, N).
 struct GemmPlan {
   enum Kind { kNone = 0, kLdsSquare, kLdsSuper, kLdsTall, kSplitkNarrow, kSplitkDecode, kReg, kLdsSuperHalves,
-              kSplitkDecodeFew, kLdsMid, kLdsMidSuper, kLdsLow, kLdsLowSuper };
+              kLdsMid, kLdsMidSuper, kLdsLow, kLdsLowSuper, kSplitk32x32, kSplitk32x64, kSplitk64x64,
+              kSplitk64x96 };
   int first, second;
   uint32_t n_split, k_parts;
 };
@@ -432,6 +434,17 @@ struct GemmPlan {
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws);
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N);
 const char* gemm_kernel_name(int kind, bool parts);
+
+// Compute units of the current device (cached per device, thread-safe).
+uint32_t cu_count();
+
+// Split-K form of a decode shape (M <= 32): waves per tile, per-wave or
+// shared activation rings, one or (pair) two weight fragments per workgroup.
+enum class DecodeShape { k4Private, k8Private, k16Private, k4Shared, k4SharedPair, k8Shared };
+DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu);
+// Weight fragments (1..3) per 32-row tile of 8 waves for a tall-skinny output
+// (N <= 96), or 0: 64 x 96 tiles of 4 waves.
+int narrow_fragments(int64_t M, int64_t N, uint32_t n_cu);
 
 // Launchers of the kernel families (each in its own translation unit).
 // Prefill tiles over output columns [n_begin, n_end) (n_begin a multiple of 32).
@@ -456,17 +469,17 @@ hipError_t launch_lds_low(const GemmOperands& o, const GemmParams& p, bool super
                           bool out_f32, hipStream_t stream);
 hipError_t launch_lds_tall(const GemmOperands& o, GemmParams p, uint32_t n_begin, uint32_t n_end, bool out_f32,
                            hipStream_t stream);
-// Split-K: 64 x 96 tiles (N <= 96, optional GDN gate epilogue); M <= 32:
-// 32 x 32 tiles (M <= 8) or 32 x 64 tiles.
+// Split-K: tall-skinny outputs (N <= 96, optional GDN gate epilogue), decode
+// shapes (M <= 32), and the small tiles kSplitk* of plan_gemm.
 hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f32, bool gate, hipStream_t stream);
 hipError_t launch_splitk_decode(const GemmOperands& o, GemmParams p, bool out_f32, hipStream_t stream);
+hipError_t launch_splitk_tile(const GemmOperands& o, const GemmParams& p, int kind, bool out_f32, hipStream_t stream);
 // Largest activation (in 16-element blocks) the fused decode launch
 // quantizes inside every workgroup: 1024 blocks = M * K <= 16384 elements.
 constexpr uint32_t kDecodeFuseMaxBlocks = 1024;
 // Activation quantization fused in front of the M <= 32 split-K GEMM, one
 // launch, with the whole quantized activation held in LDS (see
-// gemm_splitk.hip); decode_quant_lds_bytes(M, K) is the dynamic LDS it takes
-// (the rings; the activation sits in a static 9 KB array).
+// gemm_splitk.hip).
 struct DecodeQuantArgs {
   const uint16_t* x;        // bf16 [M x K], row stride ldx elements
   uint32_t ldx;
@@ -474,7 +487,6 @@ struct DecodeQuantArgs {
   uint8_t* codes;           // optional outputs ([M x K/2], [M x K/16]), written by workgroup 0
   uint8_t* scales;
 };
-size_t decode_quant_lds_bytes(int64_t M, int64_t K);
 hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
                                     bool out_f32, hipStream_t stream);
 // Register path (K % 64 != 0).

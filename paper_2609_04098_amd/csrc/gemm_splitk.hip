@@ -166,7 +166,7 @@ __device__ __forceinline__ void wait_rem(int rem) {
 }
 
 template <int KS, int FM, int FN, int kStages, bool kF32Out, bool kGate, int kQuant = 0, bool kShareA = true>
-__global__ __launch_bounds__(KS * 64, 2) void gemm_splitk_kernel(const uint8_t* __restrict__ a_codes,
+__global__ __launch_bounds__(KS * 64, KS < 8 ? 2 : KS / 4) void gemm_splitk_kernel(const uint8_t* __restrict__ a_codes,
                                                              const uint8_t* __restrict__ a_scales,
                                                              const float* __restrict__ a_g,
                                                              const uint8_t* __restrict__ w_packed,
@@ -183,7 +183,8 @@ __global__ __launch_bounds__(KS * 64, 2) void gemm_splitk_kernel(const uint8_t* 
   constexpr bool kAShared = !kALds && kShareA;
   constexpr bool kAPrivate = !kALds && !kShareA;
   static_assert(!kALds || FM == 1, "LDS-resident activation: one 32-row fragment");
-  static_assert(KS == 4, "a step is one 128-byte line group (4 chunks) of every activation row");
+  static_assert(KS % 4 == 0, "a step is KS / 4 128-byte line groups (4 chunks each) of every activation row");
+  constexpr int G = KS / 4;                                  // groups of 4 waves, one line group each
   using L = SplitkStage<kAPrivate ? FM : 0, FN>;
   constexpr int kWOff = kAPrivate ? FM : 0;                  // first weight slot of a private stage
   using AG = SplitkAGroup<FM>;
@@ -199,39 +200,43 @@ __global__ __launch_bounds__(KS * 64, 2) void gemm_splitk_kernel(const uint8_t* 
   // chunk index, buffer descriptors and LDS addresses in scalar registers.
   const uint32_t lane = threadIdx.x & 63, wave = wave_index();
   const uint32_t r = lane & 31, h = lane >> 5;
+  const uint32_t grp = wave >> 2, gw = wave & 3u;            // group of 4 waves, wave in the group
   uint32_t tm, tn;
   tile_of<8>(p, tm, tn);
   const uint32_t m0 = tm * BM, n0 = tn * BN;
   constexpr int kRingBytes = splitk_ring_bytes<KS, FM, FN, kStages, kAShared>() +
                              (kAPrivate ? KS * kStages * (L::kBytes - SplitkStage<0, FN>::kBytes) : 0);
   uint8_t* ring = smem + wave * (kStages * kStageBytes);
-  uint8_t* a_ring = smem + KS * kStages * kStageBytes;       // shared activation ring (kAShared)
+  uint8_t* a_ring = smem + KS * kStages * kStageBytes + grp * (kStages * AG::kBytes);   // the group's (kAShared)
   const uint32_t n_steps = (p.chunks + KS - 1) / KS;
 
-  // Activation DMA of a step: wave w loads line-group slices q = w FM + t.
+  const uint32_t n_groups = (p.chunks + 3) / 4;              // line groups
+  // Activation DMA of a step i: group g takes line group i G + g, wave w of
+  // the group its slices q = w FM + t.
   // Codes, slice q: rows 8q .. 8q + 7 of the tile, 128 bytes each; lane l
   // takes 16-byte piece (l % 8) ^ (l / 8) ^ (q % 8) of row 8q + l / 8 and
   // lands at slot l (16 l) of the slice's 1 KB image, so that the 16 lanes
   // of one LDS read (rows r, the same piece) hit distinct banks.  Scales,
-  // slice q: lane l < 32 takes dword l % 4 (chunk 4i + l % 4) of row
+  // slice q: lane l < 32 takes dword l % 4 (chunk l % 4 of the line group) of row
   // 8q + l / 4 (4 l in the slice's 260-byte slot; lanes >= 32 read zeros).
   uint32_t ac_off[AG::kSlicesPerWave], as_off[AG::kSlicesPerWave];
 #pragma unroll
   for (int t = 0; t < AG::kSlicesPerWave; ++t) {
-    const uint32_t q = wave * AG::kSlicesPerWave + t;
+    const uint32_t q = gw * AG::kSlicesPerWave + t;
     const uint32_t row_c = m0 + 8 * q + (lane >> 3), piece = (lane & 7) ^ (lane >> 3) ^ (q & 7);
     ac_off[t] = (kAShared && row_c < p.M) ? row_c * (p.K >> 1) + piece * 16u : kOOB;
     const uint32_t row_s = m0 + 8 * q + (lane >> 2);
     as_off[t] = (kAShared && lane < 32 && row_s < p.M) ? row_s * (p.K >> 4) + (lane & 3) * 4u : kOOB;
   }
   // Where lane (h, r) finds its activation fragment f in a shared stage:
-  // row 32 f + r, piece 2 w + h (chunk 4i + w, bytes 16 h .. 16 h + 15).
+  // row 32 f + r, piece 2 w + h (chunk w of the line group, bytes 16 h ..
+  // 16 h + 15).
   uint32_t ar_code[FM], ar_scale[FM];
 #pragma unroll
   for (int f = 0; f < FM; ++f) {
     const uint32_t q = 4 * f + (r >> 3), rr = r & 7;
-    ar_code[f] = q * 1024u + (rr * 8u + ((2 * wave + h) ^ rr ^ (q & 7))) * 16u;
-    ar_scale[f] = AG::kScaleBase + q * AG::kScaleSlot + rr * 16u + wave * 4u;
+    ar_code[f] = q * 1024u + (rr * 8u + ((2 * gw + h) ^ rr ^ (q & 7))) * 16u;
+    ar_scale[f] = AG::kScaleBase + q * AG::kScaleSlot + rr * 16u + gw * 4u;
   }
   // Private-ring activation: fragment f's codes, lane (h, r) the 16 bytes
   // of row r for its chunk; scale DMA of fragment pair j, lane l the scale
@@ -268,23 +273,23 @@ __global__ __launch_bounds__(KS * 64, 2) void gemm_splitk_kernel(const uint8_t* 
   const __amdgpu_buffer_rsrc_t rs = rsrc(a_scales, p.a_scale_bytes);
   const __amdgpu_buffer_rsrc_t rb = rsrc(w_packed, p.w_scale_offset);
   const __amdgpu_buffer_rsrc_t rbs = rsrc(w_scales, w_scale_bytes);
-  // DMA of step i into stage i % kStages: this wave's share of the
-  // activation line group, and the weight fragments of its chunk 4i + w.
+  // DMA of step i into stage i % kStages: this wave's share of its group's
+  // activation line group, and the weight fragments of its chunk KS i + w.
   // (Loads of chunks past the end of K -- prologue loads when K is short, a
   // wave without a chunk in the last step -- re-load the last chunk or step
   // so that every address stays inside its tensor; they are never read.)
   auto issue_a = [&](uint32_t i) {
     if constexpr (kAShared) {
-      const uint32_t iq = i < n_steps ? i : n_steps - 1;
+      const uint32_t lg = i * G + grp, lq = lg < n_groups ? lg : n_groups - 1;
       uint8_t* st = a_ring + (i % kStages) * AG::kBytes;
 #pragma unroll
       for (int t = 0; t < AG::kSlicesPerWave; ++t) {
-        const uint32_t q = wave * AG::kSlicesPerWave + t;
-        dma16(ra, st + q * 1024, ac_off[t], iq * 128u);
+        const uint32_t q = gw * AG::kSlicesPerWave + t;
+        dma16(ra, st + q * 1024, ac_off[t], lq * 128u);
         // Scales of chunks past the end of K read zeros: a wave without a
         // chunk in the last step then multiplies zeros into its sums.
-        dma4(rs, st + AG::kScaleBase + q * AG::kScaleSlot, 4 * iq + (lane & 3) < p.chunks ? as_off[t] : kOOB,
-             iq * 16u);
+        dma4(rs, st + AG::kScaleBase + q * AG::kScaleSlot, 4 * lg + (lane & 3) < p.chunks ? as_off[t] : kOOB,
+             lq * 16u);
       }
     }
   };
@@ -470,68 +475,118 @@ __global__ __launch_bounds__(KS * 64, 2) void gemm_splitk_kernel(const uint8_t* 
 }
 
 template <int KS, int FM, int FN, int kStages, bool kShareA>
-static hipError_t launch_splitk(const GemmOperands& o, GemmParams p, bool out_f32, bool gate, hipStream_t stream) {
+constexpr int splitk_lds() {
+  return kShareA ? splitk_ring_bytes<KS, FM, FN, kStages, true>() : KS * kStages * SplitkStage<FM, FN>::kBytes;
+}
+
+template <int KS, int FM, int FN, int kStages, bool kShareA, bool kGate>
+static hipError_t launch_splitk(const GemmOperands& o, GemmParams p, bool out_f32, hipStream_t stream) {
   constexpr int BM = FM * 32, BN = FN * 32;
-  constexpr int kLds = kShareA ? splitk_ring_bytes<KS, FM, FN, kStages, true>()
-                               : KS * kStages * SplitkStage<FM, FN>::kBytes;
-  static_assert(kLds >= KS * 64 * 64 && 2 * kLds <= 160 * 1024, "the reduction reuses the rings; two per CU");
+  constexpr int kLds = splitk_lds<KS, FM, FN, kStages, kShareA>();
+  static_assert(kLds >= KS * 64 * 64 && kLds <= 160 * 1024 - 64, "the reduction reuses the rings; LDS per CU");
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
   const dim3 grid(p.tiles_m * p.tiles_n), block(KS * 64);
-#define NVFP4_SK(F32, GATE)                                                                                  \
-  hipLaunchKernelGGL((gemm_splitk_kernel<KS, FM, FN, kStages, F32, GATE, 0, kShareA>), grid, block, kLds, stream, \
+#define NVFP4_SK(F32)                                                                                         \
+  hipLaunchKernelGGL((gemm_splitk_kernel<KS, FM, FN, kStages, F32, kGate, 0, kShareA>), grid, block, kLds, stream, \
                      o.a_codes, o.a_scales, o.a_g, o.w_packed, o.w_g, o.y, p, DecodeQuantArgs{})
-  if (gate) {
-    if (out_f32) NVFP4_SK(true, true); else NVFP4_SK(false, true);
-  } else {
-    if (out_f32) NVFP4_SK(true, false); else NVFP4_SK(false, false);
-  }
+  if (out_f32) NVFP4_SK(true); else NVFP4_SK(false);
 #undef NVFP4_SK
   return hipGetLastError();
 }
 
-hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f32, bool gate, hipStream_t stream) {
-  return launch_splitk<4, 2, 3, 3, true>(o, p, out_f32, gate, stream);
+// Tall-skinny outputs (N <= 96).  While 32-row tiles leave CUs idle, eight
+// waves share the reduction of a 32-row tile of as few fragments as still
+// give every tile its own CU (gates at N = 96, K = 5120, same box: 1000 rows
+// 33.5 -> 10.4 us, 4000 rows 34.3 -> 14.8, 8000 rows 34.5 -> 20.6 against
+// 64 x 96 tiles of four waves, which keep 16 to 125 CUs busy); beyond that
+// 64 x 96 tiles (32768 rows: 53.8 us against 77.8 for 32 x 96).
+int narrow_fragments(int64_t M, int64_t N, uint32_t n_cu) {
+  const uint64_t rows = (uint64_t)((M + 31) / 32), frags = (uint64_t)((N + 31) / 32);
+  for (uint64_t f = 1; f <= 3; ++f)
+    if (rows * ((frags + f - 1) / f) <= n_cu) return (int)f;
+  return 0;
 }
 
-// Activations of at most kDecodePrivateRows rows take the private rings (no
-// barrier; their activation loads are a few rows of 32 bytes per chunk) and
-// one weight fragment per workgroup (twice the workgroups, five per CU: 1 and
-// 7 rows against the gate/up weight 30.6 -> 28.7 and 30.9 -> 29.1 us, same
-// box); more rows the shared line-group ring with two weight fragments (one
-// fragment would repeat the activation loads in twice the workgroups).  Each
-// output column's sum runs in the same order either way.
-constexpr uint32_t kDecodePrivateRows = 8;   // the kSplitkDecodeFew plan (gemm.hip) takes the same bound
+template <bool kGate>
+static hipError_t launch_narrow(const GemmOperands& o, const GemmParams& p, bool out_f32, hipStream_t stream) {
+  switch (narrow_fragments(p.M, p.N, cu_count())) {
+    case 1: return launch_splitk<8, 1, 1, 3, true, kGate>(o, p, out_f32, stream);
+    case 2: return launch_splitk<8, 1, 2, 3, true, kGate>(o, p, out_f32, stream);
+    case 3: return launch_splitk<8, 1, 3, 3, true, kGate>(o, p, out_f32, stream);
+    default: return launch_splitk<4, 2, 3, 3, true, kGate>(o, p, out_f32, stream);
+  }
+}
+
+hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f32, bool gate, hipStream_t stream) {
+  return gate ? launch_narrow<true>(o, p, out_f32, stream) : launch_narrow<false>(o, p, out_f32, stream);
+}
+
+// Decode shapes (M <= 32).  Each output column's sum runs in the order of the
+// number of waves (4, 8 or 16) that share it, whatever the tile.  Measured,
+// same box, W cycled through copies larger than the last-level cache:
+//  * at most one 32-column tile per CU (N <= 8192): the CUs hold one
+//    workgroup each, so more waves per workgroup keep more of W in flight
+//    (per-wave rings; 8 waves: 1 x 8192 x 5120 9.9 -> 7.8 us, 4 x 4352 x 5120
+//    9.6 -> 7.6, 12 x 5120 x 17408 35.2 -> 19.3; 16 waves for long K: 4 x
+//    5120 x 17408 24.5 -> 17.6).  Above 16 rows the activation loads of
+//    per-wave rings cost more: 4 waves (32 x 8192 x 5120 13.7 -> 9.7 us), and
+//    for long K 8 waves with a shared activation ring (32 x 5120 x 17408
+//    35.5 -> 21.2 us);
+//  * more tiles: 4 waves; up to 8 rows per-wave rings and one weight fragment
+//    per workgroup (1 and 7 x 34816 x 5120: 25.0 us against 27.5 with two),
+//    above that a shared activation ring, with one fragment while the tiles
+//    are few (32 x 17408 x 5120: 18.9 us against 19.8 with two), then with
+//    two (32 x 34816 x 5120: 28.4 against 28.8 with one).
+DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
+  const uint64_t tiles = (uint64_t)((N + 31) / 32);
+  const bool long_k = K >= 8192;
+  if (tiles <= n_cu) {
+    if (M <= 16) return long_k && M <= 8 ? DecodeShape::k16Private : DecodeShape::k8Private;
+    return long_k ? DecodeShape::k8Shared : DecodeShape::k4Private;
+  }
+  if (M <= 8) return DecodeShape::k4Private;
+  return 2 * tiles <= 5 * (uint64_t)n_cu ? DecodeShape::k4Shared : DecodeShape::k4SharedPair;
+}
 
 hipError_t launch_splitk_decode(const GemmOperands& o, GemmParams p, bool out_f32, hipStream_t stream) {
-  if (p.M <= kDecodePrivateRows) return launch_splitk<4, 1, 1, 3, false>(o, p, out_f32, false, stream);
-  return launch_splitk<4, 1, 2, 3, true>(o, p, out_f32, false, stream);
+  switch (decode_shape(p.M, p.N, p.K, cu_count())) {
+    case DecodeShape::k4Private: return launch_splitk<4, 1, 1, 3, false, false>(o, p, out_f32, stream);
+    case DecodeShape::k8Private: return launch_splitk<8, 1, 1, 3, false, false>(o, p, out_f32, stream);
+    case DecodeShape::k16Private: return launch_splitk<16, 1, 1, 3, false, false>(o, p, out_f32, stream);
+    case DecodeShape::k4Shared: return launch_splitk<4, 1, 1, 3, true, false>(o, p, out_f32, stream);
+    case DecodeShape::k8Shared: return launch_splitk<8, 1, 1, 4, true, false>(o, p, out_f32, stream);
+    default: return launch_splitk<4, 1, 2, 3, true, false>(o, p, out_f32, stream);
+  }
 }
 
-// The fused decode path's weight ring is one stage deeper than the plain
-// decode kernel's (4 instead of 3: more of the weight in flight while the
-// workgroup quantizes X; one token 33.0 -> 32.6 us, same box), which still
-// leaves three workgroups per CU (36 KB of ring + the 9 KB static array of
-// the quantized activation each).
-constexpr int kDecodeQuantStages = 4;
-
-size_t decode_quant_lds_bytes(int64_t M, int64_t K) {
-  (void)M;
-  (void)K;
-  return (size_t)splitk_ring_bytes<4, 1, 2, kDecodeQuantStages, false>();
+// Small outputs with M > 32 (see plan_gemm): four waves share the reduction
+// of a tile.
+hipError_t launch_splitk_tile(const GemmOperands& o, const GemmParams& p, int kind, bool out_f32, hipStream_t stream) {
+  switch (kind) {
+    case GemmPlan::kSplitk32x32: return launch_splitk<4, 1, 1, 3, false, false>(o, p, out_f32, stream);
+    case GemmPlan::kSplitk32x64: return launch_splitk<4, 1, 2, 3, true, false>(o, p, out_f32, stream);
+    case GemmPlan::kSplitk64x64: return launch_splitk<4, 2, 2, 3, true, false>(o, p, out_f32, stream);
+    default: return launch_splitk<4, 2, 3, 3, true, false>(o, p, out_f32, stream);
+  }
 }
 
-hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
-                                    bool out_f32, hipStream_t stream) {
-  constexpr int KS = 4, FM = 1, FN = 2, kStages = kDecodeQuantStages;
-  constexpr int kRing = splitk_ring_bytes<KS, FM, FN, kStages, false>();
+// The fused decode launch: as many waves per tile as decode_shape gives (the
+// same order of sums).  Four waves: two weight fragments per workgroup, a ring
+// one stage deeper than the plain decode kernel's (4 instead of 3: more of
+// the weight in flight while the workgroup quantizes X; one token 33.0 ->
+// 32.6 us, same box), which still leaves three workgroups per CU (36 KB of
+// ring + the 9 KB static array of the quantized activation each).
+template <int KS, int FN, int kStages>
+static hipError_t launch_decode_quant(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
+                                      bool out_f32, hipStream_t stream) {
+  constexpr int kRing = splitk_ring_bytes<KS, 1, FN, kStages, false>();
   static_assert(kRing >= KS * 64 * 64, "the reduction reuses the rings");
-  const size_t lds = decode_quant_lds_bytes(p.M, p.K);
   p.tiles_m = 1;
   p.tiles_n = (p.N + FN * 32 - 1) / (FN * 32);
   const dim3 grid(p.tiles_n), block(KS * 64);
 #define NVFP4_DQ(F32, Q)                                                                                   \
-  hipLaunchKernelGGL((gemm_splitk_kernel<KS, FM, FN, kStages, F32, false, Q>), grid, block, (uint32_t)lds, stream, \
+  hipLaunchKernelGGL((gemm_splitk_kernel<KS, 1, FN, kStages, F32, false, Q>), grid, block, kRing, stream, \
                      o.a_codes, o.a_scales, o.a_g, o.w_packed, o.w_g, o.y, p, q)
   if (dynamic) {
     if (out_f32) NVFP4_DQ(true, 2); else NVFP4_DQ(false, 2);
@@ -540,6 +595,16 @@ hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const D
   }
 #undef NVFP4_DQ
   return hipGetLastError();
+}
+
+hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
+                                    bool out_f32, hipStream_t stream) {
+  switch (decode_shape(p.M, p.N, p.K, cu_count())) {
+    case DecodeShape::k16Private: return launch_decode_quant<16, 1, 4>(o, p, q, dynamic, out_f32, stream);
+    case DecodeShape::k8Private:
+    case DecodeShape::k8Shared: return launch_decode_quant<8, 1, 4>(o, p, q, dynamic, out_f32, stream);
+    default: return launch_decode_quant<4, 2, 4>(o, p, q, dynamic, out_f32, stream);
+  }
 }
 
 }  // namespace nvfp4

@@ -97,8 +97,8 @@ __global__ __launch_bounds__(KS * 64, 2) void quant_gemm_kernel(QuantGemmArgs q,
       x_rd[f][j] = tr * 1024u + (rr * 8u + ((4 * h + j) ^ rr ^ (tr & 7))) * 16u;
     }
     const uint32_t row = m0 + f * 32 + r;
-    c_off[f] = row < p.M ? row * (p.K >> 1) + h * 16u : kOOB;
-    s_off[f] = row < p.M ? row * (p.K >> 4) + h * 2u : kOOB;
+    c_off[f] = row < p.M && tn == 0 ? row * (p.K >> 1) + h * 16u : kOOB;   // one tile column stores them
+    s_off[f] = row < p.M && tn == 0 ? row * (p.K >> 4) + h * 2u : kOOB;
   }
   uint8_t* xs = smem + wave * (2 * kXSlot);
   const __amdgpu_buffer_rsrc_t rc = rsrc(q.codes, p.a_code_bytes);
@@ -325,7 +325,15 @@ hipError_t launch_quant_gemm(const void* x, int64_t M, int64_t K, int64_t ldx, f
     if (e != hipSuccess) return e;
     q.n_partial = (uint32_t)n_partial;
   }
-  if (N <= 96) return launch_quant_gemm_fn<4, 2, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
+  if (N <= 96) {
+    // The tiles (and so the order of the sums) of the unfused GEMM.
+    switch (narrow_fragments(M, N, cu_count())) {
+      case 1: return launch_quant_gemm_fn<8, 1, 1>(q, dynamic, wp, w_g, y, p, out_f32, stream);
+      case 2: return launch_quant_gemm_fn<8, 1, 2>(q, dynamic, wp, w_g, y, p, out_f32, stream);
+      case 3: return launch_quant_gemm_fn<8, 1, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
+      default: return launch_quant_gemm_fn<4, 2, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
+    }
+  }
   return launch_quant_gemm_fn<4, 1, 4>(q, dynamic, wp, w_g, y, p, out_f32, stream);
 }
 

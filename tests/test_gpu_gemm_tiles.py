@@ -66,7 +66,9 @@ def test_gemm_tiles_and_k_parts(m, n, k, offs, ldy):
 
 def test_gemm_k_parts_without_their_workspace():
     """A workspace short of the K parts' (or none) gives the nvfp4_gemm result."""
-    need, aq, pw = _case(70, 300, 8192, [0, 300], 300)
+    # Long K on few tiles: the shape stays on K parts whatever the small
+    # split-K tiles cost.
+    need, aq, pw = _case(256, 2600, 17408, [0, 2600], 2600)
     assert need > 0
     y0 = L.gemm_no_workspace(aq, pw, out_dtype=torch.float32)
     y1 = torch.empty_like(y0)

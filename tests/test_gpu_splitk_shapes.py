@@ -1,0 +1,90 @@
+"""GPU parity of the split-K kernel's shapes (4, 8 and 16 waves per tile,
+per-wave and shared activation rings, 1 to 3 weight fragments) on either side
+of the dispatch rules, against the CPU oracle: the plain GEMM, the fused
+quantize + GEMM (which must sum in the same order) and the gate epilogue."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import gates as OGT
+from oracle import gemm as OG
+from oracle import quant as OQ
+from paper_2609_04098_amd import linear as L
+from paper_2609_04098_amd import synth
+from tests.gpu_common import bf16_rne_of, check_gemm, log, to_dev_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(m, n, k):
+    rng = np.random.default_rng(m * 17 + n * 3 + k)
+    x = rng.standard_normal((m, k))
+    x[:, rng.choice(k, max(1, k // 200), replace=False)] *= 100.0
+    return synth.f64_to_bf16_bits(x), synth.f64_to_bf16_bits(rng.standard_normal((n, k)) * 0.02)
+
+
+def _check(m, n, k, offs):
+    xb, wb = _inputs(m, n, k)
+    x, pw = to_dev_bf16(xb), L.pack_weight(to_dev_bf16(wb), offs)
+    aq = L.quantize_act(x)
+    y32 = L.gemm(aq, pw, out_dtype=torch.float32)
+    y16 = L.gemm(aq, pw)
+    act = L.alloc_act(m, k, x.device)
+    f32, _ = L.quantize_gemm(x, pw, out_dtype=torch.float32, act_out=act)
+    s32, _ = L.quantize_gemm(x, pw, g=float(aq.g.item()), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert torch.equal(act.codes, aq.codes) and torch.equal(act.scales, aq.scales) and torch.equal(act.g, aq.g)
+    assert torch.equal(f32, y32) and torch.equal(s32, y32), "fused and unfused sums differ"
+    xp, xs, gx = OQ.quantize_tensor(xb)
+    wp, ws, gw = OQ.quantize_segments(wb, offs)
+    check_gemm(y32.cpu().numpy().astype(np.float64), OG.gemm_f64(xp, xs, gx, wp, ws, gw, offs),
+               OG.abs_bound(xp, xs, gx, wp, ws, gw, offs), "%dx%dx%d" % (m, n, k))
+    np.testing.assert_array_equal(y16.view(torch.int16).cpu().numpy().view(np.uint16), bf16_rne_of(y32))
+    log("%dx%dx%d: %s" % (m, n, k, L.gemm_kernels(m, n, k)))
+
+
+@pytest.mark.parametrize("m,n,k,offs", [
+    (1, 200, 64, [0, 200]),                # one chunk for 8 waves
+    (3, 290, 5120, [0, 100, 290]),         # 8 waves, one launch (fused quantizer)
+    (16, 8192, 576, [0, 4096, 8192]),      # one tile per CU, 9 chunks over 8 waves, most rows of the 8-wave form
+    (17, 8192, 512, [0, 8192]),            # the fewest rows of the 4-wave form
+    (16, 8193, 512, [0, 8193]),            # one tile past one per CU: shared ring, one fragment
+    (9, 20480, 192, [0, 20480]),           # most tiles with one fragment
+    (9, 20481, 192, [0, 20481]),           # fewest tiles with two
+    (1, 160, 8192, [0, 160]),              # long K: 16 waves, one launch
+    (8, 170, 8256, [0, 85, 170]),          # long K: 129 chunks over 16 waves
+    (9, 170, 8256, [0, 170]),              # long K, 9 rows: 8 waves
+    (20, 170, 8192, [0, 170]),             # long K, more rows: shared ring of 4 stages
+    (32, 140, 17408, [0, 140]),
+])
+def test_decode_shapes(m, n, k, offs):
+    _check(m, n, k, offs)
+
+
+@pytest.mark.parametrize("m,n,k,offs", [
+    (5, 96, 5120, [0, 48, 96]),
+    (33, 64, 320, [0, 64]),                # 5 chunks over 8 waves, two row tiles
+    (2720, 90, 192, [0, 30, 90]),          # 85 x 3 tiles: one fragment per tile
+    (2721, 90, 192, [0, 30, 90]),          # 86 x 3 tiles would not fit the CUs: two fragments
+    (4097, 96, 128, [0, 48, 96]),          # three fragments
+    (8192, 96, 64, [0, 48, 96]),           # one tile per CU
+    (8193, 96, 64, [0, 48, 96]),           # 64 x 96 tiles
+])
+def test_narrow_shapes(m, n, k, offs):
+    _check(m, n, k, offs)
+
+
+@pytest.mark.parametrize("m", [1, 70, 3000, 6000])
+def test_gate_epilogue_shapes(m):
+    h, k = 48, 576
+    xb, wb = _inputs(m, 2 * h, k)
+    rng = np.random.default_rng(m)
+    a_log, dt = np.log(rng.uniform(1, 16, h)).astype(np.float32), rng.uniform(-4, 2, h).astype(np.float32)
+    aq, pw = L.quantize_act(to_dev_bf16(xb)), L.pack_weight(to_dev_bf16(wb), [0, h, 2 * h])
+    y = L.gemm_gdn_gates(aq, pw, torch.from_numpy(a_log).cuda(), torch.from_numpy(dt).cuda(), out_dtype=torch.float32)
+    v = L.gemm(aq, pw, out_dtype=torch.float32).cpu().numpy().astype(np.float64)
+    # The gate of the kernel's own product: alpha = exp(g) has a relative error
+    # of |g| times a few ulps of binary32, below 100 * 8 * 2^-24 = 5e-5 while
+    # alpha is above 1e-38.
+    np.testing.assert_allclose(y.cpu().numpy(), OGT.gdn_gates(v, a_log, dt), rtol=1e-4, atol=1e-30)
