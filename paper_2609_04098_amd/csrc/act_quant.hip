@@ -1,8 +1,8 @@
 // Dynamic activation quantization to NVFP4 on gfx950 (paper, section 2
 // "NVFP4"; the run-time "A4" half of W4A4).
 //
-// Two launches on the caller's stream (one for activations of at most 4096
-// blocks, see act_quant_small_kernel), no atomics and no memset:
+// Two launches on the caller's stream (one for activations of at most
+// kSmallMaxBlocks blocks, see act_quant_small_kernel), no atomics and no memset:
 //   1. amax_partial: each workgroup reduces |x| over a grid-strided share of
 //      X and writes one partial maximum to the workspace.  bf16 magnitudes
 //      order like unsigned integers, so the reduction is packed u16 max.
@@ -162,66 +162,71 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(
 
 __global__ void write_zero_scale_kernel(float* g_enc) { *g_enc = 0.0f; }
 
-// Small activations (decode-shaped calls, a few tokens): one workgroup does
-// both passes, so the quantizer is one launch instead of two.  The amax is
-// the same order-free maximum; the blocks are quantized by the same code.
+// Small activations (decode-shaped calls, up to some tens of tokens): one
+// launch.  Every workgroup takes the maximum over the whole of X itself (the
+// maximum is order-free, so all form the same G; workgroup 0 writes it), then
+// quantizes its share of the blocks, one per thread, with the same code.  What
+// bounds it is latency and the 64 bytes a clock a CU reads from L2.  GPU time
+// per call, same box: one workgroup that walks all blocks 4.8 us at 2560
+// blocks and 6.1 at 3840, this 3.9 and 4.0; two launches 4.8 us from 4352 to
+// 16384 blocks, this 4.3 at 4352, 4.5 at 5120, 5.0 at 8000 (and one launch,
+// 3.5 us of host time, less), 5.8 at 10240.
 constexpr int kSmallThreads = 1024;
-// Up to 4096 blocks (M * K <= 65536, e.g. a few tokens of width 5120) one
-// CU does the work faster than two launches spread over the chip.
-constexpr uint32_t kSmallMaxBlocks = 4096;
+constexpr int kSmallLoads = 4;           // 16-byte loads in flight per thread
+constexpr uint32_t kSmallMaxBlocks = 8192;
 
 template <bool kDynamic, bool kContig>
 __global__ __launch_bounds__(kSmallThreads) void act_quant_small_kernel(
     const uint16_t* __restrict__ x, uint32_t n_blocks, uint32_t blocks_per_row, uint32_t ldx,
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ g_enc) {
   __shared__ uint32_t lds[kSmallThreads / 64];
+  const uint32_t b = blockIdx.x * kSmallThreads + threadIdx.x;
+  const uint32_t bq = b < n_blocks ? b : n_blocks - 1;
+  const uint4 d0 = *vec_ptr<kContig>(x, 2 * bq, 2 * blocks_per_row, ldx);
+  const uint4 d1 = *vec_ptr<kContig>(x, 2 * bq + 1, 2 * blocks_per_row, ldx);
   float g;
   if (kDynamic) {
-    uint32_t m = 0;
-    for (uint32_t b = threadIdx.x; b < n_blocks; b += kSmallThreads) {
-      const uint4* src;
-      if (kContig) {
-        src = reinterpret_cast<const uint4*>(x) + 2 * (size_t)b;
-      } else {
-        uint32_t row = b / blocks_per_row, col = b - row * blocks_per_row;
-        src = reinterpret_cast<const uint4*>(x + (size_t)row * ldx) + 2 * col;
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    auto amax = [](u16x2 m, const uint4& d) {
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d.x & 0x7FFF7FFFu));
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d.y & 0x7FFF7FFFu));
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d.z & 0x7FFF7FFFu));
+      return __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d.w & 0x7FFF7FFFu));
+    };
+    // The thread's own block; in a single workgroup these are all of X.
+    u16x2 mp = amax(amax(u16x2{0, 0}, d0), d1);
+    const uint32_t n_vec = gridDim.x == 1 ? 0 : 2 * n_blocks;
+    for (uint32_t v = threadIdx.x; v < n_vec; v += kSmallLoads * kSmallThreads) {
+      uint4 d[kSmallLoads];
+#pragma unroll
+      for (int u = 0; u < kSmallLoads; ++u) {
+        const uint32_t vu = v + u * kSmallThreads;             // past the end: the last vector again
+        d[u] = *vec_ptr<kContig>(x, vu < n_vec ? vu : n_vec - 1, 2 * blocks_per_row, ldx);
       }
-      const uint4 d0 = src[0], d1 = src[1];
-      const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-      const uint32_t a = __float_as_uint(block_amax(v));
-      m = m > a ? m : a;
+#pragma unroll
+      for (int u = 0; u < kSmallLoads; ++u) mp = amax(mp, d[u]);
     }
-    // Workgroup maximum (16 waves).
-    m = wave_max_u32(m);
+    // Workgroup maximum (16 waves); bf16 magnitudes order like integers.
+    uint32_t m = wave_max_u32(mp[0] > mp[1] ? mp[0] : mp[1]);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
     __syncthreads();
     m = lds[0];
 #pragma unroll
     for (int w = 1; w < kSmallThreads / 64; ++w) m = m > lds[w] ? m : lds[w];
-    g = global_scale(__uint_as_float(m));
-    if (threadIdx.x == 0) *g_enc = g;
+    g = global_scale(__uint_as_float(m << 16));
+    if (b == 0) *g_enc = g;
   } else {
     g = *g_enc;
   }
-  const float gd6 = g * (1.0f / 6.0f);
-  for (uint32_t b = threadIdx.x; b < n_blocks; b += kSmallThreads) {
-    const uint4* src;
-    if (kContig) {
-      src = reinterpret_cast<const uint4*>(x) + 2 * (size_t)b;
-    } else {
-      uint32_t row = b / blocks_per_row, col = b - row * blocks_per_row;
-      src = reinterpret_cast<const uint4*>(x + (size_t)row * ldx) + 2 * col;
-    }
-    const uint4 d0 = src[0], d1 = src[1];
-    const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-    uint32_t c0, c1, sc;
-    if (g > kHugeScale)
-      sc = quantize_block<true>(v, g, gd6, c0, c1);
-    else
-      sc = quantize_block<false>(v, g, gd6, c0, c1);
-    reinterpret_cast<uint2*>(codes)[b] = make_uint2(c0, c1);
-    scales[b] = (uint8_t)sc;
-  }
+  if (b >= n_blocks) return;
+  const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+  uint32_t c0, c1, sc;
+  if (g > kHugeScale)
+    sc = quantize_block<true>(v, g, g * (1.0f / 6.0f), c0, c1);
+  else
+    sc = quantize_block<false>(v, g, g * (1.0f / 6.0f), c0, c1);
+  reinterpret_cast<uint2*>(codes)[b] = make_uint2(c0, c1);
+  scales[b] = (uint8_t)sc;
 }
 
 static int grid_for(uint64_t work_items, int cap) {
@@ -280,8 +285,9 @@ hipError_t launch_act_quant(const void* x, int64_t M, int64_t K, int64_t ldx, ui
   const uint32_t n_vec = (uint32_t)(M * K / 8), vec_per_row = (uint32_t)(K / 8);
   const uint32_t n_blocks = (uint32_t)(M * K / 16), blocks_per_row = (uint32_t)(K / 16);
   if (n_blocks <= kSmallMaxBlocks) {
+    const uint32_t grid = (n_blocks + kSmallThreads - 1) / kSmallThreads;
 #define NVFP4_AQS(D, C)                                                                             \
-  hipLaunchKernelGGL((act_quant_small_kernel<D, C>), dim3(1), dim3(kSmallThreads), 0, stream, xp, n_blocks, \
+  hipLaunchKernelGGL((act_quant_small_kernel<D, C>), dim3(grid), dim3(kSmallThreads), 0, stream, xp, n_blocks, \
                      blocks_per_row, (uint32_t)ldx, codes, scales, g_enc)
     if (dynamic) {
       if (contig) NVFP4_AQS(true, true); else NVFP4_AQS(true, false);

@@ -88,3 +88,27 @@ def test_gate_epilogue_shapes(m):
     # of |g| times a few ulps of binary32, below 100 * 8 * 2^-24 = 5e-5 while
     # alpha is above 1e-38.
     np.testing.assert_allclose(y.cpu().numpy(), OGT.gdn_gates(v, a_log, dt), rtol=1e-4, atol=1e-30)
+
+
+@pytest.mark.parametrize("m,k,ldx", [
+    (1, 16, None),                          # one block
+    (64, 256, None),                        # 1024 blocks: one workgroup, its own blocks are all of X
+    (41, 400, 416),                         # 1025 blocks, strided rows: two workgroups
+    (32, 4096, None),                       # 8192 blocks: the largest one-launch activation
+    (8193, 16, 24),                         # 8193 blocks: two launches
+])
+def test_one_launch_quantizer_limits(m, k, ldx):
+    rng = np.random.default_rng(m + k)
+    for where in (0, m - 1):                # the maximum in the first or the last block
+        x = rng.standard_normal((m, k))
+        x[where, -1 if where else 0] = -300.0
+        xb = synth.f64_to_bf16_bits(x)
+        buf = np.full((m, ldx or k), 0x7F00, dtype=np.uint16)      # padding far above the maximum
+        buf[:, :k] = xb
+        xd = to_dev_bf16(buf)[:, :k]
+        xp, xs, gx = OQ.quantize_tensor(xb)
+        for g in (None, gx):
+            aq = L.quantize_act(xd, g=g)
+            assert np.float32(aq.g.item()) == gx
+            np.testing.assert_array_equal(aq.codes.cpu().numpy(), xp)
+            np.testing.assert_array_equal(aq.scales.cpu().numpy(), xs)
