@@ -6,6 +6,7 @@ order only (the arithmetic is in the HIP kernels).
     y  = gemm(aq, pw)                         # Y = dq(A) dq(W)^T, segment-scaled
 """
 
+import ctypes
 from dataclasses import dataclass
 from typing import List
 
@@ -82,6 +83,21 @@ def act_workspace(m, k, device):
     return torch.empty(_c.nvfp4_quantize_act_workspace(m, k), dtype=torch.uint8, device=device)
 
 
+def _set_scale(buf, g, stream):
+    """Write the calibrated scale ``g`` to the device float ``buf``.  On the
+    current stream (``stream`` None) a number goes out with a fill kernel and
+    a device tensor with a device copy, neither waiting for the device (5 us of
+    host time; a copy from host memory takes 16 us and drains the queue).  For
+    another stream the copy from host memory, which has arrived when it
+    returns, keeps the order."""
+    if stream is not None:
+        buf.copy_(torch.as_tensor([float(g)], dtype=torch.float32))
+    elif torch.is_tensor(g) and g.is_cuda:
+        buf.copy_(g.reshape(1))
+    else:
+        buf.fill_(ctypes.c_float(float(g)).value)
+
+
 def quantize_act(x, g=None, out: QuantizedAct = None, workspace=None, stream=None) -> QuantizedAct:
     """Quantize a bf16 [M, K] activation (dynamic G unless ``g`` is given)."""
     m, k = x.shape
@@ -91,7 +107,7 @@ def quantize_act(x, g=None, out: QuantizedAct = None, workspace=None, stream=Non
         ws = act_workspace(m, k, dev) if workspace is None else workspace
         _c.nvfp4_quantize_act(x, aq.codes, aq.scales, aq.g, _c.NVFP4_DYNAMIC, ws, stream)
     else:
-        aq.g.copy_(torch.as_tensor([float(g)], dtype=torch.float32))
+        _set_scale(aq.g, g, stream)
         _c.nvfp4_quantize_act(x, aq.codes, aq.scales, aq.g, _c.NVFP4_STATIC, None, stream)
     return aq
 
@@ -104,7 +120,7 @@ def rmsnorm_quantize_act(x, gamma, eps, g, out: QuantizedAct = None, y=None, str
     if torch.is_tensor(g):
         aq.g.copy_(g.reshape(1))
     else:
-        aq.g.copy_(torch.as_tensor([float(g)], dtype=torch.float32))
+        _set_scale(aq.g, g, stream)
     _c.nvfp4_rmsnorm_quantize_act(x, gamma, eps, aq.codes, aq.scales, aq.g, y, stream)
     return aq
 
@@ -184,7 +200,7 @@ def quantize_gemm(x, pw: PackedWeight, g=None, out_dtype=torch.bfloat16, out=Non
         _c.nvfp4_quantize_gemm(x, gbuf, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, _c.NVFP4_DYNAMIC, ws,
                                codes, scales, kind, stream)
     else:
-        gbuf.copy_(torch.as_tensor([float(g)], dtype=torch.float32))
+        _set_scale(gbuf, g, stream)
         _c.nvfp4_quantize_gemm(x, gbuf, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, _c.NVFP4_STATIC, ws,
                                codes, scales, kind, stream)
     return y, gbuf

@@ -55,6 +55,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_raw_stream = _raw_device = None
 
 
 class Nvfp4Error(RuntimeError):
@@ -84,11 +85,25 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+def _current_stream():
+    """Handle of PyTorch's current stream on the current device.  The raw
+    query takes 0.3 us where building a torch.cuda.Stream takes 2.9."""
+    global _raw_stream, _raw_device
+    if _raw_stream is None:
+        import torch
+        handle = torch.cuda.current_stream().cuda_stream    # initializes the device
+        _raw_device = getattr(torch._C, "_cuda_getDevice", None)
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if _raw_device is None or _raw_stream is None:
+            _raw_device, _raw_stream = int, lambda _: torch.cuda.current_stream().cuda_stream
+        return handle
+    return _raw_stream(_raw_device())
+
+
 def _stream(stream):
     if stream is not None:
         return ctypes.c_void_p(getattr(stream, "cuda_stream", stream))
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_current_stream())
 
 
 def _check(status, where):
