@@ -245,14 +245,17 @@ int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
 /*
  * Workspace bytes that let nvfp4_gemm_with_workspace split the K range of an
  * M x N x K call over several workgroups per output tile on the current
- * device; 0 when the shape does not use it (then any workspace, or none,
- * gives the nvfp4_gemm launches) or the arguments are invalid.  Two forms:
+ * device, or run a K that is no multiple of 64 on the kernels for those that
+ * are; 0 when the shape does not use it (then any workspace, or none,
+ * gives the nvfp4_gemm launches) or the arguments are invalid.  Three forms:
  *   - K halves of the last round: the last round of 256 x 256 output tiles
  *     (one per compute unit) would be at most half full, those tiles make
  *     whole tile columns, and K % 512 == 0 (e.g. 8192 x 5120 x 17408:
  *     2 * 8192 * 1024 * 4 bytes);
  *   - K parts: the whole output has too few tiles to fill the compute units
- *     (e.g. 200 x 5120 x 17408); at most 128 MB.
+ *     (e.g. 200 x 5120 x 17408); at most 128 MB;
+ *   - a padded copy of the activation's codes and scales (K % 64 != 0), in
+ *     front of either.
  */
 size_t nvfp4_gemm_workspace(int64_t M, int64_t N, int64_t K);
 
@@ -267,7 +270,7 @@ size_t nvfp4_gemm_workspace(int64_t M, int64_t N, int64_t K);
  *   workspace_bytes  its size.
  * Errors: as nvfp4_gemm; NVFP4_EINVAL for a misaligned workspace;
  * NVFP4_EWORKSPACE if the shape has a K-halves form and the workspace is
- * smaller than that needs.  A workspace smaller than the K-parts form needs is
+ * smaller than that needs.  A workspace smaller than the other forms need is
  * not an error: the call then takes the K-halves form if there is one, else
  * the nvfp4_gemm launches.
  */

@@ -146,16 +146,23 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
       if (!tail || cost < rounds * (float)(K / 64) * chunk_us + sq.fixed_us) g = t;
     }
   } else {
-    g.first = GemmPlan::kReg;
+    const int64_t k_pad = (K + 63) / 64 * 64;
+    if (with_ws && M * k_pad < ((int64_t)1 << 31)) {
+      g = plan_gemm(M, N, k_pad, n_cu, true);
+      g.k_pad = (uint32_t)k_pad;
+    } else {
+      g.first = GemmPlan::kReg;
+    }
   }
   return g;
 }
 
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N) {
+  const size_t pad = g.k_pad ? pad_bytes(M, g.k_pad) : 0;
   if (g.second == GemmPlan::kLdsSuperHalves)
-    return (size_t)2 * (size_t)M * (size_t)parts_row((uint32_t)N - g.n_split) * sizeof(float);
-  if (g.k_parts > 1) return (size_t)g.k_parts * (size_t)M * (size_t)parts_row((uint32_t)N) * sizeof(float);
-  return 0;
+    return pad + (size_t)2 * (size_t)M * (size_t)parts_row((uint32_t)N - g.n_split) * sizeof(float);
+  if (g.k_parts > 1) return pad + (size_t)g.k_parts * (size_t)M * (size_t)parts_row((uint32_t)N) * sizeof(float);
+  return pad;
 }
 
 const char* gemm_kernel_name(int kind, bool parts) {
@@ -212,6 +219,7 @@ const char* gemm_kernel_for(int64_t M, int64_t N, int64_t K, int part, bool with
   const uint32_t n_cu = cu_count();
   if (n_cu == 0) return nullptr;
   const GemmPlan g = plan_gemm(M, N, K, n_cu, with_ws);
+  if (g.k_pad) K = g.k_pad;                  // after pad_act_kernel
   const int kind = part == 0 ? g.first : g.second;
   if (kind == GemmPlan::kSplitkDecode) return decode_kernel_name(decode_shape(M, N, K, n_cu));
   if (kind == GemmPlan::kSplitkNarrow) return narrow_kernel_name(narrow_fragments(M, N, n_cu));
@@ -252,10 +260,6 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
                        const int64_t* seg_offsets, int n_seg, const float* w_g, void* y,
                        int64_t ldy, bool out_f32, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  GemmParams p = gemm_params(M, K, N, seg_offsets, n_seg, ldy);
-  p.y_pairs = (ldy % 2 == 0) && (reinterpret_cast<uintptr_t>(y) % 4 == 0) ? 1u : 0u;
-  p.y_stream = !out_f32 && (uint64_t)M * (uint64_t)N * 2u >= kMallBytes ? 1u : 0u;
-  const GemmOperands o{a_codes, a_scales, a_g, static_cast<const uint8_t*>(w_packed), w_g, y};
   GemmPlan g = plan_gemm(M, N, K, cu_count(), workspace != nullptr);
   if (workspace_bytes != kNoWorkspace && workspace_bytes < plan_workspace_bytes(plan_gemm(M, N, K, cu_count(), true), M, N)) {
     g = plan_gemm(M, N, K, cu_count(), false);
@@ -265,8 +269,22 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
       if (h.second == GemmPlan::kLdsSuperHalves) g = h;
     }
   }
-  const bool aligned = (K % 64) == 0;
   float* parts = static_cast<float*>(workspace);
+  if (g.k_pad) {
+    uint8_t* pc = static_cast<uint8_t*>(workspace);
+    uint8_t* ps = pc + pad_code_bytes(M, g.k_pad);
+    const hipError_t e = launch_pad_act(a_codes, a_scales, M, K, g.k_pad, pc, ps, stream);
+    if (e != hipSuccess) return e;
+    a_codes = pc;
+    a_scales = ps;
+    parts = reinterpret_cast<float*>(pc + pad_bytes(M, g.k_pad));
+    K = g.k_pad;
+  }
+  GemmParams p = gemm_params(M, K, N, seg_offsets, n_seg, ldy);
+  p.y_pairs = (ldy % 2 == 0) && (reinterpret_cast<uintptr_t>(y) % 4 == 0) ? 1u : 0u;
+  p.y_stream = !out_f32 && (uint64_t)M * (uint64_t)N * 2u >= kMallBytes ? 1u : 0u;
+  const GemmOperands o{a_codes, a_scales, a_g, static_cast<const uint8_t*>(w_packed), w_g, y};
+  const bool aligned = (K % 64) == 0;
   if (g.k_parts > 1) {
     hipError_t e;
     if (g.first == GemmPlan::kLdsSuper)

@@ -428,11 +428,22 @@ struct GemmPlan {
               kSplitk64x96 };
   int first, second;
   uint32_t n_split, k_parts;
+  // K % 64 != 0 with a workspace: the activation is first copied into it with
+  // its rows padded to k_pad = 64 ceil(K / 64) (zero scales past K; the packed
+  // weight is padded already), and the kernels above run on that; else 0.
+  uint32_t k_pad;
 };
 // with_ws: the caller provides gemm_workspace_bytes of workspace (tiles may
 // then run as several K parts).
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws);
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N);
+// Bytes of the padded activation's codes and scales (each a multiple of 16).
+inline size_t pad_code_bytes(int64_t M, int64_t k_pad) { return ((size_t)(M * k_pad / 2) + 15) & ~(size_t)15; }
+inline size_t pad_bytes(int64_t M, int64_t k_pad) {
+  return pad_code_bytes(M, k_pad) + (((size_t)(M * k_pad / 16) + 15) & ~(size_t)15);
+}
+hipError_t launch_pad_act(const uint8_t* codes, const uint8_t* scales, int64_t M, int64_t K, int64_t k_pad,
+                          uint8_t* pad_codes, uint8_t* pad_scales, hipStream_t stream);
 const char* gemm_kernel_name(int kind, bool parts);
 
 // Compute units of the current device (cached per device, thread-safe).

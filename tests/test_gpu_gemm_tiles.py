@@ -58,6 +58,17 @@ def _case(m, n, k, offs, ldy):
     (100, 2600, 5120, [0, 1300, 2600], 2600),        # segment boundary inside a tile
     (40, 1000, 17408, [0, 1000], 1000),              # long K, many parts
     (600, 1100, 1280, [0, 1100], 1104),              # more rows than columns of tiles
+    (1030, 770, 4352, [0, 770], 776),                # past the split-K tiles' rows: 17 groups of chunks
+    (1030, 770, 4416, [0, 385, 770], 771),           #   69 chunks, no super-stages
+    (1088, 260, 320, [0, 260], 260),
+    (1153, 129, 1024, [0, 129], 129),
+    (1100, 1500, 64, [0, 700, 1500], 1504),
+    (1, 33, 16, [0, 33], 33),                        # K % 64 != 0 (padded with the workspace, register path without):
+    (70, 90, 48, [0, 90], 90),                       #   tall-skinny
+    (7, 200, 1040, [0, 200], 200),                   #   decode shape
+    (300, 515, 80, [0, 256, 515], 515),
+    (257, 1300, 4368, [0, 433, 1300], 1304),         #   273 blocks per row
+    (200, 600, 17392, [0, 600], 600),                #   K parts behind the padded copy
 ])
 def test_gemm_tiles_and_k_parts(m, n, k, offs, ldy):
     need, _, _ = _case(m, n, k, offs, ldy)
