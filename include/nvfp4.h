@@ -253,7 +253,8 @@ int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
  *     whole tile columns, and K % 512 == 0 (e.g. 8192 x 5120 x 17408:
  *     2 * 8192 * 1024 * 4 bytes);
  *   - K parts: the whole output has too few tiles to fill the compute units
- *     (e.g. 200 x 5120 x 17408); at most 128 MB;
+ *     (e.g. 200 x 5120 x 17408), or the last round of its tiles has (e.g. 7000
+ *     x 5120 x 17408); at most 128 MB;
  *   - a padded copy of the activation's codes and scales (K % 64 != 0), in
  *     front of either.
  */

@@ -27,13 +27,24 @@ uint32_t cu_count() {
 // choice between tile shapes and numbers of K parts.  A workgroup alone on a
 // CU and two that share it take the same time per chunk and workgroup
 // (measured: 240 workgroups of 91 chunks and 480 of 45 both 50 us), so the
-// busiest CU's work is ceil(workgroups / CUs) runs of chunks whatever the
-// occupancy.
+// work is counted in rounds of one workgroup per CU whatever the occupancy.
+// The clock is held by power, so a round that leaves CUs idle runs faster: a
+// partly filled last round takes 0.74 to 0.8 of a full one (320 and 384 tiles
+// at K = 5120, 400 at K = 17408: 240, 242 and 699 us against 138 and 389 for
+// one round), a lone round of 160 tiles 0.94.  Smaller tiles, several to a
+// CU, gain less from it (`last`: the least a partly filled last round costs).
+static float rounds_of(uint64_t workgroups, uint32_t n_cu, float last) {
+  const float frac = (float)(workgroups % n_cu) / (float)n_cu;
+  if (workgroups < n_cu) return 0.85f + 0.15f * frac;
+  return (float)(workgroups / n_cu) + (frac == 0.0f ? 0.0f : frac > last ? frac : last);
+}
+
 struct TileCost {
   int kind, super_kind;
   uint32_t bm, bn;
   float chunk_us, chunk_us_super;   // one 64-deep chunk of a tile
   float fixed_us;                   // first loads, epilogue, launch
+  float last_round;                 // see rounds_of
   uint32_t max_parts;               // K parts the launcher offers (with super-stages; square: only with them)
 };
 // Fitted, on one box, to M = 50 .. 1000 against N = 4352 .. 34816 at K = 5120,
@@ -41,13 +52,13 @@ struct TileCost {
 // split-K tiles (four waves share a tile's reduction and meet in LDS) have
 // the cheaper small tile, the LDS tiles the cheaper large one and K parts.
 constexpr TileCost kTileCosts[] = {
-    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.60f, 1.46f, 7.5f, 32},
-    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.51f, 0.45f, 7.0f, 32},
-    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.51f, 0.45f, 7.0f, 32},
-    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.19f, 0.19f, 8.0f, 1},
-    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.155f, 0.155f, 6.0f, 1},
-    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.09f, 0.09f, 5.0f, 1},
-    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1},
+    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 7.5f, 0.75f, 32},
+    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.54f, 0.485f, 7.0f, 0.92f, 32},
+    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.57f, 0.515f, 7.0f, 0.92f, 32},
+    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.19f, 0.19f, 8.0f, 1.0f, 1},
+    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.155f, 0.155f, 6.0f, 1.0f, 1},
+    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.09f, 0.09f, 5.0f, 1.0f, 1},
+    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1.0f, 1},
 };
 // The summing pass: a launch, and every partial sum written and read once
 // (they stay in the last-level cache).
@@ -57,15 +68,24 @@ constexpr uint64_t kMaxPartBytes = 128ull << 20;
 constexpr uint32_t kMinPartChunks = 4;   // one group of chunks with super-stages
 
 // The split-K tiles are offered where their costs were fitted: a batch of up
-// to 1024 rows, at most 5 rounds of tiles (100 x 34816 x 5120 with 32 x 64
+// to 1024 rows, or a K below 2048, where the longer first loads of the LDS tiles
+// weigh more (1300 x 1300 x 1088: 24 us with 128 x 128 tiles; 1000 rows 10 us
+// with split-K tiles); at most 5 rounds of tiles (100 x 34816 x 5120 with 32 x 64
 // tiles, 9 rounds, took 75 us for an estimate of 70; the LDS tiles, which share
 // each operand between their waves, are the better ones there).
 constexpr int64_t kSplitkMaxRows = 1024;
+constexpr int64_t kSplitkShortK = 2048;
 constexpr uint64_t kSplitkMaxRounds = 5;
 
 // Below this K the K-halves / tall-tile form of the last round is kept as
 // it is: the cost of a tile is then mostly its first loads and epilogue.
 constexpr int64_t kTailMinK = 2048;
+
+// K parts of the last round's tiles: at most kMaxTailParts.
+constexpr uint32_t kMaxTailParts = 8;
+// Another plan replaces whole square tiles only for an estimated gain beyond
+// the estimate's own error.
+constexpr float kPlanGain = 0.96f;
 
 // The cheapest single launch over all columns: tile shape and K parts.
 static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws, float* cost) {
@@ -76,15 +96,15 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
   for (const TileCost& t : kTileCosts) {
     const bool square = t.kind == GemmPlan::kLdsSquare;
     const uint64_t tiles = (uint64_t)((M + t.bm - 1) / t.bm) * (uint64_t)((N + t.bn - 1) / t.bn);
-    if (t.kind == t.super_kind && (M > kSplitkMaxRows || tiles > kSplitkMaxRounds * n_cu)) continue;   // split-K tile
+    const bool splitk = t.kind == t.super_kind;
+    if (splitk && ((M > kSplitkMaxRows && K >= kSplitkShortK) || tiles > kSplitkMaxRounds * n_cu)) continue;
     for (uint32_t parts = 1; parts <= t.max_parts; ++parts) {
       const uint64_t part_bytes = (uint64_t)parts * (uint64_t)M * parts_row((uint32_t)N) * sizeof(float);
       if (parts > 1 && (!with_ws || units * unit < parts * kMinPartChunks || part_bytes > kMaxPartBytes ||
                         (square && !super)))
         break;
-      const uint64_t rounds = (tiles * parts + n_cu - 1) / n_cu;
       const uint32_t chunks = (units + parts - 1) / parts * unit;
-      const float c = (float)rounds * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us +
+      const float c = rounds_of(tiles * parts, n_cu, t.last_round) * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us +
                       (parts > 1 ? kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs : 0.0f);
       if (best.first == GemmPlan::kNone || c < *cost) {
         best.first = super ? t.super_kind : t.kind;
@@ -119,6 +139,36 @@ static GemmPlan plan_square(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool
   return g;
 }
 
+// Full rounds of square tiles, then the tiles of the last round in K parts
+// that spread them over all CUs: for last rounds more than half full (or not
+// whole tile columns), which K halves would not shorten.  FP32 partial tiles,
+// then a summing pass.  K % 256 == 0.
+static GemmPlan plan_square_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, float* cost) {
+  GemmPlan best{};
+  const TileCost& sq = kTileCosts[0];
+  const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
+  const uint64_t rem = tiles % n_cu;
+  const uint32_t units = (uint32_t)(K / 256);
+  for (uint32_t parts = 2; parts <= kMaxTailParts && parts <= units && rem != 0 && tiles > n_cu; ++parts) {
+    const uint64_t part_bytes = (uint64_t)parts * rem * kSquareTile * kSquareTile * sizeof(float);
+    if (part_bytes > kMaxPartBytes) break;
+    const float tail_rounds = rounds_of(rem * parts, n_cu, sq.last_round);
+    const float c = ((float)(tiles / n_cu) * (float)units + tail_rounds * (float)((units + parts - 1) / parts)) *
+                        4.0f * sq.chunk_us_super + (1.0f + tail_rounds) * sq.fixed_us + kSumLaunchUs +
+                    2.0f * (float)part_bytes / kPartBytesPerUs;
+    if (best.first == GemmPlan::kNone || c < *cost) {
+      *cost = c;
+      best.first = GemmPlan::kLdsSuper;
+      best.second = GemmPlan::kLdsSuperTiles;
+      best.n_full = (uint32_t)(tiles - rem);
+      best.tail_parts = parts;
+    }
+  }
+  best.n_split = (uint32_t)N;
+  best.k_parts = 1;
+  return best;
+}
+
 // The kernels one nvfp4_gemm call launches for a shape (n_cu: compute units
 // of the device).
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws) {
@@ -132,18 +182,23 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
   } else if (aligned && M <= 32) {
     g.first = GemmPlan::kSplitkDecode;
   } else if (aligned) {
+    // Square tiles, unless another tile shape or K parts are estimated to be
+    // faster.
     g = plan_square(M, N, K, n_cu, with_ws);
     const bool tail = g.second != GemmPlan::kNone;
     if (n_cu != 0 && (!tail || K >= kTailMinK)) {
-      // The cheapest tile shape and number of K parts, where that beats the
-      // second launch of the last round (0.6 or 0.75 of a round).
-      float cost;
-      const GemmPlan t = plan_tiles(M, N, K, n_cu, with_ws, &cost);
       const TileCost& sq = kTileCosts[0];
       const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
-      const float rounds = (float)(tiles / n_cu) + (g.second == GemmPlan::kLdsSuperHalves ? 0.6f : 0.75f);
-      const float chunk_us = (K % 256) == 0 ? sq.chunk_us_super : sq.chunk_us;
-      if (!tail || cost < rounds * (float)(K / 64) * chunk_us + sq.fixed_us) g = t;
+      const float last = g.second == GemmPlan::kLdsSuperHalves ? 0.55f : sq.last_round;
+      const float rounds = tail ? (float)(tiles / n_cu) + last : rounds_of(tiles, n_cu, sq.last_round);
+      const float base = rounds * (float)(K / 64) * (K % 256 == 0 ? sq.chunk_us_super : sq.chunk_us) + sq.fixed_us;
+      float cost, tail_cost;
+      const GemmPlan t = plan_tiles(M, N, K, n_cu, with_ws, &cost);
+      if (cost < kPlanGain * base) g = t; else cost = base;
+      if (with_ws && K % 256 == 0) {
+        const GemmPlan q = plan_square_tiles(M, N, K, n_cu, &tail_cost);
+        if (q.first != GemmPlan::kNone && tail_cost < kPlanGain * cost) g = q;
+      }
     }
   } else {
     const int64_t k_pad = (K + 63) / 64 * 64;
@@ -161,6 +216,10 @@ size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N) {
   const size_t pad = g.k_pad ? pad_bytes(M, g.k_pad) : 0;
   if (g.second == GemmPlan::kLdsSuperHalves)
     return pad + (size_t)2 * (size_t)M * (size_t)parts_row((uint32_t)N - g.n_split) * sizeof(float);
+  if (g.second == GemmPlan::kLdsSuperTiles) {
+    const size_t tiles = (size_t)((M + kSquareTile - 1) / kSquareTile) * (size_t)((N + kSquareTile - 1) / kSquareTile);
+    return pad + (size_t)g.tail_parts * (tiles - g.n_full) * kSquareTile * kSquareTile * sizeof(float);
+  }
   if (g.k_parts > 1) return pad + (size_t)g.k_parts * (size_t)M * (size_t)parts_row((uint32_t)N) * sizeof(float);
   return pad;
 }
@@ -183,6 +242,8 @@ const char* gemm_kernel_name(int kind, bool parts) {
     case GemmPlan::kLdsLowSuper:
       return parts ? "gemm_lds_kernel<LdsLowSuper> (64x256 tiles, scale super-stages, K parts) + sum_parts_kernel"
                    : "gemm_lds_kernel<LdsLowSuper> (64x256 tiles, scale super-stages)";
+    case GemmPlan::kLdsSuperTiles:
+      return "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles of the last round, K parts) + sum_tiles_kernel";
     case GemmPlan::kLdsTall: return "gemm_lds_kernel<LdsTall> (256x128 tiles)";
     case GemmPlan::kLdsSuperHalves:
       return "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, two K halves, FP32 partials) + sum_parts_kernel";
@@ -295,6 +356,13 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
       e = launch_lds_low(o, p, g.first == GemmPlan::kLdsLowSuper, g.k_parts, parts, true, stream);
     if (e != hipSuccess) return e;
     return launch_sum_parts(parts, g.k_parts, (uint32_t)M, (uint32_t)N, y, (uint32_t)ldy, 0, out_f32, stream);
+  }
+  if (g.second == GemmPlan::kLdsSuperTiles) {
+    const uint32_t tiles = (uint32_t)((M + kSquareTile - 1) / kSquareTile) * (uint32_t)((N + kSquareTile - 1) / kSquareTile);
+    hipError_t e = launch_lds_super_tiles(o, p, 0, g.n_full, out_f32, stream);
+    if (e == hipSuccess) e = launch_lds_super_tile_parts(o, p, g.n_full, tiles, g.tail_parts, parts, stream);
+    if (e == hipSuccess) e = launch_sum_tiles(parts, p, g.n_full, tiles, g.tail_parts, y, out_f32, stream);
+    return e;
   }
   hipError_t e = run_one(g.first, o, p, 0, g.n_split, out_f32, aligned, stream);
   if (e != hipSuccess || g.second == GemmPlan::kNone) return e;

@@ -94,6 +94,11 @@ struct GemmParams {
   // k_parts times, each on its own run of chunks, part j writing its partial
   // sums at y + j * part_stride floats.
   uint32_t k_parts, part_stride;
+  // Run of tiles (in tile order) of a launch over part of the output (LDS
+  // kernel): tiles [tile_begin, tile_begin + tile_count); tile_count = 0: all.
+  // With K parts, part j of the i-th of them goes to a tile of its own, rows
+  // of kSquareTile floats, at y + (j * tile_count + i) tiles.
+  uint32_t tile_begin, tile_count;
   // GDN gate epilogue (split-K kernel only): H b-columns, then H a-columns.
   const float* gate_a_log;
   const float* gate_dt_bias;
@@ -425,9 +430,12 @@ constexpr uint32_t kSquareTile = 256;
 struct GemmPlan {
   enum Kind { kNone = 0, kLdsSquare, kLdsSuper, kLdsTall, kSplitkNarrow, kSplitkDecode, kReg, kLdsSuperHalves,
               kLdsMid, kLdsMidSuper, kLdsLow, kLdsLowSuper, kSplitk32x32, kSplitk32x64, kSplitk64x64,
-              kSplitk64x96 };
+              kSplitk64x96, kLdsSuperTiles };
+  // second == kLdsSuperTiles: `first` runs the first n_full square tiles (in
+  // tile order) over all columns, `second` the others in tail_parts runs of K.
   int first, second;
   uint32_t n_split, k_parts;
+  uint32_t n_full, tail_parts;
   // K % 64 != 0 with a workspace: the activation is first copied into it with
   // its rows padded to k_pad = 64 ceil(K / 64) (zero scales past K; the packed
   // weight is padded already), and the kernels above run on that; else 0.
@@ -470,6 +478,14 @@ hipError_t launch_lds_super_f32(const GemmOperands& o, GemmParams p, uint32_t n_
 inline uint32_t parts_row(uint32_t width) { return (width + 3u) & ~3u; }
 hipError_t launch_lds_super_parts(const GemmOperands& o, const GemmParams& p, uint32_t n_begin, uint32_t n_end,
                                   uint32_t k_parts, float* parts, hipStream_t stream);
+// Square tiles [tile_begin, tile_end) of the tile order: whole (bf16 or FP32
+// output), or as k_parts partial tiles each, and the pass that sums those.
+hipError_t launch_lds_super_tiles(const GemmOperands& o, const GemmParams& p, uint32_t tile_begin, uint32_t tile_end,
+                                  bool out_f32, hipStream_t stream);
+hipError_t launch_lds_super_tile_parts(const GemmOperands& o, const GemmParams& p, uint32_t tile_begin,
+                                       uint32_t tile_end, uint32_t k_parts, float* parts, hipStream_t stream);
+hipError_t launch_sum_tiles(const float* parts, const GemmParams& p, uint32_t tile_begin, uint32_t tile_end,
+                            uint32_t k_parts, void* y, bool out_f32, hipStream_t stream);
 hipError_t launch_sum_parts(const float* parts, uint32_t k_parts, uint32_t M, uint32_t width, void* y, uint32_t ldy,
                             uint32_t col0, bool out_f32, hipStream_t stream);
 // 128 x 128 and 64 x 256 tiles over all columns, with scale super-stages

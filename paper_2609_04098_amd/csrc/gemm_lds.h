@@ -256,15 +256,17 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   // read the same K range of A and W, and so share them in the XCD's L2).
   constexpr uint32_t kUnit = C::kSuper ? 4 : 1;
   uint32_t part = 0, kc0 = 0, chunks = p.chunks, tm, tn;
+  uint32_t tile_out = 0;                     // partial tile (tile runs with K parts)
   if (kF32Out && p.k_parts > 1) {
-    const uint32_t tiles = p.tiles_m * p.tiles_n, units = p.chunks / kUnit;
+    const uint32_t tiles = p.tile_count ? p.tile_count : p.tiles_m * p.tiles_n, units = p.chunks / kUnit;
     const uint32_t pid = xcd_contiguous(tiles * p.k_parts);
     part = pid / tiles;
     kc0 = part * units / p.k_parts * kUnit;
     chunks = (part + 1) * units / p.k_parts * kUnit - kc0;
-    tile_at<C::kGroupM>(p, pid - part * tiles, tm, tn);
+    tile_at<C::kGroupM>(p, p.tile_begin + pid - part * tiles, tm, tn);
+    tile_out = pid;
   } else {
-    tile_of<C::kGroupM>(p, tm, tn);
+    tile_at<C::kGroupM>(p, p.tile_begin + xcd_contiguous(p.tile_count ? p.tile_count : p.tiles_m * p.tiles_n), tm, tn);
   }
   const uint32_t wm = wave / WN, wn = wave % WN;
 
@@ -504,7 +506,15 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   }
   // Drain the DMA of the chunks past the end before the workgroup exits.
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  void* yo = kF32Out ? static_cast<void*>(static_cast<float*>(y) + (size_t)part * p.part_stride) : y;
+  void* yo = y;
+  if constexpr (kF32Out) {
+    // A partial tile's element (row, col) sits at row * ldy + col of the whole
+    // output's rows (ldy = kSquareTile for a tile of its own).
+    ptrdiff_t off = (ptrdiff_t)part * p.part_stride;
+    if (p.k_parts > 1 && p.tile_count)
+      off = (ptrdiff_t)tile_out * (BM * BN) - ((ptrdiff_t)tm * BM * p.ldy + (ptrdiff_t)tn * BN);
+    yo = reinterpret_cast<void*>(reinterpret_cast<intptr_t>(y) + off * (ptrdiff_t)sizeof(float));
+  }
   if constexpr (kTransposed) {
     constexpr int kPitch = C::kEpiPitch;
     if constexpr (C::kEpiInRing) __syncthreads();            // every wave has left the ring
@@ -522,7 +532,7 @@ static hipError_t launch_lds_as(const GemmOperands& o, GemmParams p, uint32_t n_
   p.n_off = n_begin;
   p.tiles_m = (p.M + C::BM - 1) / C::BM;
   p.tiles_n = (n_end - n_begin + C::BN - 1) / C::BN;
-  const dim3 grid(p.tiles_m * p.tiles_n * p.k_parts), block(C::kThreads);
+  const dim3 grid((p.tile_count ? p.tile_count : p.tiles_m * p.tiles_n) * p.k_parts), block(C::kThreads);
   const uint32_t lds = kF32Out ? C::kLdsBytes : C::kLdsTotal;
   hipLaunchKernelGGL((gemm_lds_kernel<C, kF32Out>), grid, block, lds, stream, o.a_codes, o.a_scales, o.a_g,
                      o.w_packed, o.w_g, o.y, p);

@@ -56,6 +56,76 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float4* __restrict
   }
 }
 
+hipError_t launch_lds_super_tile_parts(const GemmOperands& o, const GemmParams& p, uint32_t tile_begin,
+                                       uint32_t tile_end, uint32_t k_parts, float* parts, hipStream_t stream) {
+  GemmParams q = p;
+  q.tile_begin = tile_begin;
+  q.tile_count = tile_end - tile_begin;
+  q.k_parts = k_parts;
+  q.ldy = kSquareTile;
+  GemmOperands r = o;
+  r.y = parts;
+  return launch_lds_as<LdsSquareSuper, true>(r, q, 0, p.N, stream);
+}
+
+// The same sum over partial tiles [k_parts][tile_count][kSquareTile][kSquareTile].
+template <bool kF32Out>
+__global__ __launch_bounds__(256) void sum_tiles_kernel(const float4* __restrict__ parts, GemmParams p, uint32_t n4,
+                                                        void* __restrict__ y, bool y_vec) {
+  constexpr uint32_t kTile4 = kSquareTile * kSquareTile / 4, kRow4 = kSquareTile / 4;
+  for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n4; i += gridDim.x * 256u) {
+    uint32_t tm, tn;
+    tile_at<LdsSquareSuper::kGroupM>(p, p.tile_begin + i / kTile4, tm, tn);
+    const uint32_t row = tm * kSquareTile + i % kTile4 / kRow4, col = tn * kSquareTile + i % kRow4 * 4u;
+    if (row >= p.M || col >= p.N) continue;
+    const float4* q = parts + i;
+    float4 a = *q;
+#pragma unroll 4
+    for (uint32_t j = 1; j < p.k_parts; ++j) {
+      q += n4;
+      const float4 b = *q;
+      a.x += b.x;
+      a.y += b.y;
+      a.z += b.z;
+      a.w += b.w;
+    }
+    const float v[4] = {a.x, a.y, a.z, a.w};
+    if (kF32Out) {
+      float* d = static_cast<float*>(y) + (size_t)row * p.ldy + col;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (col + j < p.N) d[j] = v[j];
+    } else {
+      uint16_t* d = static_cast<uint16_t*>(y) + (size_t)row * p.ldy + col;
+      if (y_vec && col + 4 <= p.N) {
+        *reinterpret_cast<uint2*>(d) = make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3]));
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (col + j < p.N) d[j] = f32_to_bf16_rne(v[j]);
+      }
+    }
+  }
+}
+
+hipError_t launch_sum_tiles(const float* parts, const GemmParams& p, uint32_t tile_begin, uint32_t tile_end,
+                            uint32_t k_parts, void* y, bool out_f32, hipStream_t stream) {
+  GemmParams q = p;
+  q.tiles_m = (p.M + kSquareTile - 1) / kSquareTile;
+  q.tiles_n = (p.N + kSquareTile - 1) / kSquareTile;
+  q.tile_begin = tile_begin;
+  q.k_parts = k_parts;
+  const uint32_t n4 = (tile_end - tile_begin) * (kSquareTile * kSquareTile / 4);
+  const dim3 grid(n4 / 256 < 2048 ? n4 / 256 : 2048), block(256);
+  const float4* p4 = reinterpret_cast<const float4*>(parts);
+  const bool y_vec = p.ldy % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0;
+  if (out_f32)
+    hipLaunchKernelGGL(sum_tiles_kernel<true>, grid, block, 0, stream, p4, q, n4, y, false);
+  else
+    hipLaunchKernelGGL(sum_tiles_kernel<false>, grid, block, 0, stream, p4, q, n4, y, y_vec);
+  return hipGetLastError();
+}
+
 hipError_t launch_sum_parts(const float* parts, uint32_t k_parts, uint32_t M, uint32_t width, void* y, uint32_t ldy,
                             uint32_t col0, bool out_f32, hipStream_t stream) {
   const uint32_t w4 = parts_row(width) / 4, n4 = M * w4;

@@ -11,7 +11,7 @@ from oracle import quant as OQ
 from paper_2609_04098_amd import linear as L
 from paper_2609_04098_amd import nvfp4 as C
 from paper_2609_04098_amd import synth
-from tests.gpu_common import bf16_rne_of, check_gemm, log, to_dev_bf16
+from tests.gpu_common import bf16_rne_of, check_gemm, log, to_dev_bf16, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -89,3 +89,35 @@ def test_gemm_k_parts_without_their_workspace():
     C.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y2, C.NVFP4_F32,
                                 None, None, M=aq.m, K=aq.k)
     assert torch.equal(y0, y2)
+
+
+def test_gemm_last_round_in_k_parts():
+    """7000 x 5120 x 17408: 560 tiles of 256 x 256, on 256 CUs two full rounds
+    and 48 tiles in K parts (ragged last tile row); sampled rows of every tile
+    row against the oracle, the bf16 output equal to RNE of the FP32 output,
+    strided output rows, and the first round's columns bit for bit those of
+    nvfp4_gemm."""
+    wl = workload("mlp_down")
+    cfg, m = wl["cfg"], 7000
+    aq = L.quantize_act(to_dev_bf16(wl["x"][:m]), g=float(wl["gx"]))
+    pw = L.pack_weight(to_dev_bf16(wl["w"]), cfg.seg_offsets)
+    kernels = L.gemm_kernels(m, cfg.n, cfg.k)
+    log("%s" % kernels)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert "last round" in kernels[1]
+    need = C.nvfp4_gemm_workspace(m, cfg.n, cfg.k)
+    guard = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    big = torch.full((m, cfg.n + 4), -7.0, dtype=torch.float32, device="cuda")
+    y32 = L.gemm(aq, pw, out=big[:, :cfg.n], workspace=guard[:need])
+    y16 = L.gemm(aq, pw)
+    y_nows = L.gemm_no_workspace(aq, pw, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert bool((guard[need:] == 0x5A).all()) and bool((big[:, cfg.n:] == -7.0).all())
+    assert torch.equal(y16.view(torch.int16), y32.to(torch.bfloat16).view(torch.int16))
+    assert torch.equal(y32[:6144], y_nows[:6144])            # six groups of four tile rows: the full rounds
+    rows = np.array(sorted(set([t * 256 + (t * 37) % 256 for t in range(20, 27)] + list(range(m - 4, m)))))
+    args = (wl["xp"], wl["xs"], wl["gx"], wl["wp"], wl["ws"], wl["gw"], cfg.seg_offsets)
+    y_ref, r_ref = OG.gemm_f64(*args, rows=rows), OG.abs_bound(*args, rows=rows)
+    at = torch.from_numpy(rows).cuda()
+    check_gemm(y32[at].cpu().numpy().astype(np.float64), y_ref, r_ref, "last round in K parts")
+    check_gemm(y_nows[at].cpu().numpy().astype(np.float64), y_ref, r_ref, "no workspace")
