@@ -101,11 +101,11 @@ __global__ __launch_bounds__(kThreads) void amax_partial_kernel(const uint16_t* 
 // thread).  (Walking the blocks from the end of X to its start after the
 // amax pass, so as to meet the most recently read part of X in the MALL,
 // measured 2% slower on a 335 MB activation and is not done.)
-template <bool kContig, bool kHuge>
+template <bool kContig, bool kExact>
 __device__ __forceinline__ void quantize_blocks(const uint16_t* __restrict__ x, uint32_t n_blocks,
                                                 uint32_t blocks_per_row, uint32_t ldx,
                                                 uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                                                float g) {
+                                                float g, float gf4) {
   const float gd6 = g * (1.0f / 6.0f);
   const uint32_t stride = gridDim.x * kThreads;
   auto src_of = [&](uint32_t b) -> const uint4* {
@@ -127,7 +127,7 @@ __device__ __forceinline__ void quantize_blocks(const uint16_t* __restrict__ x, 
     }
     const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
     uint32_t c0, c1;
-    const uint32_t sc = quantize_block<kHuge>(v, g, gd6, c0, c1);
+    const uint32_t sc = quantize_block_as<kExact>(v, g, gd6, gf4, c0, c1);
     reinterpret_cast<uint2*>(codes)[b] = make_uint2(c0, c1);
     scales[b] = (uint8_t)sc;
     d0 = e0;
@@ -153,11 +153,12 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(
   } else {
     g = *g_enc;
   }
-  // The scale path is chosen per tensor, uniformly across the launch.
-  if (g > kHugeScale)
-    quantize_blocks<kContig, true>(x, n_blocks, blocks_per_row, ldx, codes, scales, g);
+  // The form is chosen per tensor, uniformly across the launch.
+  const QuantMode q = quant_mode(g);
+  if (q.exact)
+    quantize_blocks<kContig, true>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.0f);
   else
-    quantize_blocks<kContig, false>(x, n_blocks, blocks_per_row, ldx, codes, scales, g);
+    quantize_blocks<kContig, false>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.25f * q.gf);
 }
 
 __global__ void write_zero_scale_kernel(float* g_enc) { *g_enc = 0.0f; }
@@ -218,13 +219,14 @@ __global__ __launch_bounds__(kSmallThreads) void act_quant_small_kernel(
   } else {
     g = *g_enc;
   }
+  const QuantMode q = quant_mode(g);                           // before any lane leaves
   if (b >= n_blocks) return;
   const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
   uint32_t c0, c1, sc;
-  if (g > kHugeScale)
-    sc = quantize_block<true>(v, g, g * (1.0f / 6.0f), c0, c1);
+  if (q.exact)
+    sc = quantize_block_as<true>(v, g, g * (1.0f / 6.0f), 0.0f, c0, c1);
   else
-    sc = quantize_block<false>(v, g, g * (1.0f / 6.0f), c0, c1);
+    sc = quantize_block_as<false>(v, g, g * (1.0f / 6.0f), 0.25f * q.gf, c0, c1);
   reinterpret_cast<uint2*>(codes)[b] = make_uint2(c0, c1);
   scales[b] = (uint8_t)sc;
 }

@@ -120,6 +120,7 @@ __device__ float quantize_into_lds(const DecodeQuantArgs& q, const GemmParams& p
     g = *q.g_enc;
   }
   const float gd6 = g * (1.0f / 6.0f);
+  const QuantMode qm = quant_mode(g);
   const bool out = q.codes != nullptr && blockIdx.x == 0;
   // All blocks first, then the LDS writes: a write to LDS waits for the
   // weight ring's direct-to-LDS loads issued before it (the compiler cannot
@@ -129,10 +130,10 @@ __device__ float quantize_into_lds(const DecodeQuantArgs& q, const GemmParams& p
   for (int t = 0; t < kSlots; ++t) {
     const uint32_t b = threadIdx.x + t * kThreads;
     if (b < n_blocks) {
-      if (g > kHugeScale)
-        c[t][2] = quantize_block<true>(v[t], g, gd6, c[t][0], c[t][1]);
+      if (qm.exact)
+        c[t][2] = quantize_block_as<true>(v[t], g, gd6, 0.0f, c[t][0], c[t][1]);
       else
-        c[t][2] = quantize_block<false>(v[t], g, gd6, c[t][0], c[t][1]);
+        c[t][2] = quantize_block_as<false>(v[t], g, gd6, 0.25f * qm.gf, c[t][0], c[t][1]);
     }
   }
 #pragma unroll

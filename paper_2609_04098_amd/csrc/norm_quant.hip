@@ -39,9 +39,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 
 // Normalize, round to bf16 and quantize block b of one row (d0, d1: its
 // 16 bf16 values).
-template <bool kHuge>
+template <bool kExact>
 __device__ __forceinline__ void norm_quant_block(uint4 d0, uint4 d1, uint32_t b, const uint4* __restrict__ gr,
-                                                 float r, float g, float gd6, uint2* __restrict__ codes_row,
+                                                 float r, float g, float gd6, float gf4, uint2* __restrict__ codes_row,
                                                  uint8_t* __restrict__ scales_row, uint4* __restrict__ y_row) {
   const uint4 e0 = gr[2 * b], e1 = gr[2 * b + 1];
   const uint32_t xv[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
@@ -55,7 +55,7 @@ __device__ __forceinline__ void norm_quant_block(uint4 d0, uint4 d1, uint32_t b,
     y_row[2 * b + 1] = make_uint4(v[4], v[5], v[6], v[7]);
   }
   uint32_t c0, c1;
-  const uint32_t sc = quantize_block<kHuge>(v, g, gd6, c0, c1);
+  const uint32_t sc = quantize_block_as<kExact>(v, g, gd6, gf4, c0, c1);
   codes_row[b] = make_uint2(c0, c1);
   scales_row[b] = (uint8_t)sc;
 }
@@ -125,21 +125,23 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_kernel(
   uint8_t* scales_row = scales + (size_t)row * nb;
   uint4* y_row = y == nullptr ? nullptr : reinterpret_cast<uint4*>(y + (size_t)row * ldy);
   const float gd6 = g * (1.0f / 6.0f);
-  auto pass2 = [&](auto huge_tag) {
-    constexpr bool kHuge = decltype(huge_tag)::value;
+  const QuantMode qm = quant_mode(g);
+  const float gf4 = 0.25f * qm.gf;
+  auto pass2 = [&](auto exact_tag) {
+    constexpr bool kExact = decltype(exact_tag)::value;
     if constexpr (kPerLane > 0) {
       // From the registers of pass 1: X is read from memory once.
 #pragma unroll
       for (int j = 0; j < kPerLane; ++j) {
         const uint32_t b = lane + 64u * j;
-        if (b < nb) norm_quant_block<kHuge>(d[j][0], d[j][1], b, gr, r, g, gd6, codes_row, scales_row, y_row);
+        if (b < nb) norm_quant_block<kExact>(d[j][0], d[j][1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
       }
     } else {
       for (uint32_t b = lane; b < nb; b += 64)
-        norm_quant_block<kHuge>(xr[2 * b], xr[2 * b + 1], b, gr, r, g, gd6, codes_row, scales_row, y_row);
+        norm_quant_block<kExact>(xr[2 * b], xr[2 * b + 1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
     }
   };
-  if (g > kHugeScale)
+  if (qm.exact)
     pass2(std::integral_constant<bool, true>{});
   else
     pass2(std::integral_constant<bool, false>{});
@@ -190,15 +192,17 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_pair_kernel(
   uint8_t* scales_row = scales + (size_t)row * nb;
   uint4* y_row = y == nullptr ? nullptr : reinterpret_cast<uint4*>(y + (size_t)row * ldy);
   const float gd6 = g * (1.0f / 6.0f);
-  auto pass2 = [&](auto huge_tag) {
-    constexpr bool kHuge = decltype(huge_tag)::value;
+  const QuantMode qm = quant_mode(g);
+  const float gf4 = 0.25f * qm.gf;
+  auto pass2 = [&](auto exact_tag) {
+    constexpr bool kExact = decltype(exact_tag)::value;
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
       const uint32_t b = 64u * hw + lane + 128u * j;
-      if (b < nb) norm_quant_block<kHuge>(d[j][0], d[j][1], b, gr, r, g, gd6, codes_row, scales_row, y_row);
+      if (b < nb) norm_quant_block<kExact>(d[j][0], d[j][1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
     }
   };
-  if (g > kHugeScale)
+  if (qm.exact)
     pass2(std::integral_constant<bool, true>{});
   else
     pass2(std::integral_constant<bool, false>{});

@@ -222,4 +222,89 @@ __device__ __forceinline__ uint32_t quantize_block(const uint32_t v[8], float g,
   return bs.code;
 }
 
+// ---------------------------------------------------------------- fast form
+//
+// One multiplication per element instead of the exact decision, where that is
+// provably the same.  A bf16 magnitude is an integer of at most 8 bits times a
+// power of two, a midpoint times a block scale is mu times one, mu = {1, 3, 5,
+// 7} x {8 .. 15} (the midpoints' and the E4M3 scales' significands).  So for a
+// given G only the 32 values mu / G matter: a threshold that is no bf16 value
+// to within 2^-20 (relative) cannot be crossed by the rounding errors of
+// fl(x fl(G / S)), below 5 * 2^-24 = 2^-21.6 (the reciprocal 2^-23, three
+// roundings 2^-24 each).  A threshold that is one (with G = fl(2688 / amax)
+// many products are a midpoint but for the rounding of G) is on one known side
+// of it; scaling G by 1 +- 2^-21 moves the product past the error to that
+// side, and no further threshold than 2^-20 with it.  quant_mode decides once
+// per wave: `exact` if the sides differ or an exact tie exists (G = 2688 /
+// amax exact), or for G outside [2^-100, 2^100].
+//
+// Per element: widening, the product, half a conversion (2.5 instructions
+// against 7.5 of the exact decision).
+struct QuantMode {
+  bool exact;
+  float gf;     // G, or G (1 +- 2^-21)
+};
+
+// All 64 lanes of the wave take part, with the same g.
+__device__ __forceinline__ QuantMode quant_mode(float g) {
+  const uint32_t lane = threadIdx.x & 31u;
+  const uint32_t gb = __float_as_uint(g);
+  const float gm = __uint_as_float((gb & 0x007FFFFFu) | 0x3F800000u);        // significand of G, [1, 2)
+  const float mu = (float)((2u * (lane & 3u) + 1u) * (8u + (lane >> 2)));
+  const float t = mu / gm;
+  // Power of two that brings t to [128, 256).
+  const float p = __uint_as_float((127u + 7u + 127u - (__float_as_uint(t) >> 23)) << 23);
+  const float x = __builtin_rintf(t * p);                                    // the only bf16 significand near it
+  const float m = mu * p;
+  const float e = __builtin_fmaf(x, gm, -m);                                 // sign of x G - mu 2^k, exactly
+  const bool near = __builtin_fabsf(e) <= m * 0x1p-20f;
+  const uint64_t above = __ballot(near && e > 0.0f), below = __ballot(near && e < 0.0f);
+  const uint64_t tie = __ballot(near && e == 0.0f);
+  QuantMode q;
+  q.exact = tie != 0 || (above != 0 && below != 0) || !(g >= 0x1p-100f && g <= 0x1p100f);
+  q.gf = __builtin_fmaf(g, above ? 0x1p-21f : below ? -0x1p-21f : 0.0f, g);
+  return q;
+}
+
+// quantize_block for a tensor whose quant_mode is not exact (gf4 = gf / 4).
+template <bool kBranch = true>
+__device__ __forceinline__ uint32_t quantize_block_fast(const uint32_t v[8], float g, float gd6, float gf4,
+                                                        uint32_t& c0, uint32_t& c1) {
+  float f[16];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    f[2 * i] = bf16_lo(v[i]);
+    f[2 * i + 1] = bf16_hi(v[i]);
+  }
+  float amax_b = max3_abs(f[0], f[1], f[2]);
+#pragma unroll
+  for (int i = 3; i < 15; i += 2) amax_b = max3_abs(amax_b, f[i], f[i + 1]);
+  amax_b = max3_abs(amax_b, f[15], f[15]);
+  const BlockScale bs = block_scale<kBranch>(amax_b, g, gd6);
+  const float c = gf4 * bs.rq4;                                              // ~ G / S (0 when S = 0)
+  uint32_t r[2] = {0u, 0u};
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const float* u = f + 8 * w;
+    r[w] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r[w], u[0] * c, u[1] * c, 1.0f, 0);
+    r[w] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r[w], u[2] * c, u[3] * c, 1.0f, 1);
+    r[w] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r[w], u[4] * c, u[5] * c, 1.0f, 2);
+    r[w] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r[w], u[6] * c, u[7] * c, 1.0f, 3);
+  }
+  c0 = r[0];
+  c1 = r[1];
+  return bs.code;
+}
+
+// One block in the form `kExact` of a tensor's quant_mode (gf4:
+// gf / 4 of the fast form, unused in the exact one).
+template <bool kExact, bool kBranch = true>
+__device__ __forceinline__ uint32_t quantize_block_as(const uint32_t v[8], float g, float gd6, float gf4,
+                                                      uint32_t& c0, uint32_t& c1) {
+  if constexpr (kExact)
+    return quantize_block<true, kBranch>(v, g, gd6, c0, c1);
+  else
+    return quantize_block_fast<kBranch>(v, g, gd6, gf4, c0, c1);
+}
+
 }  // namespace nvfp4
