@@ -18,7 +18,7 @@ OBJ_CACHE = os.path.join(HERE, "_build")
 
 SOURCES = ["api.cpp", "act_quant.hip", "norm_quant.hip", "weight_pack.hip", "gemm.hip", "gemm_lds_square.hip",
            "gemm_lds_super.hip", "gemm_lds_super_f32.hip", "gemm_lds_tall.hip", "gemm_lds_mid.hip", "gemm_lds_low.hip",
-           "gemm_splitk.hip", "gemm_reg.hip", "quant_gemm.hip"]
+           "gemm_splitk.hip", "gemm_rows16.hip", "gemm_reg.hip", "quant_gemm.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -258,9 +258,11 @@ const char* gemm_kernel_name(int kind, bool parts) {
 
 static const char* decode_kernel_name(DecodeShape d) {
   switch (d) {
+    case DecodeShape::kRows16w1: return "gemm_rows16_kernel<16,1,2> (16x32 tiles, split-K)";
+    case DecodeShape::kRows8w2: return "gemm_rows16_kernel<8,2,2> (16x64 tiles, split-K)";
+    case DecodeShape::kRows8w3: return "gemm_rows16_kernel<8,3,2> (16x96 tiles, split-K)";
+    case DecodeShape::kRows4w2: return "gemm_rows16_kernel<4,2,3> (16x64 tiles, split-K)";
     case DecodeShape::k4Private: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
-    case DecodeShape::k8Private: return "gemm_splitk_kernel<8,1,1,3> (32x32 tiles, split-K, per-wave rings)";
-    case DecodeShape::k16Private: return "gemm_splitk_kernel<16,1,1,3> (32x32 tiles, split-K, per-wave rings)";
     case DecodeShape::k4Shared: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, shared activation ring)";
     case DecodeShape::k8Shared: return "gemm_splitk_kernel<8,1,1,4> (32x32 tiles, split-K, shared activation ring)";
     default: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";

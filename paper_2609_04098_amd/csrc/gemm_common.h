@@ -457,9 +457,11 @@ const char* gemm_kernel_name(int kind, bool parts);
 // Compute units of the current device (cached per device, thread-safe).
 uint32_t cu_count();
 
-// Split-K form of a decode shape (M <= 32): waves per tile, per-wave or
-// shared activation rings, one or (pair) two weight fragments per workgroup.
-enum class DecodeShape { k4Private, k8Private, k16Private, k4Shared, k4SharedPair, k8Shared };
+// Form of a decode shape (M <= 32).  At most 16 rows: gemm_rows16_kernel,
+// waves and 32-column weight tiles per workgroup; more: the split-K kernel,
+// waves per tile, per-wave or shared activation rings, one or (pair) two weight
+// tiles per workgroup.
+enum class DecodeShape { kRows16w1, kRows8w2, kRows8w3, kRows4w2, k4Private, k4Shared, k4SharedPair, k8Shared };
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu);
 // Weight fragments (1..3) per 32-row tile of 8 waves for a tall-skinny output
 // (N <= 96), or 0: 64 x 96 tiles of 4 waves.
@@ -514,6 +516,10 @@ struct DecodeQuantArgs {
   uint8_t* codes;           // optional outputs ([M x K/2], [M x K/16]), written by workgroup 0
   uint8_t* scales;
 };
+hipError_t launch_rows16(DecodeShape shape, const GemmOperands& o, const GemmParams& p, bool out_f32,
+                         hipStream_t stream);
+hipError_t launch_rows16_quant(DecodeShape shape, const GemmOperands& o, const GemmParams& p, const DecodeQuantArgs& q,
+                               bool dynamic, bool out_f32, hipStream_t stream);
 hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
                                     bool out_f32, hipStream_t stream);
 // Register path (K % 64 != 0).

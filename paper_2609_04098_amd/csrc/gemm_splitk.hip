@@ -1,6 +1,6 @@
 // Split-K NVFP4 GEMM for outputs with few 32 x 32 tiles (tall-skinny gate
 // projections, decode-shaped calls).
-#include "gemm_common.h"
+#include "gemm_splitk.h"
 
 namespace nvfp4 {
 
@@ -25,146 +25,6 @@ namespace nvfp4 {
 // fragments from LDS while it decodes and multiplies the current one, and
 // the partial sums meet in LDS at the end; fragment f is summed in wave
 // order (deterministic) and stored by wave f % KS.  Requires K % 64 == 0.
-
-// Activation quantization fused in front of the split-K GEMM, one launch,
-// for decode shapes whose whole activation fits in LDS (kQuant = 1 with a
-// given G, 2 with the dynamic G).  Every workgroup reads all of X (a few KB
-// to a few tens of KB, from L2 after the first workgroup), takes the global
-// maximum itself in dynamic mode (the maximum is order-free, so every
-// workgroup forms the same G), quantizes every block with the stand-alone
-// quantizer's device code into LDS, and the GEMM then reads its activation
-// fragments from LDS instead of streaming them: one launch, no hand-off
-// between workgroups, and the results of nvfp4_quantize_act + nvfp4_gemm
-// bit for bit (same codes, same summation order).  Workgroup 0 also writes
-// G and, when asked for, the codes and scales.
-
-// Workgroup barrier for LDS data only: waits for this wave's LDS accesses,
-// not for its outstanding global loads (__syncthreads' fence would also wait
-// for the weight ring's DMA issued before the activation is quantized).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(lds::kWaitLgkm0);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Maximum over the workgroup (kThreads threads) of a non-negative value.
-template <int kThreads>
-__device__ __forceinline__ uint32_t wg_max_u32(uint32_t v, uint32_t* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint32_t o = __shfl_xor(v, off, 64);
-    v = v > o ? v : o;
-  }
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  lds_barrier();
-  uint32_t r = red[0];
-#pragma unroll
-  for (int w = 1; w < kThreads / 64; ++w) r = r > red[w] ? r : red[w];
-  lds_barrier();
-  return r;
-}
-
-// The 8 dwords (16 bf16) of block b of X (row-major blocks, bpr per row).
-__device__ __forceinline__ void load_x_block(const DecodeQuantArgs& q, uint32_t b, uint32_t bpr, uint32_t v[8]) {
-  const uint32_t row = b / bpr, col = b - row * bpr;
-  const uint4* src = reinterpret_cast<const uint4*>(q.x + (size_t)row * q.ldx) + 2 * col;
-  const uint4 d0 = src[0], d1 = src[1];
-  v[0] = d0.x; v[1] = d0.y; v[2] = d0.z; v[3] = d0.w;
-  v[4] = d1.x; v[5] = d1.y; v[6] = d1.z; v[7] = d1.w;
-}
-
-// Quantize all of X into the LDS activation (codes [M][K/2], then scales
-// [M][K/16]); returns G.  X has at most kDecodeFuseMaxBlocks blocks (the
-// launcher's bound): each thread loads its blocks once (load_x_slots, issued
-// before the weight's first ring stages, so that waiting for X does not
-// wait for them too: the memory counter counts loads in issue order) and
-// keeps them in registers from the maximum to the quantization.
-template <int kThreads>
-struct XSlots {
-  static constexpr int kSlots = kDecodeFuseMaxBlocks / kThreads;
-  static_assert(kSlots * kThreads == kDecodeFuseMaxBlocks, "blocks per thread");
-  uint32_t v[kSlots][8];
-};
-
-template <int kThreads>
-__device__ __forceinline__ void load_x_slots(const DecodeQuantArgs& q, const GemmParams& p, XSlots<kThreads>& xs) {
-  const uint32_t bpr = p.K >> 4, n_blocks = p.M * bpr;
-#pragma unroll
-  for (int t = 0; t < XSlots<kThreads>::kSlots; ++t) {
-    const uint32_t b = threadIdx.x + t * kThreads;
-    if (b < n_blocks) load_x_block(q, b, bpr, xs.v[t]);
-  }
-}
-
-template <int kThreads, bool kDynamic>
-__device__ float quantize_into_lds(const DecodeQuantArgs& q, const GemmParams& p, XSlots<kThreads>& xs,
-                                   uint8_t* lds_codes, uint8_t* lds_scales, uint32_t* red) {
-  constexpr int kSlots = XSlots<kThreads>::kSlots;
-  const uint32_t bpr = p.K >> 4, n_blocks = p.M * bpr;
-  uint32_t (&v)[kSlots][8] = xs.v;
-  uint32_t m = 0;
-#pragma unroll
-  for (int t = 0; t < kSlots; ++t) {
-    const uint32_t b = threadIdx.x + t * kThreads;
-    if (kDynamic && b < n_blocks) {
-      const uint32_t a = __float_as_uint(block_amax(v[t]));
-      m = m > a ? m : a;                     // non-negative floats order as integers
-    }
-  }
-  float g;
-  if (kDynamic) {
-    g = global_scale(__uint_as_float(wg_max_u32<kThreads>(m, red)));
-    if (blockIdx.x == 0 && threadIdx.x == 0) *q.g_enc = g;
-  } else {
-    g = *q.g_enc;
-  }
-  const float gd6 = g * (1.0f / 6.0f);
-  const QuantMode qm = quant_mode(g);
-  const bool out = q.codes != nullptr && blockIdx.x == 0;
-  // All blocks first, then the LDS writes: a write to LDS waits for the
-  // weight ring's direct-to-LDS loads issued before it (the compiler cannot
-  // tell the addresses apart), so the quantization runs before that wait.
-  uint32_t c[kSlots][3];
-#pragma unroll
-  for (int t = 0; t < kSlots; ++t) {
-    const uint32_t b = threadIdx.x + t * kThreads;
-    if (b < n_blocks) {
-      if (qm.exact)
-        c[t][2] = quantize_block_as<true>(v[t], g, gd6, 0.0f, c[t][0], c[t][1]);
-      else
-        c[t][2] = quantize_block_as<false>(v[t], g, gd6, 0.25f * qm.gf, c[t][0], c[t][1]);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < kSlots; ++t) {
-    const uint32_t b = threadIdx.x + t * kThreads;
-    if (b < n_blocks) {
-      reinterpret_cast<uint2*>(lds_codes)[b] = make_uint2(c[t][0], c[t][1]);
-      lds_scales[b] = (uint8_t)c[t][2];
-      if (out) {
-        reinterpret_cast<uint2*>(q.codes)[b] = make_uint2(c[t][0], c[t][1]);
-        q.scales[b] = (uint8_t)c[t][2];
-      }
-    }
-  }
-  lds_barrier();
-  return g;
-}
-
-// Wait until at most rem * kL loads of this wave are outstanding (rem <= R;
-// rem < 0 waits for all).
-template <int kL, int R>
-__device__ __forceinline__ void wait_rem(int rem) {
-  if constexpr (R <= 0) {
-    __builtin_amdgcn_s_waitcnt(lds::vmcnt_imm(0));
-  } else {
-    if (rem >= R)
-      __builtin_amdgcn_s_waitcnt(lds::vmcnt_imm(R * kL));
-    else
-      wait_rem<kL, R - 1>(rem);
-  }
-}
 
 template <int KS, int FM, int FN, int kStages, bool kF32Out, bool kGate, int kQuant = 0, bool kShareA = true>
 __global__ __launch_bounds__(KS * 64, KS < 8 ? 2 : KS / 4) void gemm_splitk_kernel(const uint8_t* __restrict__ a_codes,
@@ -523,41 +383,46 @@ hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f3
   return gate ? launch_narrow<true>(o, p, out_f32, stream) : launch_narrow<false>(o, p, out_f32, stream);
 }
 
-// Decode shapes (M <= 32).  Each output column's sum runs in the order of the
-// number of waves (4, 8 or 16) that share it, whatever the tile.  Measured,
-// same box, W cycled through copies larger than the last-level cache:
-//  * at most one 32-column tile per CU (N <= 8192): the CUs hold one
-//    workgroup each, so more waves per workgroup keep more of W in flight
-//    (per-wave rings; 8 waves: 1 x 8192 x 5120 9.9 -> 7.8 us, 4 x 4352 x 5120
-//    9.6 -> 7.6, 12 x 5120 x 17408 35.2 -> 19.3; 16 waves for long K: 4 x
-//    5120 x 17408 24.5 -> 17.6).  Above 16 rows the activation loads of
-//    per-wave rings cost more: 4 waves (32 x 8192 x 5120 13.7 -> 9.7 us), and
-//    for long K 8 waves with a shared activation ring (32 x 5120 x 17408
-//    35.5 -> 21.2 us);
-//  * more tiles: 4 waves; up to 8 rows per-wave rings and one weight fragment
-//    per workgroup (1 and 7 x 34816 x 5120: 25.0 us against 27.5 with two),
-//    above that a shared activation ring, with one fragment while the tiles
-//    are few (32 x 17408 x 5120: 18.9 us against 19.8 with two), then with
-//    two (32 x 34816 x 5120: 28.4 against 28.8 with one).
+// Decode shapes (M <= 32).  The order of an output column's sum follows from
+// the number of waves that share it, so the fused quantize + GEMM launch
+// (M * K <= 16 * kDecodeFuseMaxBlocks) takes the same form as the plain one.
+// Measured, same box, W cycled through copies larger than the last-level cache:
+//  * up to 16 rows (gemm_rows16_kernel).  At most one 32-column tile per CU: 16
+//    waves (1 x 8192 x 5120 fused 9.1 us with 8-wave 32 x 32 tiles, 7.7 with
+//    this; 4 x 5120 x 17408 18.8 with 16-wave 32 x 32 tiles, 16.1).  More: 8
+//    waves and two tiles (1 x 8704 x 5120 fused 13.1 -> 10.1), three while that
+//    makes no more workgroups than CUs, and for the fused launch (every
+//    workgroup quantizes X) beyond: 1 x 17408 x 5120 fused 19.1 -> 13.5, 16 x
+//    17408 x 5120 18.2 -> 14.0, 1 x 34816 x 5120 fused 27.4 -> 22.7 (23.8 with
+//    4 waves and two tiles).  Else 4 waves and two tiles (4 and 16 x 34816 x
+//    5120 25.1 -> 22.0 and 28.6 -> 24.3; 23.9 and 26.1 with 8 waves and three).
+//  * 17 to 32 rows, at most one tile per CU: 4 waves with per-wave rings
+//    (32 x 8192 x 5120: two tiles per workgroup and a shared activation ring
+//    13.7 us, this 9.7), for long K 8 waves with a shared ring (32 x 5120 x
+//    17408 35.5 -> 21.2).
+//  * more tiles: a shared activation ring, with one tile per workgroup while
+//    they are few (32 x 17408 x 5120: 18.9 us against 19.8 with two), then
+//    with two (32 x 34816 x 5120: 28.4 against 28.8 with one).
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
   const uint64_t tiles = (uint64_t)((N + 31) / 32);
-  const bool long_k = K >= 8192;
-  if (tiles <= n_cu) {
-    if (M <= 16) return long_k && M <= 8 ? DecodeShape::k16Private : DecodeShape::k8Private;
-    return long_k ? DecodeShape::k8Shared : DecodeShape::k4Private;
+  if (M <= 16) {
+    if (tiles <= n_cu) return DecodeShape::kRows16w1;
+    if (5 * tiles < 9 * (uint64_t)n_cu) return DecodeShape::kRows8w2;        // three: under 0.6 of the CUs
+    if (tiles <= 3 * (uint64_t)n_cu || M * K <= 16 * (int64_t)kDecodeFuseMaxBlocks) return DecodeShape::kRows8w3;
+    return DecodeShape::kRows4w2;
   }
-  if (M <= 8) return DecodeShape::k4Private;
+  if (tiles <= n_cu) return K >= 8192 ? DecodeShape::k8Shared : DecodeShape::k4Private;
   return 2 * tiles <= 5 * (uint64_t)n_cu ? DecodeShape::k4Shared : DecodeShape::k4SharedPair;
 }
 
 hipError_t launch_splitk_decode(const GemmOperands& o, GemmParams p, bool out_f32, hipStream_t stream) {
-  switch (decode_shape(p.M, p.N, p.K, cu_count())) {
+  const DecodeShape shape = decode_shape(p.M, p.N, p.K, cu_count());
+  switch (shape) {
     case DecodeShape::k4Private: return launch_splitk<4, 1, 1, 3, false, false>(o, p, out_f32, stream);
-    case DecodeShape::k8Private: return launch_splitk<8, 1, 1, 3, false, false>(o, p, out_f32, stream);
-    case DecodeShape::k16Private: return launch_splitk<16, 1, 1, 3, false, false>(o, p, out_f32, stream);
     case DecodeShape::k4Shared: return launch_splitk<4, 1, 1, 3, true, false>(o, p, out_f32, stream);
     case DecodeShape::k8Shared: return launch_splitk<8, 1, 1, 4, true, false>(o, p, out_f32, stream);
-    default: return launch_splitk<4, 1, 2, 3, true, false>(o, p, out_f32, stream);
+    case DecodeShape::k4SharedPair: return launch_splitk<4, 1, 2, 3, true, false>(o, p, out_f32, stream);
+    default: return launch_rows16(shape, o, p, out_f32, stream);
   }
 }
 
@@ -572,12 +437,10 @@ hipError_t launch_splitk_tile(const GemmOperands& o, const GemmParams& p, int ki
   }
 }
 
-// The fused decode launch: as many waves per tile as decode_shape gives (the
-// same order of sums).  Four waves: two weight fragments per workgroup, a ring
-// one stage deeper than the plain decode kernel's (4 instead of 3: more of
-// the weight in flight while the workgroup quantizes X; one token 33.0 ->
-// 32.6 us, same box), which still leaves three workgroups per CU (36 KB of
-// ring + the 9 KB static array of the quantized activation each).
+// The fused decode launch, in the form of decode_shape.  Above 16 rows (K below
+// 1024) four waves and two weight tiles per workgroup, a ring one stage deeper
+// than the plain kernel's: more of the weight in flight while the workgroup
+// quantizes X.
 template <int KS, int FN, int kStages>
 static hipError_t launch_decode_quant(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
                                       bool out_f32, hipStream_t stream) {
@@ -600,12 +463,9 @@ static hipError_t launch_decode_quant(const GemmOperands& o, GemmParams p, const
 
 hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
                                     bool out_f32, hipStream_t stream) {
-  switch (decode_shape(p.M, p.N, p.K, cu_count())) {
-    case DecodeShape::k16Private: return launch_decode_quant<16, 1, 4>(o, p, q, dynamic, out_f32, stream);
-    case DecodeShape::k8Private:
-    case DecodeShape::k8Shared: return launch_decode_quant<8, 1, 4>(o, p, q, dynamic, out_f32, stream);
-    default: return launch_decode_quant<4, 2, 4>(o, p, q, dynamic, out_f32, stream);
-  }
+  if (p.M <= 16)
+    return launch_rows16_quant(decode_shape(p.M, p.N, p.K, cu_count()), o, p, q, dynamic, out_f32, stream);
+  return launch_decode_quant<4, 2, 4>(o, p, q, dynamic, out_f32, stream);
 }
 
 }  // namespace nvfp4

@@ -1,6 +1,6 @@
-"""GPU parity of the split-K kernel's shapes (4, 8 and 16 waves per tile,
-per-wave and shared activation rings, 1 to 3 weight fragments) on either side
-of the dispatch rules, against the CPU oracle: the plain GEMM, the fused
+"""GPU parity of the decode kernels' shapes (16 x 16 and 32 x 32 products, 4, 8
+and 16 waves per tile, per-wave and shared activation rings, 1 to 3 weight
+tiles) on either side of the dispatch rules, against the CPU oracle: the plain GEMM, the fused
 quantize + GEMM (which must sum in the same order) and the gate epilogue."""
 
 import numpy as np
@@ -45,16 +45,20 @@ def _check(m, n, k, offs):
 
 
 @pytest.mark.parametrize("m,n,k,offs", [
-    (1, 200, 64, [0, 200]),                # one chunk for 8 waves
-    (3, 290, 5120, [0, 100, 290]),         # 8 waves, one launch (fused quantizer)
-    (16, 8192, 576, [0, 4096, 8192]),      # one tile per CU, 9 chunks over 8 waves, most rows of the 8-wave form
-    (17, 8192, 512, [0, 8192]),            # the fewest rows of the 4-wave form
-    (16, 8193, 512, [0, 8193]),            # one tile past one per CU: shared ring, one fragment
-    (9, 20480, 192, [0, 20480]),           # most tiles with one fragment
-    (9, 20481, 192, [0, 20481]),           # fewest tiles with two
-    (1, 160, 8192, [0, 160]),              # long K: 16 waves, one launch
+    (1, 200, 64, [0, 200]),                # one chunk for 16 waves
+    (3, 290, 5120, [0, 100, 290]),         # one launch (fused quantizer), 80 chunks over 16 waves
+    (16, 8192, 1088, [0, 4096, 8192]),     # one tile per CU, 17 chunks over 16 waves, most rows of 16 x 16 products
+    (17, 8192, 512, [0, 8192]),            # the fewest rows of 32 x 32 products
+    (16, 8193, 512, [0, 8193]),            # one tile past one per CU: two tiles for 8 waves, ragged N
+    (2, 14720, 320, [0, 14720]),           # 460 tiles: the most in twos, 5 chunks over 8 waves, one launch
+    (9, 14721, 320, [0, 9999, 14721]),     # 461 tiles: the fewest in threes
+    (16, 24576, 1088, [0, 24576]),         # 768 tiles: a workgroup of three per CU
+    (16, 24577, 1088, [0, 24577]),         # one more: two tiles for 4 waves
+    (15, 24609, 1088, [0, 24609]),         # ... and at the one-launch limit (M K = 16320): three for 8 waves
+    (17, 20480, 192, [0, 20480]),          # most tiles with one weight tile per workgroup
+    (17, 20481, 192, [0, 20481]),          # fewest tiles with two
+    (1, 160, 8192, [0, 160]),              # long K, one launch
     (8, 170, 8256, [0, 85, 170]),          # long K: 129 chunks over 16 waves
-    (9, 170, 8256, [0, 170]),              # long K, 9 rows: 8 waves
     (20, 170, 8192, [0, 170]),             # long K, more rows: shared ring of 4 stages
     (32, 140, 17408, [0, 140]),
 ])
