@@ -291,61 +291,57 @@ __device__ __forceinline__ void segment_alpha(const GemmParams& p, float ga, con
 }
 
 // Split-K epilogue: the KS waves' partial sums meet in LDS, kGroup fragments
-// at a time (part: kGroup x KS x 64 floatx16), and are summed in wave order
-// (deterministic).  Plain outputs of 4 waves: fragment f is summed and stored
-// by wave f % KS.  With the GDN gate transform (kGate), whose transcendentals
-// dominate the epilogue, and with more waves, every wave takes 16 / KS of each
-// lane's 16 accumulator entries of every fragment instead, so that all waves
-// share that work.  Each value is scaled by its column's alpha.  LDS at part
-// must be free (a caller that used it for other data synchronizes first).
+// at a time, and are summed in wave order (deterministic).  Every wave takes
+// 16 / KS of each lane's 16 accumulator entries of every fragment, so that all
+// waves share the sums, the stores and the GDN gate transform (kGate).  A
+// wave's partial fragment lies as 4 quads of 4 entries, 16 bytes per lane side
+// by side (a lane's 64 bytes in one piece put the lanes of an access on the
+// same banks: half of the kernel's LDS cycles at 100 x 34816 x 5120 were bank
+// conflicts).  Each value is scaled by its column's alpha.  LDS at part
+// (kGroup x KS x 4 KB) must be free (a caller that used it for other data
+// synchronizes first).
 template <int KS, int FM, int FN, int kGroup, bool kF32Out, bool kGate>
-__device__ __forceinline__ void splitk_epilogue(const floatx16 (&acc)[FM][FN], floatx16* part, const GemmParams& p,
+__device__ __forceinline__ void splitk_epilogue(const floatx16 (&acc)[FM][FN], float* part, const GemmParams& p,
                                                 const float (&alpha)[FN], void* __restrict__ y,
                                                 uint32_t m0, uint32_t n0, uint32_t wave, uint32_t lane) {
-  static_assert(16 % KS == 0, "entries per wave");
+  static_assert(KS == 4 || KS == 8 || KS == 16, "entries per wave");
   constexpr int kPer = 16 / KS, kFrags = FM * FN;
-  constexpr bool kSpread = kGate || KS > 4;
+  typedef float entries __attribute__((ext_vector_type(kPer)));
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
   const uint32_t r = lane & 31, h = lane >> 5;
-  const float* partf = reinterpret_cast<const float*>(part);
-  auto store = [&](float v, uint32_t row, uint32_t col) {
-    if (row < p.M && col < p.N) {
-      if (kGate) v = gdn_gate(v, col, p);
-      if (kF32Out)
-        static_cast<float*>(y)[(size_t)row * p.ldy + col] = v;
-      else
-        static_cast<uint16_t*>(y)[(size_t)row * p.ldy + col] = f32_to_bf16_rne(v);
-    }
-  };
 #pragma unroll
   for (int g0 = 0; g0 < kFrags; g0 += kGroup) {
     if (g0 > 0) __syncthreads();                   // the previous group has been read
 #pragma unroll
-    for (int j = 0; j < kGroup; ++j)
-      if (g0 + j < kFrags) part[(j * KS + wave) * 64 + lane] = acc[(g0 + j) / FN][(g0 + j) % FN];
+    for (int j = 0; j < kGroup; ++j) {
+      if (g0 + j >= kFrags) break;
+      const floatx16& v = acc[(g0 + j) / FN][(g0 + j) % FN];
+      floatx4* q = reinterpret_cast<floatx4*>(part) + (j * KS + wave) * 256 + lane;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e * 64] = floatx4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
+    }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kGroup; ++j) {
       const int f = g0 + j;
       if (f >= kFrags) break;
       const int fa = f / FN, fb = f % FN;
-      const uint32_t col = n0 + fb * 32 + r;
-      const floatx16* pj = part + j * KS * 64;
-      if (kSpread) {
-        const float* pf = partf + j * KS * 64 * 16;
+      const uint32_t i0 = wave * kPer, col = n0 + fb * 32 + r;        // this wave's first entry
+      const float* q = part + j * (KS * 1024) + (i0 >> 2) * 256 + lane * 4 + (i0 & 3u);
+      entries sum = *reinterpret_cast<const entries*>(q);
 #pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-          const uint32_t i = wave * kPer + e;               // accumulator entry of this wave
-          float sum = pf[lane * 16 + i];
+      for (int w = 1; w < KS; ++w) sum += *reinterpret_cast<const entries*>(q + w * 1024);
 #pragma unroll
-          for (int w = 1; w < KS; ++w) sum += pf[(w * 64 + lane) * 16 + i];
-          store(sum * alpha[fb], m0 + fa * 32 + (i >> 2) * 8 + h * 4 + (i & 3), col);
+      for (int e = 0; e < kPer; ++e) {
+        const uint32_t i = i0 + e, row = m0 + fa * 32 + (i >> 2) * 8 + h * 4 + (i & 3);
+        if (row < p.M && col < p.N) {
+          float v = sum[e] * alpha[fb];
+          if (kGate) v = gdn_gate(v, col, p);
+          if (kF32Out)
+            static_cast<float*>(y)[(size_t)row * p.ldy + col] = v;
+          else
+            static_cast<uint16_t*>(y)[(size_t)row * p.ldy + col] = f32_to_bf16_rne(v);
         }
-      } else if (wave == (uint32_t)(f % KS)) {
-        floatx16 sum = pj[lane];
-#pragma unroll
-        for (int w = 1; w < KS; ++w) sum += pj[w * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) store(sum[i] * alpha[fb], m0 + fa * 32 + (i >> 2) * 8 + h * 4 + (i & 3), col);
       }
     }
   }

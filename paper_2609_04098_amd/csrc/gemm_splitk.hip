@@ -331,7 +331,7 @@ __global__ __launch_bounds__(KS * 64, KS < 8 ? 2 : KS / 4) void gemm_splitk_kern
   constexpr int kFit = kRingBytes / (KS * 64 * 64);            // fragments whose partials fit the rings
   constexpr int kGroup = kFit < FM * FN ? kFit : FM * FN;
   static_assert(kGroup >= 1, "partial sums of one fragment fit the ring");
-  splitk_epilogue<KS, FM, FN, kGroup, kF32Out, kGate>(acc, reinterpret_cast<floatx16*>(smem), p, alpha, y, m0, n0,
+  splitk_epilogue<KS, FM, FN, kGroup, kF32Out, kGate>(acc, reinterpret_cast<float*>(smem), p, alpha, y, m0, n0,
                                                       wave, lane);
 }
 

@@ -233,7 +233,7 @@ __global__ __launch_bounds__(KS * 64, 2) void quant_gemm_kernel(QuantGemmArgs q,
   // The partial sums reuse the X slots (every load has landed: the last
   // chunk waited for all of them).
   __syncthreads();
-  splitk_epilogue<KS, FM, FN, 1, kF32Out, false>(acc, reinterpret_cast<floatx16*>(smem), p, alpha, y, m0, n0, wave,
+  splitk_epilogue<KS, FM, FN, 1, kF32Out, false>(acc, reinterpret_cast<float*>(smem), p, alpha, y, m0, n0, wave,
                                                  lane);
 }
 
