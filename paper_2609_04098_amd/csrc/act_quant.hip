@@ -101,27 +101,27 @@ __global__ __launch_bounds__(kThreads) void amax_partial_kernel(const uint16_t* 
 // thread).  (Walking the blocks from the end of X to its start after the
 // amax pass, so as to meet the most recently read part of X in the MALL,
 // measured 2% slower on a 335 MB activation and is not done.)
+// d0, d1: the thread's first block.
+template <bool kContig>
+__device__ __forceinline__ const uint4* block_ptr(const uint16_t* x, uint32_t b, uint32_t blocks_per_row,
+                                                  uint32_t ldx) {
+  if (kContig) return reinterpret_cast<const uint4*>(x) + 2 * (size_t)b;
+  const uint32_t row = b / blocks_per_row, col = b - row * blocks_per_row;
+  return reinterpret_cast<const uint4*>(x + (size_t)row * ldx) + 2 * col;
+}
+
 template <bool kContig, bool kExact>
 __device__ __forceinline__ void quantize_blocks(const uint16_t* __restrict__ x, uint32_t n_blocks,
                                                 uint32_t blocks_per_row, uint32_t ldx,
                                                 uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                                                float g, float gf4) {
+                                                float g, float gf4, uint4 d0, uint4 d1) {
   const float gd6 = g * (1.0f / 6.0f);
   const uint32_t stride = gridDim.x * kThreads;
-  auto src_of = [&](uint32_t b) -> const uint4* {
-    if (kContig) return reinterpret_cast<const uint4*>(x) + 2 * (size_t)b;
-    const uint32_t row = b / blocks_per_row, col = b - row * blocks_per_row;
-    return reinterpret_cast<const uint4*>(x + (size_t)row * ldx) + 2 * col;
-  };
-  uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n_blocks) return;
-  const uint4* src = src_of(i);
-  uint4 d0 = src[0], d1 = src[1];
-  for (; i < n_blocks; i += stride) {
+  for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n_blocks; i += stride) {
     const uint32_t b = i;
     uint4 e0 = d0, e1 = d1;
     if (i + stride < n_blocks) {
-      const uint4* nxt = src_of(i + stride);
+      const uint4* nxt = block_ptr<kContig>(x, i + stride, blocks_per_row, ldx);
       e0 = nxt[0];
       e1 = nxt[1];
     }
@@ -141,6 +141,11 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ g_enc,
     const float* __restrict__ partial, uint32_t n_partial) {
   __shared__ uint32_t lds[kThreads / 64];
+  // The first block is on its way while G is formed (the last block again past
+  // the end).
+  const uint32_t first = blockIdx.x * kThreads + threadIdx.x;
+  const uint4* src = block_ptr<kContig>(x, first < n_blocks ? first : n_blocks - 1, blocks_per_row, ldx);
+  const uint4 d0 = src[0], d1 = src[1];
   float g;
   if (kDynamic) {
     uint32_t m = 0;
@@ -156,9 +161,9 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(
   // The form is chosen per tensor, uniformly across the launch.
   const QuantMode q = quant_mode(g);
   if (q.exact)
-    quantize_blocks<kContig, true>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.0f);
+    quantize_blocks<kContig, true>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.0f, d0, d1);
   else
-    quantize_blocks<kContig, false>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.25f * q.gf);
+    quantize_blocks<kContig, false>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.25f * q.gf, d0, d1);
 }
 
 __global__ void write_zero_scale_kernel(float* g_enc) { *g_enc = 0.0f; }

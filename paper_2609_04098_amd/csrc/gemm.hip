@@ -274,6 +274,7 @@ static const char* narrow_kernel_name(int fragments) {
     case 1: return "gemm_splitk_kernel<8,1,1,3> (32x32 tiles, split-K, shared activation ring)";
     case 2: return "gemm_splitk_kernel<8,1,2,3> (32x64 tiles, split-K, shared activation ring)";
     case 3: return "gemm_splitk_kernel<8,1,3,3> (32x96 tiles, split-K, shared activation ring)";
+    case 4: return "gemm_splitk_kernel<4,1,3,3> (32x96 tiles, split-K, shared activation ring)";
     default: return "gemm_splitk_kernel<4,2,3,3> (64x96 tiles, split-K)";
   }
 }

@@ -459,8 +459,8 @@ uint32_t cu_count();
 // tiles per workgroup.
 enum class DecodeShape { kRows16w1, kRows8w2, kRows8w3, kRows4w2, k4Private, k4Shared, k4SharedPair, k8Shared };
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu);
-// Weight fragments (1..3) per 32-row tile of 8 waves for a tall-skinny output
-// (N <= 96), or 0: 64 x 96 tiles of 4 waves.
+// Tiles of a tall-skinny output (N <= 96): 1..3: 32 rows x that many weight
+// fragments, 8 waves; 4: 32 x 96, 4 waves; 0: 64 x 96, 4 waves.
 int narrow_fragments(int64_t M, int64_t N, uint32_t n_cu);
 
 // Launchers of the kernel families (each in its own translation unit).

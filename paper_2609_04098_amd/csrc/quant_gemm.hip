@@ -333,6 +333,7 @@ hipError_t launch_quant_gemm(const void* x, int64_t M, int64_t K, int64_t ldx, f
       case 1: return launch_quant_gemm_fn<8, 1, 1>(q, dynamic, wp, w_g, y, p, out_f32, stream);
       case 2: return launch_quant_gemm_fn<8, 1, 2>(q, dynamic, wp, w_g, y, p, out_f32, stream);
       case 3: return launch_quant_gemm_fn<8, 1, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
+      case 4: return launch_quant_gemm_fn<4, 1, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
       default: return launch_quant_gemm_fn<4, 2, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
     }
   }
