@@ -29,13 +29,15 @@ uint32_t cu_count() {
 // (measured: 240 workgroups of 91 chunks and 480 of 45 both 50 us), so the
 // work is counted in rounds of one workgroup per CU whatever the occupancy.
 // The clock is held by power, so a round that leaves CUs idle runs faster: a
-// partly filled last round takes 0.74 to 0.8 of a full one (320 and 384 tiles
-// at K = 5120, 400 at K = 17408: 240, 242 and 699 us against 138 and 389 for
-// one round), a lone round of 160 tiles 0.94.  Smaller tiles, several to a
-// CU, gain less from it (`last`: the least a partly filled last round costs).
-static float rounds_of(uint64_t workgroups, uint32_t n_cu, float last) {
+// partly filled last round of square tiles takes 0.74 to 0.8 of a full one (320
+// and 384 tiles at K = 5120, 400 at K = 17408: 240, 242 and 699 us against 138
+// and 389 for one round), a lone round of up to 0.85 of the CUs 0.9 (128 to 204
+// tiles).  Smaller tiles, several to a CU, gain less (`last`, `lone`), and
+// split-K tiles, whose waves wait more, need a second workgroup on the CU to
+// reach their rate (lone 1.1).
+static float rounds_of(uint64_t workgroups, uint32_t n_cu, float last, float lone) {
   const float frac = (float)(workgroups % n_cu) / (float)n_cu;
-  if (workgroups < n_cu) return 0.85f + 0.15f * frac;
+  if (workgroups < n_cu) return lone >= 1.0f || frac <= 0.85f ? lone : lone + (1.0f - lone) * (frac - 0.85f) / 0.15f;
   return (float)(workgroups / n_cu) + (frac == 0.0f ? 0.0f : frac > last ? frac : last);
 }
 
@@ -44,25 +46,27 @@ struct TileCost {
   uint32_t bm, bn;
   float chunk_us, chunk_us_super;   // one 64-deep chunk of a tile
   float fixed_us;                   // first loads, epilogue, launch
-  float last_round;                 // see rounds_of
+  float last, lone;                 // see rounds_of
   uint32_t max_parts;               // K parts the launcher offers (with super-stages; square: only with them)
 };
 // Fitted, on one box, to M = 50 .. 1000 against N = 4352 .. 34816 at K = 5120,
 // to N = 5120 at K = 2176 .. 17408, and for the square tile to larger M.  The
-// split-K tiles (four waves share a tile's reduction and meet in LDS) have
+// split-K tiles (four or eight waves share a tile's reduction and meet in LDS) have
 // the cheaper small tile, the LDS tiles the cheaper large one and K parts.
 constexpr TileCost kTileCosts[] = {
-    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 7.5f, 0.75f, 32},
-    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.54f, 0.485f, 7.0f, 0.92f, 32},
-    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.57f, 0.515f, 7.0f, 0.92f, 32},
-    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.19f, 0.19f, 8.0f, 1.0f, 1},
-    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.155f, 0.155f, 6.0f, 1.0f, 1},
-    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.09f, 0.09f, 5.0f, 1.0f, 1},
-    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1.0f, 1},
+    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 7.5f, 0.75f, 0.9f, 32},
+    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.53f, 0.465f, 6.5f, 0.92f, 0.95f, 32},
+    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.57f, 0.515f, 7.0f, 0.92f, 0.95f, 32},
+    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.175f, 0.175f, 6.5f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.15f, 0.15f, 5.5f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x160, GemmPlan::kSplitk32x160, 32, 160, 0.185f, 0.185f, 6.0f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x96, GemmPlan::kSplitk32x96, 32, 96, 0.15f, 0.15f, 3.0f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.08f, 0.08f, 5.5f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1.0f, 1.1f, 1},
 };
 // The summing pass: a launch, and every partial sum written and read once
 // (they stay in the last-level cache).
-constexpr float kSumLaunchUs = 2.5f, kPartBytesPerUs = 8.0e6f;
+constexpr float kSumLaunchUs = 2.5f, kPartBytesPerUs = 6.0e6f;
 // Bound on the partial sums of one call.
 constexpr uint64_t kMaxPartBytes = 128ull << 20;
 constexpr uint32_t kMinPartChunks = 4;   // one group of chunks with super-stages
@@ -104,7 +108,7 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
                         (square && !super)))
         break;
       const uint32_t chunks = (units + parts - 1) / parts * unit;
-      const float c = rounds_of(tiles * parts, n_cu, t.last_round) * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us +
+      const float c = rounds_of(tiles * parts, n_cu, t.last, t.lone) * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us +
                       (parts > 1 ? kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs : 0.0f);
       if (best.first == GemmPlan::kNone || c < *cost) {
         best.first = super ? t.super_kind : t.kind;
@@ -152,7 +156,7 @@ static GemmPlan plan_square_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu
   for (uint32_t parts = 2; parts <= kMaxTailParts && parts <= units && rem != 0 && tiles > n_cu; ++parts) {
     const uint64_t part_bytes = (uint64_t)parts * rem * kSquareTile * kSquareTile * sizeof(float);
     if (part_bytes > kMaxPartBytes) break;
-    const float tail_rounds = rounds_of(rem * parts, n_cu, sq.last_round);
+    const float tail_rounds = rounds_of(rem * parts, n_cu, sq.last, sq.lone);
     const float c = ((float)(tiles / n_cu) * (float)units + tail_rounds * (float)((units + parts - 1) / parts)) *
                         4.0f * sq.chunk_us_super + (1.0f + tail_rounds) * sq.fixed_us + kSumLaunchUs +
                     2.0f * (float)part_bytes / kPartBytesPerUs;
@@ -189,8 +193,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
     if (n_cu != 0 && (!tail || K >= kTailMinK)) {
       const TileCost& sq = kTileCosts[0];
       const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
-      const float last = g.second == GemmPlan::kLdsSuperHalves ? 0.55f : sq.last_round;
-      const float rounds = tail ? (float)(tiles / n_cu) + last : rounds_of(tiles, n_cu, sq.last_round);
+      const float last = g.second == GemmPlan::kLdsSuperHalves ? 0.55f : sq.last;
+      const float rounds = tail ? (float)(tiles / n_cu) + last : rounds_of(tiles, n_cu, sq.last, sq.lone);
       const float base = rounds * (float)(K / 64) * (K % 256 == 0 ? sq.chunk_us_super : sq.chunk_us) + sq.fixed_us;
       float cost, tail_cost;
       const GemmPlan t = plan_tiles(M, N, K, n_cu, with_ws, &cost);
@@ -250,7 +254,9 @@ const char* gemm_kernel_name(int kind, bool parts) {
     case GemmPlan::kSplitk32x32: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
     case GemmPlan::kSplitk32x64: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";
     case GemmPlan::kSplitk64x64: return "gemm_splitk_kernel<4,2,2,3> (64x64 tiles, split-K)";
-    case GemmPlan::kSplitk64x96: return "gemm_splitk_kernel<4,2,3,3> (64x96 tiles, split-K)";
+    case GemmPlan::kSplitk64x96: return "gemm_splitk_kernel<4,2,3,2> (64x96 tiles, split-K)";
+    case GemmPlan::kSplitk32x96: return "gemm_splitk_kernel<8,1,3,3> (32x96 tiles, split-K, shared activation ring)";
+    case GemmPlan::kSplitk32x160: return "gemm_splitk_kernel<4,1,5,2> (32x160 tiles, split-K, shared activation ring)";
     case GemmPlan::kReg: return "gemm_reg_kernel<2,2,4,4> (256x256 tiles, register path)";
     default: return "none";
   }
@@ -263,7 +269,9 @@ static const char* decode_kernel_name(DecodeShape d) {
     case DecodeShape::kRows8w3: return "gemm_rows16_kernel<8,3,2> (16x96 tiles, split-K)";
     case DecodeShape::kRows4w2: return "gemm_rows16_kernel<4,2,3> (16x64 tiles, split-K)";
     case DecodeShape::k4Private: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, per-wave rings)";
-    case DecodeShape::k4Shared: return "gemm_splitk_kernel<4,1,1,3> (32x32 tiles, split-K, shared activation ring)";
+    case DecodeShape::k8SharedPair: return "gemm_splitk_kernel<8,1,2,3> (32x64 tiles, split-K, shared activation ring)";
+    case DecodeShape::k8Shared3: return "gemm_splitk_kernel<8,1,3,3> (32x96 tiles, split-K, shared activation ring)";
+    case DecodeShape::k4Shared5: return "gemm_splitk_kernel<4,1,5,2> (32x160 tiles, split-K, shared activation ring)";
     case DecodeShape::k8Shared: return "gemm_splitk_kernel<8,1,1,4> (32x32 tiles, split-K, shared activation ring)";
     default: return "gemm_splitk_kernel<4,1,2,3> (32x64 tiles, split-K, shared activation ring)";
   }
@@ -306,6 +314,8 @@ static hipError_t run_one(int kind, const GemmOperands& o, const GemmParams& p, 
     case GemmPlan::kSplitk32x32:
     case GemmPlan::kSplitk32x64:
     case GemmPlan::kSplitk64x64:
+    case GemmPlan::kSplitk32x96:
+    case GemmPlan::kSplitk32x160:
     case GemmPlan::kSplitk64x96: return launch_splitk_tile(o, p, kind, out_f32, stream);
     case GemmPlan::kSplitkDecode: return launch_splitk_decode(o, p, out_f32, stream);
     case GemmPlan::kReg: return launch_reg_square(o, p, out_f32, aligned, stream);

@@ -426,7 +426,7 @@ constexpr uint32_t kSquareTile = 256;
 struct GemmPlan {
   enum Kind { kNone = 0, kLdsSquare, kLdsSuper, kLdsTall, kSplitkNarrow, kSplitkDecode, kReg, kLdsSuperHalves,
               kLdsMid, kLdsMidSuper, kLdsLow, kLdsLowSuper, kSplitk32x32, kSplitk32x64, kSplitk64x64,
-              kSplitk64x96, kLdsSuperTiles };
+              kSplitk64x96, kSplitk32x96, kSplitk32x160, kLdsSuperTiles };
   // second == kLdsSuperTiles: `first` runs the first n_full square tiles (in
   // tile order) over all columns, `second` the others in tail_parts runs of K.
   int first, second;
@@ -455,9 +455,10 @@ uint32_t cu_count();
 
 // Form of a decode shape (M <= 32).  At most 16 rows: gemm_rows16_kernel,
 // waves and 32-column weight tiles per workgroup; more: the split-K kernel,
-// waves per tile, per-wave or shared activation rings, one or (pair) two weight
-// tiles per workgroup.
-enum class DecodeShape { kRows16w1, kRows8w2, kRows8w3, kRows4w2, k4Private, k4Shared, k4SharedPair, k8Shared };
+// waves per tile, per-wave or shared activation rings, one or (pair) two, three
+// or five weight tiles per workgroup.
+enum class DecodeShape { kRows16w1, kRows8w2, kRows8w3, kRows4w2, k4Private, k4SharedPair, k4Shared5, k8Shared,
+                         k8SharedPair, k8Shared3 };
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu);
 // Tiles of a tall-skinny output (N <= 96): 1..3: 32 rows x that many weight
 // fragments, 8 waves; 4: 32 x 96, 4 waves; 0: 64 x 96, 4 waves.

@@ -403,9 +403,12 @@ hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f3
 //    (32 x 8192 x 5120: two tiles per workgroup and a shared activation ring
 //    13.7 us, this 9.7), for long K 8 waves with a shared ring (32 x 5120 x
 //    17408 35.5 -> 21.2).
-//  * more tiles: a shared activation ring, with one tile per workgroup while
-//    they are few (32 x 17408 x 5120: 18.9 us against 19.8 with two), then
-//    with two (32 x 34816 x 5120: 28.4 against 28.8 with one).
+//  * more tiles: a shared activation ring and as many tiles per workgroup as
+//    bring the workgroups to between 0.6 of the CUs and one each: the
+//    activation's decode and loads are shared by them (32 x 17408 x 5120, 8
+//    waves and three tiles: 15.1 us against 16.6 with 4 waves and three and
+//    18.1 with two; 32 x 34816 x 5120, 4 waves and five tiles: 22.3 against 25.8
+//    with three and 26.2 with two).
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
   const uint64_t tiles = (uint64_t)((N + 31) / 32);
   if (M <= 16) {
@@ -415,35 +418,42 @@ DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
     return DecodeShape::kRows4w2;
   }
   if (tiles <= n_cu) return K >= 8192 ? DecodeShape::k8Shared : DecodeShape::k4Private;
-  return 2 * tiles <= 5 * (uint64_t)n_cu ? DecodeShape::k4Shared : DecodeShape::k4SharedPair;
+  if (5 * tiles < 9 * (uint64_t)n_cu) return DecodeShape::k8SharedPair;
+  if (tiles <= 3 * (uint64_t)n_cu) return DecodeShape::k8Shared3;
+  return tiles <= 5 * (uint64_t)n_cu ? DecodeShape::k4Shared5 : DecodeShape::k4SharedPair;
 }
 
 hipError_t launch_splitk_decode(const GemmOperands& o, GemmParams p, bool out_f32, hipStream_t stream) {
   const DecodeShape shape = decode_shape(p.M, p.N, p.K, cu_count());
   switch (shape) {
     case DecodeShape::k4Private: return launch_splitk<4, 1, 1, 3, false, false>(o, p, out_f32, stream);
-    case DecodeShape::k4Shared: return launch_splitk<4, 1, 1, 3, true, false>(o, p, out_f32, stream);
+    case DecodeShape::k8SharedPair: return launch_splitk<8, 1, 2, 3, true, false>(o, p, out_f32, stream);
+    case DecodeShape::k8Shared3: return launch_splitk<8, 1, 3, 3, true, false>(o, p, out_f32, stream);
+    case DecodeShape::k4Shared5: return launch_splitk<4, 1, 5, 2, true, false>(o, p, out_f32, stream);
     case DecodeShape::k8Shared: return launch_splitk<8, 1, 1, 4, true, false>(o, p, out_f32, stream);
     case DecodeShape::k4SharedPair: return launch_splitk<4, 1, 2, 3, true, false>(o, p, out_f32, stream);
     default: return launch_rows16(shape, o, p, out_f32, stream);
   }
 }
 
-// Small outputs with M > 32 (see plan_gemm): four waves share the reduction
-// of a tile.
+// Small outputs with M > 32 (see plan_gemm): four or eight waves share the
+// reduction of a tile.  64 x 96: two ring stages (100 x 34816 x 5120 49.9 us,
+// 55.5 with three).
 hipError_t launch_splitk_tile(const GemmOperands& o, const GemmParams& p, int kind, bool out_f32, hipStream_t stream) {
   switch (kind) {
     case GemmPlan::kSplitk32x32: return launch_splitk<4, 1, 1, 3, false, false>(o, p, out_f32, stream);
     case GemmPlan::kSplitk32x64: return launch_splitk<4, 1, 2, 3, true, false>(o, p, out_f32, stream);
     case GemmPlan::kSplitk64x64: return launch_splitk<4, 2, 2, 3, true, false>(o, p, out_f32, stream);
-    default: return launch_splitk<4, 2, 3, 3, true, false>(o, p, out_f32, stream);
+    case GemmPlan::kSplitk32x96: return launch_splitk<8, 1, 3, 3, true, false>(o, p, out_f32, stream);
+    case GemmPlan::kSplitk32x160: return launch_splitk<4, 1, 5, 2, true, false>(o, p, out_f32, stream);
+    default: return launch_splitk<4, 2, 3, 2, true, false>(o, p, out_f32, stream);
   }
 }
 
-// The fused decode launch, in the form of decode_shape.  Above 16 rows (K below
-// 1024) four waves and two weight tiles per workgroup, a ring one stage deeper
-// than the plain kernel's: more of the weight in flight while the workgroup
-// quantizes X.
+// The fused decode launch, with the waves of decode_shape.  Above 16 rows (K
+// below 1024) two weight tiles (eight waves: one) per workgroup, a ring one
+// stage deeper than the plain kernel's: more of the weight in flight while the
+// workgroup quantizes X.
 template <int KS, int FN, int kStages>
 static hipError_t launch_decode_quant(const GemmOperands& o, GemmParams p, const DecodeQuantArgs& q, bool dynamic,
                                       bool out_f32, hipStream_t stream) {
@@ -468,7 +478,12 @@ hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const D
                                     bool out_f32, hipStream_t stream) {
   if (p.M <= 16)
     return launch_rows16_quant(decode_shape(p.M, p.N, p.K, cu_count()), o, p, q, dynamic, out_f32, stream);
-  return launch_decode_quant<4, 2, 4>(o, p, q, dynamic, out_f32, stream);
+  switch (decode_shape(p.M, p.N, p.K, cu_count())) {
+    case DecodeShape::k8Shared:
+    case DecodeShape::k8SharedPair:
+    case DecodeShape::k8Shared3: return launch_decode_quant<8, 1, 4>(o, p, q, dynamic, out_f32, stream);
+    default: return launch_decode_quant<4, 2, 4>(o, p, q, dynamic, out_f32, stream);
+  }
 }
 
 }  // namespace nvfp4

@@ -55,8 +55,12 @@ def _check(m, n, k, offs):
     (16, 24576, 1088, [0, 24576]),         # 768 tiles: a workgroup of three per CU
     (16, 24577, 1088, [0, 24577]),         # one more: two tiles for 4 waves
     (15, 24609, 1088, [0, 24609]),         # ... and at the one-launch limit (M K = 16320): three for 8 waves
-    (17, 20480, 192, [0, 20480]),          # most tiles with one weight tile per workgroup
-    (17, 20481, 192, [0, 20481]),          # fewest tiles with two
+    (17, 8193, 512, [0, 8193]),            # one tile past one per CU: two tiles for 8 waves, one launch
+    (17, 14720, 1024, [0, 14720]),         # the most in twos
+    (32, 14721, 192, [0, 9999, 14721]),    # the fewest in threes, 3 chunks over 8 waves
+    (18, 24577, 576, [0, 24577]),          # five tiles for 4 waves, one launch, ragged N
+    (32, 24700, 1088, [0, 24700]),
+    (17, 40961, 128, [0, 40961]),          # past five tiles per CU: two tiles for 4 waves
     (1, 160, 8192, [0, 160]),              # long K, one launch
     (8, 170, 8256, [0, 85, 170]),          # long K: 129 chunks over 16 waves
     (20, 170, 8192, [0, 170]),             # long K, more rows: shared ring of 4 stages
