@@ -60,7 +60,7 @@ constexpr TileCost kTileCosts[] = {
     {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.175f, 0.175f, 6.5f, 1.0f, 1.1f, 1},
     {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.15f, 0.15f, 5.5f, 1.0f, 1.1f, 1},
     {GemmPlan::kSplitk32x160, GemmPlan::kSplitk32x160, 32, 160, 0.185f, 0.185f, 6.0f, 1.0f, 1.1f, 1},
-    {GemmPlan::kSplitk32x96, GemmPlan::kSplitk32x96, 32, 96, 0.15f, 0.15f, 3.0f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x96, GemmPlan::kSplitk32x96, 32, 96, 0.12f, 0.12f, 0.0f, 1.0f, 1.0f, 1},
     {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.08f, 0.08f, 5.5f, 1.0f, 1.1f, 1},
     {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1.0f, 1.1f, 1},
 };
@@ -74,12 +74,13 @@ constexpr uint32_t kMinPartChunks = 4;   // one group of chunks with super-stage
 // The split-K tiles are offered where their costs were fitted: a batch of up
 // to 1024 rows, or a K below 2048, where the longer first loads of the LDS tiles
 // weigh more (1300 x 1300 x 1088: 24 us with 128 x 128 tiles; 1000 rows 10 us
-// with split-K tiles); at most 5 rounds of tiles (100 x 34816 x 5120 with 32 x 64
+// with split-K tiles); at most 6 rounds of tiles (100 x 34816 x 5120 with 32 x 64
 // tiles, 9 rounds, took 75 us for an estimate of 70; the LDS tiles, which share
-// each operand between their waves, are the better ones there).
+// each operand between their waves, are the better ones there), 5 below K =
+// 1024, where the estimates are mostly fixed cost.
 constexpr int64_t kSplitkMaxRows = 1024;
 constexpr int64_t kSplitkShortK = 2048;
-constexpr uint64_t kSplitkMaxRounds = 5;
+constexpr uint64_t kSplitkMaxRounds = 6, kSplitkMaxRoundsShort = 5;
 
 // Below this K the K-halves / tall-tile form of the last round is kept as
 // it is: the cost of a tile is then mostly its first loads and epilogue.
@@ -101,15 +102,19 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
     const bool square = t.kind == GemmPlan::kLdsSquare;
     const uint64_t tiles = (uint64_t)((M + t.bm - 1) / t.bm) * (uint64_t)((N + t.bn - 1) / t.bn);
     const bool splitk = t.kind == t.super_kind;
-    if (splitk && ((M > kSplitkMaxRows && K >= kSplitkShortK) || tiles > kSplitkMaxRounds * n_cu)) continue;
+    const uint64_t max_rounds = K < 1024 ? kSplitkMaxRoundsShort : kSplitkMaxRounds;
+    if (splitk && ((M > kSplitkMaxRows && K >= kSplitkShortK) || tiles > max_rounds * n_cu)) continue;
     for (uint32_t parts = 1; parts <= t.max_parts; ++parts) {
       const uint64_t part_bytes = (uint64_t)parts * (uint64_t)M * parts_row((uint32_t)N) * sizeof(float);
       if (parts > 1 && (!with_ws || units * unit < parts * kMinPartChunks || part_bytes > kMaxPartBytes ||
                         (square && !super)))
         break;
-      const uint32_t chunks = (units + parts - 1) / parts * unit;
-      const float c = rounds_of(tiles * parts, n_cu, t.last, t.lone) * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us +
-                      (parts > 1 ? kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs : 0.0f);
+      // 32 x 96 tiles of eight waves fill a CU's LDS: a round's first loads and
+      // epilogue (5 us, 42 chunks' worth) are not covered by another workgroup.
+      const uint32_t chunks = (units + parts - 1) / parts * unit + (t.kind == GemmPlan::kSplitk32x96 ? 42 : 0);
+      const float c = rounds_of(tiles * parts, n_cu, t.last, t.lone) * (float)chunks *
+                          (super ? t.chunk_us_super : t.chunk_us) +
+                      t.fixed_us + (parts > 1 ? kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs : 0.0f);
       if (best.first == GemmPlan::kNone || c < *cost) {
         best.first = super ? t.super_kind : t.kind;
         best.k_parts = parts;

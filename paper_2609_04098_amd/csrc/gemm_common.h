@@ -1,6 +1,6 @@
 // Shared device code and host-side plumbing of the NVFP4 GEMM kernels
-// (gemm_lds_*.hip, gemm_splitk.hip, gemm_reg.hip, quant_gemm.hip; the host
-// dispatch is in gemm.hip).
+// (gemm_lds_*.hip, gemm_splitk.hip, gemm_rows16.hip, gemm_reg.hip,
+// quant_gemm.hip; the host dispatch is in gemm.hip).
 //
 // NVFP4 x NVFP4 GEMM with FP32 accumulation and a per-segment scaled
 // epilogue, for gfx950 (paper, section 2: W4A4 GEMM on 4-bit operands;
@@ -23,7 +23,8 @@
 // exactly 4 bytes of packed codes under one block scale; see packed_layout.h
 // for the index map shared by the activation and the prepacked weight.
 //
-// Three kernels:
+// Four kernels (plan_gemm in gemm.hip chooses the kernel, tile and K parts of a
+// shape by estimated time):
 //  * gemm_lds_kernel (K % 64 == 0, N > 96, M > 32; the prefill shapes): 256
 //    threads, 256 x 256 tile, wave tile 128 x 128 (4 x 4 accumulator
 //    fragments, 256 accumulator registers), one wave per SIMD; its own decode
@@ -36,16 +37,21 @@
 //    last.  One barrier per 64-deep chunk.  The loop body is a single basic
 //    block in which MFMAs, decode VALU, LDS reads and the DMA issue of a
 //    later chunk are interleaved (sched_group_barrier), so that the vector
-//    memory queue and the VALU never stall the MFMA stream in bursts.
-//  * gemm_splitk_kernel (N <= 96, the tall-skinny gate projections; M <= 32,
-//    decode shapes): the output has too few 32 x 32 tiles to fill the chip,
-//    so the four waves of a workgroup share one tile and split its
+//    memory queue and the VALU never stall the MFMA stream in bursts.  Outputs
+//    with too few such tiles take 128 x 128 or 64 x 256 tiles, two workgroups
+//    per CU, and K parts (FP32 partial sums in a workspace, then a summing
+//    pass).
+//  * gemm_splitk_kernel (N <= 96, the tall-skinny gate projections; 17 to 32
+//    rows; small outputs up to about 1000 rows): too few 32 x 32 tiles to fill
+//    the chip, so the 4 or 8 waves of a workgroup share one tile and split its
 //    reduction, each streaming its weight chunks through a private LDS ring
 //    and the activation, whole 128-byte row lines of 4 chunks, through a
-//    ring shared by the workgroup; the partial sums meet in LDS.
-//  * gemm_reg_kernel (K % 64 != 0, N > 96): operands go straight from global
-//    memory to registers one chunk ahead; per-block masking of the scales
-//    handles a K tail.
+//    ring shared by 4 waves; the partial sums meet in LDS.
+//  * gemm_rows16_kernel (at most 16 rows): the same with per-wave rings and 16 x
+//    16 x 32 products.
+//  * gemm_reg_kernel (K % 64 != 0 without a workspace): operands go straight
+//    from global memory to registers one chunk ahead; per-block masking of the
+//    scales handles a K tail.
 // All remap workgroups so that each XCD (its own L2) runs a contiguous,
 // M-grouped range of tiles; out-of-range rows/columns read zeros through the
 // buffer bounds and are not stored.

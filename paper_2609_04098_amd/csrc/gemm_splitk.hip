@@ -7,24 +7,23 @@ namespace nvfp4 {
 // ----------------------------------------------------------- split-K path
 //
 // Shapes whose output has too few 32 x 32 tiles to give every SIMD two waves
-// (N <= 96: the tall-skinny gate projections; M <= 32: decode-shaped calls,
-// weight-bandwidth-bound): the KS = 4 waves of a workgroup share one FM x FN
-// fragment tile and split its reduction, wave w taking chunks w, w + 4, ...,
-// so that at step i the workgroup consumes chunks 4i .. 4i + 3.
+// (N <= 96: the tall-skinny gate projections; M <= 32: decode-shaped calls;
+// small outputs of plan_gemm): the KS = 4 or 8 waves of a workgroup share one FM
+// x FN fragment tile and split its reduction, wave w taking chunks w, w + KS,
+// ..., so that at step i the workgroup consumes chunks KS i .. KS i + KS - 1.
 // The weight fragments of a wave's chunk go through a private LDS ring
 // (direct-to-LDS loads, refilled as soon as the wave has read a stage).
-// The activation of a step, the same rows for all four waves, is one
-// 128-byte line group per row (4 chunks x 32 bytes of codes, 16 bytes of
-// scales), which the waves load together, a quarter each, into a ring shared
-// by the workgroup: a wave-wide load then covers 8 whole rows instead of 32
-// rows x 16 bytes, and a row's line is fetched once per workgroup instead of
+// The activation of a step is, for each group of four waves, one 128-byte line
+// group per row (4 chunks x 32 bytes of codes, 16 bytes of scales), which the
+// four load together, a quarter each, into a ring they share: a wave-wide load then covers 8 whole rows instead of 32
+// rows x 16 bytes, and a row's line is fetched once per group instead of
 // once per wave (the per-chunk loads of 32-byte row pieces took 3-4 times
 // as many memory requests as the weight).  One barrier per step: after it
 // every wave's share of the next step has landed and every wave has read
 // the stage about to be refilled.  Each wave reads the next chunk's raw
 // fragments from LDS while it decodes and multiplies the current one, and
-// the partial sums meet in LDS at the end; fragment f is summed in wave
-// order (deterministic) and stored by wave f % KS.  Requires K % 64 == 0.
+// the partial sums meet in LDS at the end, summed in wave order
+// (deterministic).  Requires K % 64 == 0.
 
 template <int KS, int FM, int FN, int kStages, bool kF32Out, bool kGate, int kQuant = 0, bool kShareA = true>
 __global__ __launch_bounds__(KS * 64, KS < 8 ? 2 : KS / 4) void gemm_splitk_kernel(const uint8_t* __restrict__ a_codes,

@@ -296,8 +296,9 @@ __device__ __forceinline__ uint32_t quantize_block_fast(const uint32_t v[8], flo
   return bs.code;
 }
 
-// One block in the form `kExact` of a tensor's quant_mode (gf4:
-// gf / 4 of the fast form, unused in the exact one).
+// One block in the form `kExact` of a tensor's quant_mode (gf4: gf / 4 of the
+// fast form, unused in the exact one, which takes the two-multiply q: it holds
+// for every G).
 template <bool kExact, bool kBranch = true>
 __device__ __forceinline__ uint32_t quantize_block_as(const uint32_t v[8], float g, float gd6, float gf4,
                                                       uint32_t& c0, uint32_t& c1) {

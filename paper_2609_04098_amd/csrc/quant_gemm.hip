@@ -1,6 +1,6 @@
 // Activation quantization fused into the NVFP4 GEMM (nvfp4_quantize_gemm):
 // the narrow-output kernel below (N <= 128), and the host side of the fused
-// decode path (M <= 32, the split-K kernel's fused prologue).
+// decode path (M <= 32, the decode kernels' fused prologue).
 #include "gemm_common.h"
 
 namespace nvfp4 {
@@ -266,10 +266,10 @@ size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // The fused decode kernel quantizes all of X in every workgroup (there is
 // no hand-off between workgroups), so it pays off only while X is a few
-// tokens: up to M * K = 16384 elements (3 tokens of width 5120) it beats
-// the quantizer launch in front of the GEMM (1 token: 30.2 vs 32.4 us on
-// the gate/up weight read from HBM); at 7 tokens the repeated quantization
-// already costs more than the launch (43.6 vs 36.7 us).
+// tokens: up to M * K = 16384 elements (3 tokens of width 5120) it beats the
+// quantizer launch in front of the GEMM (1 and 3 tokens on the gate/up weight
+// read from HBM 22.7 and 23.4 us; the GEMM alone 22 us and the quantizer's own
+// launch 2.7 to 3.5 in front of it).
 constexpr int64_t kDecodeFuseMaxElems = 16 * (int64_t)kDecodeFuseMaxBlocks;
 
 }  // namespace
