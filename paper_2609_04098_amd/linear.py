@@ -6,6 +6,7 @@ order only (the arithmetic is in the HIP kernels).
     y  = gemm(aq, pw)                         # Y = dq(A) dq(W)^T, segment-scaled
 """
 
+import contextlib
 import ctypes
 from dataclasses import dataclass
 from typing import List
@@ -37,6 +38,25 @@ def _dev(t):
     return t.device
 
 
+def _on(stream, device):
+    """Context in which PyTorch's current stream is ``stream`` (a torch stream
+    or a raw handle; None: the current one)."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if not hasattr(stream, "cuda_stream"):
+        stream = torch.cuda.ExternalStream(stream, device) if stream else torch.cuda.default_stream(device)
+    return torch.cuda.stream(stream)
+
+
+def _scratch(nbytes, device, stream):
+    """Scratch memory of one call on ``stream``.  The caching allocator hands a
+    freed block to the next allocation on the stream it was allocated on, in
+    that stream's order: scratch that its call drops on return has to come from
+    the stream that uses it."""
+    with _on(stream, device):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 def pack_weight(w, seg_offsets=None, g_seg=None, stream=None) -> PackedWeight:
     """Quantize a bf16 [N, K] weight whose row ranges are separately
     calibrated segments; dynamic per-segment scales unless g_seg is given."""
@@ -47,7 +67,7 @@ def pack_weight(w, seg_offsets=None, g_seg=None, stream=None) -> PackedWeight:
     packed = torch.empty(_c.nvfp4_packed_weight_bytes(n, k), dtype=torch.uint8, device=dev)
     if g_seg is None:
         gs = torch.empty(n_seg, dtype=torch.float32, device=dev)
-        ws = torch.empty(_c.nvfp4_pack_weight_workspace_bytes(n, k, n_seg), dtype=torch.uint8, device=dev)
+        ws = _scratch(_c.nvfp4_pack_weight_workspace_bytes(n, k, n_seg), dev, stream)
         _c.nvfp4_pack_weight(w, seg_offsets, gs, packed, _c.NVFP4_DYNAMIC, ws, stream)
     else:
         gs = torch.as_tensor(g_seg, dtype=torch.float32).to(dev).contiguous()
@@ -79,8 +99,8 @@ def alloc_act(m, k, device) -> QuantizedAct:
                         torch.empty(1, dtype=torch.float32, device=device), m, k)
 
 
-def act_workspace(m, k, device):
-    return torch.empty(_c.nvfp4_quantize_act_workspace(m, k), dtype=torch.uint8, device=device)
+def act_workspace(m, k, device, stream=None):
+    return _scratch(_c.nvfp4_quantize_act_workspace(m, k), device, stream)
 
 
 def _set_scale(buf, g, stream):
@@ -104,7 +124,7 @@ def quantize_act(x, g=None, out: QuantizedAct = None, workspace=None, stream=Non
     dev = _dev(x)
     aq = alloc_act(m, k, dev) if out is None else out
     if g is None:
-        ws = act_workspace(m, k, dev) if workspace is None else workspace
+        ws = act_workspace(m, k, dev, stream) if workspace is None else workspace
         _c.nvfp4_quantize_act(x, aq.codes, aq.scales, aq.g, _c.NVFP4_DYNAMIC, ws, stream)
     else:
         _set_scale(aq.g, g, stream)
@@ -125,10 +145,10 @@ def rmsnorm_quantize_act(x, gamma, eps, g, out: QuantizedAct = None, y=None, str
     return aq
 
 
-def gemm_workspace(m, n, k, device):
+def gemm_workspace(m, n, k, device, stream=None):
     """Workspace for gemm() at this shape (None when the shape needs none)."""
     nbytes = _c.nvfp4_gemm_workspace(m, n, k)
-    return None if nbytes == 0 else torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return None if nbytes == 0 else _scratch(nbytes, device, stream)
 
 
 def gemm(aq: QuantizedAct, pw: PackedWeight, out_dtype=torch.bfloat16, out=None, workspace=None, stream=None):
@@ -139,7 +159,7 @@ def gemm(aq: QuantizedAct, pw: PackedWeight, out_dtype=torch.bfloat16, out=None,
     dev = aq.codes.device
     y = out if out is not None else torch.empty((aq.m, pw.n), dtype=out_dtype, device=dev)
     kind = _c.NVFP4_F32 if y.dtype == torch.float32 else _c.NVFP4_BF16
-    ws = gemm_workspace(aq.m, pw.n, aq.k, dev) if workspace is None else workspace
+    ws = gemm_workspace(aq.m, pw.n, aq.k, dev, stream) if workspace is None else workspace
     _c.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, kind,
                                  ws, stream, M=aq.m, K=aq.k)
     return y
@@ -176,8 +196,8 @@ def gemm_gdn_gates(aq: QuantizedAct, pw: PackedWeight, a_log, dt_bias, out_dtype
     return y
 
 
-def quantize_gemm_workspace(m, n, k, device):
-    return torch.empty(_c.nvfp4_quantize_gemm_workspace(m, n, k), dtype=torch.uint8, device=device)
+def quantize_gemm_workspace(m, n, k, device, stream=None):
+    return _scratch(_c.nvfp4_quantize_gemm_workspace(m, n, k), device, stream)
 
 
 def quantize_gemm(x, pw: PackedWeight, g=None, out_dtype=torch.bfloat16, out=None, act_out: QuantizedAct = None,
@@ -195,7 +215,7 @@ def quantize_gemm(x, pw: PackedWeight, g=None, out_dtype=torch.bfloat16, out=Non
     gbuf = act_out.g if act_out is not None else torch.empty(1, dtype=torch.float32, device=dev)
     codes = act_out.codes if act_out is not None else None
     scales = act_out.scales if act_out is not None else None
-    ws = quantize_gemm_workspace(m, pw.n, k, dev) if workspace is None else workspace
+    ws = quantize_gemm_workspace(m, pw.n, k, dev, stream) if workspace is None else workspace
     if g is None:
         _c.nvfp4_quantize_gemm(x, gbuf, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, _c.NVFP4_DYNAMIC, ws,
                                codes, scales, kind, stream)
