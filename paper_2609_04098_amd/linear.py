@@ -57,6 +57,12 @@ def _scratch(nbytes, device, stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
+def _copy_on(dst, src, stream):
+    """``dst.copy_(src)`` in the order of ``stream``, whose next kernel reads it."""
+    with _on(stream, dst.device):
+        return dst.copy_(src)
+
+
 def pack_weight(w, seg_offsets=None, g_seg=None, stream=None) -> PackedWeight:
     """Quantize a bf16 [N, K] weight whose row ranges are separately
     calibrated segments; dynamic per-segment scales unless g_seg is given."""
@@ -70,7 +76,9 @@ def pack_weight(w, seg_offsets=None, g_seg=None, stream=None) -> PackedWeight:
         ws = _scratch(_c.nvfp4_pack_weight_workspace_bytes(n, k, n_seg), dev, stream)
         _c.nvfp4_pack_weight(w, seg_offsets, gs, packed, _c.NVFP4_DYNAMIC, ws, stream)
     else:
-        gs = torch.as_tensor(g_seg, dtype=torch.float32).to(dev).contiguous()
+        gs = g_seg if torch.is_tensor(g_seg) else torch.as_tensor(g_seg, dtype=torch.float32)
+        if gs.device != dev or gs.dtype != torch.float32 or not gs.is_contiguous():
+            gs = _copy_on(torch.empty(gs.shape, dtype=torch.float32, device=dev), gs, stream)
         _c.nvfp4_pack_weight(w, seg_offsets, gs, packed, _c.NVFP4_STATIC, None, stream)
     return PackedWeight(packed, gs, n, k, seg_offsets)
 
@@ -87,7 +95,7 @@ def unpack_weight(pw: PackedWeight, stream=None):
 def harmonize_weight(pw: PackedWeight, in_place=False, stream=None) -> PackedWeight:
     """The one-global-scale form of a fused weight group (section 6 repair):
     a PackedWeight with a single segment whose scale is the shared G."""
-    packed = pw.packed if in_place else pw.packed.clone()
+    packed = pw.packed if in_place else _copy_on(torch.empty_like(pw.packed), pw.packed, stream)
     g = torch.empty(1, dtype=torch.float32, device=packed.device)
     _c.nvfp4_harmonize_weight(packed, pw.n, pw.k, pw.seg_offsets, pw.g_seg, g, stream)
     return PackedWeight(packed, g, pw.n, pw.k, [0, pw.n])
@@ -138,7 +146,7 @@ def rmsnorm_quantize_act(x, gamma, eps, g, out: QuantizedAct = None, y=None, str
     m, k = x.shape
     aq = alloc_act(m, k, x.device) if out is None else out
     if torch.is_tensor(g):
-        aq.g.copy_(g.reshape(1))
+        _copy_on(aq.g, g.reshape(1), stream)
     else:
         _set_scale(aq.g, g, stream)
     _c.nvfp4_rmsnorm_quantize_act(x, gamma, eps, aq.codes, aq.scales, aq.g, y, stream)

@@ -40,6 +40,14 @@ class Recorder:
             self.allocated[t.data_ptr()] = self.current
             return t
 
+        self.copied = {}                       # data_ptr of the target -> stream of its copy
+        copy = torch.Tensor.copy_
+
+        def recorded_copy(t, src, *args):
+            self.copied[t.data_ptr()] = self.current
+            return copy(t, src, *args)
+
+        monkeypatch.setattr(torch.Tensor, "copy_", recorded_copy)
         monkeypatch.setattr(torch.cuda, "stream", switch)
         monkeypatch.setattr(torch, "empty", recorded_empty)
         for name in ("nvfp4_quantize_act", "nvfp4_rmsnorm_quantize_act", "nvfp4_pack_weight", "nvfp4_harmonize_weight",
@@ -74,6 +82,23 @@ def test_scratch_belongs_to_the_stream_that_uses_it(monkeypatch, stream):
         assert rec.stream_of(ws) is stream, name
     for t in (aq.codes, aq.scales, aq.g, y, yf):
         assert rec.stream_of(t) is None
+
+
+@pytest.mark.parametrize("stream", [FakeStream(), None])
+def test_copies_are_in_the_order_of_the_call(monkeypatch, stream):
+    """A scale given as a tensor, and the weight that harmonize_weight leaves
+    as it was, are copied on the stream whose kernel reads the copy."""
+    x, w, pw = _tensors()
+    rec = Recorder(monkeypatch)
+    aq = L.rmsnorm_quantize_act(x, x[0], 1e-6, torch.tensor([3.0]), stream=stream)
+    hw = L.harmonize_weight(pw, stream=stream)
+    pg = L.pack_weight(w, g_seg=torch.tensor([3.0], dtype=torch.float64), stream=stream)
+    for t in (aq.g, hw.packed, pg.g_seg):
+        assert rec.copied[t.data_ptr()] is stream
+    assert aq.g.item() == 3.0 and pg.g_seg.dtype == torch.float32 and pg.g_seg.item() == 3.0
+    assert torch.equal(hw.packed, pw.packed) and hw.packed.data_ptr() != pw.packed.data_ptr()
+    g = torch.tensor([2.0])
+    assert L.pack_weight(w, g_seg=g).g_seg is g and L.pack_weight(w, g_seg=[5.0]).g_seg.item() == 5.0
 
 
 @pytest.mark.gpu
