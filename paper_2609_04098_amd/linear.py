@@ -58,9 +58,10 @@ def _scratch(nbytes, device, stream):
 
 
 def _copy_on(dst, src, stream):
-    """``dst.copy_(src)`` in the order of ``stream``, whose next kernel reads it."""
+    """``dst.copy_(src)`` in the order of ``stream``, whose next kernel reads it.
+    No gradient flows through a scale: a learned one leaves dst a plain buffer."""
     with _on(stream, dst.device):
-        return dst.copy_(src)
+        return dst.copy_(src.detach())
 
 
 def pack_weight(w, seg_offsets=None, g_seg=None, stream=None) -> PackedWeight:
@@ -121,7 +122,7 @@ def _set_scale(buf, g, stream):
     if stream is not None:
         buf.copy_(torch.as_tensor([float(g)], dtype=torch.float32))
     elif torch.is_tensor(g) and g.is_cuda:
-        buf.copy_(g.reshape(1))
+        _copy_on(buf, g.reshape(1), None)
     else:
         buf.fill_(ctypes.c_float(float(g)).value)
 

@@ -101,6 +101,25 @@ def test_copies_are_in_the_order_of_the_call(monkeypatch, stream):
     assert L.pack_weight(w, g_seg=g).g_seg is g and L.pack_weight(w, g_seg=[5.0]).g_seg.item() == 5.0
 
 
+def test_a_learned_scale_leaves_plain_buffers(monkeypatch):
+    """A scale tensor that requires a gradient does not make G one that does."""
+    x, w, pw = _tensors()
+    Recorder(monkeypatch)
+    g = torch.nn.Parameter(torch.tensor([3.0]))
+    for aq in (L.rmsnorm_quantize_act(x, x[0], 1e-6, g), L.quantize_act(x, g=g)):
+        assert not aq.g.requires_grad and aq.g.item() == 3.0
+    assert not L.quantize_gemm(x[:8], pw, g=g)[1].requires_grad
+
+
+@pytest.mark.gpu
+def test_a_learned_scale_on_the_device():
+    x = torch.ones((40, 64), dtype=torch.bfloat16, device="cuda")
+    pw = L.pack_weight(torch.ones((96, 64), dtype=torch.bfloat16, device="cuda"))
+    g = torch.nn.Parameter(torch.tensor([3.0], device="cuda"))
+    for got in (L.rmsnorm_quantize_act(x, x[0], 1e-6, g).g, L.quantize_act(x, g=g).g, L.quantize_gemm(x, pw, g=g)[1]):
+        assert not got.requires_grad and got.item() == 3.0
+
+
 @pytest.mark.gpu
 def test_side_stream_calls_while_the_current_stream_allocates():
     """K parts (whole output; 12 MB of partial sums), the padded activation copy
