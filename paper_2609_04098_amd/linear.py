@@ -162,15 +162,31 @@ def gemm_workspace(m, n, k, device, stream=None):
 
 def gemm(aq: QuantizedAct, pw: PackedWeight, out_dtype=torch.bfloat16, out=None, workspace=None, stream=None):
     """Y = dq(A) dq(W)^T through nvfp4_gemm_with_workspace (a workspace is
-    allocated here when the shape uses one and none is given)."""
+    allocated here when the shape uses one and none is given; where there is no
+    memory left for its partial sums or padded activation, the call runs in the
+    form that needs none, if the shape has one)."""
     if aq.k != pw.k:
         raise ValueError("K mismatch between activation and weight")
     dev = aq.codes.device
     y = out if out is not None else torch.empty((aq.m, pw.n), dtype=out_dtype, device=dev)
     kind = _c.NVFP4_F32 if y.dtype == torch.float32 else _c.NVFP4_BF16
-    ws = gemm_workspace(aq.m, pw.n, aq.k, dev, stream) if workspace is None else workspace
-    _c.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, kind,
-                                 ws, stream, M=aq.m, K=aq.k)
+
+    def run(ws):
+        _c.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, kind,
+                                     ws, stream, M=aq.m, K=aq.k)
+
+    if workspace is None:
+        try:
+            workspace = gemm_workspace(aq.m, pw.n, aq.k, dev, stream)
+        except torch.OutOfMemoryError:
+            try:
+                run(None)
+                return y
+            except _c.Nvfp4Error as e:
+                if e.status != _c.NVFP4_EWORKSPACE:
+                    raise
+            raise
+    run(workspace)
     return y
 
 
