@@ -263,10 +263,10 @@ size_t nvfp4_gemm_workspace(int64_t M, int64_t N, int64_t K);
 /*
  * nvfp4_gemm with a caller workspace (same arguments, same result contract
  * up to the summation order).  Each K half or K part of an output tile writes
- * its segment-scaled FP32 partial sums to the workspace ([parts][M][columns]),
- * and a last pass writes their sum (FP32 additions in part order; bf16 output
- * is that sum rounded to nearest even).  The workspace is overwritten and must
- * not be used by another call in flight.
+ * its FP32 partial sums to the workspace ([parts][M][columns]), and a last pass
+ * writes their segment-scaled sum (FP32 additions in part order, then the scale;
+ * bf16 output is that rounded to nearest even).  The workspace is overwritten
+ * and must not be used by another call in flight.
  *   workspace        device memory, 16-byte aligned, or NULL.
  *   workspace_bytes  its size.
  * Errors: as nvfp4_gemm; NVFP4_EINVAL for a misaligned workspace;

@@ -373,13 +373,13 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
     else
       e = launch_lds_low(o, p, g.first == GemmPlan::kLdsLowSuper, g.k_parts, parts, true, stream);
     if (e != hipSuccess) return e;
-    return launch_sum_parts(parts, g.k_parts, (uint32_t)M, (uint32_t)N, y, (uint32_t)ldy, 0, out_f32, stream);
+    return launch_sum_parts(parts, o, p, g.k_parts, 0, out_f32, stream);
   }
   if (g.second == GemmPlan::kLdsSuperTiles) {
     const uint32_t tiles = (uint32_t)((M + kSquareTile - 1) / kSquareTile) * (uint32_t)((N + kSquareTile - 1) / kSquareTile);
     hipError_t e = launch_lds_super_tiles(o, p, 0, g.n_full, out_f32, stream);
     if (e == hipSuccess) e = launch_lds_super_tile_parts(o, p, g.n_full, tiles, g.tail_parts, parts, stream);
-    if (e == hipSuccess) e = launch_sum_tiles(parts, p, g.n_full, tiles, g.tail_parts, y, out_f32, stream);
+    if (e == hipSuccess) e = launch_sum_tiles(parts, o, p, g.n_full, tiles, g.tail_parts, out_f32, stream);
     return e;
   }
   hipError_t e = run_one(g.first, o, p, 0, g.n_split, out_f32, aligned, stream);
@@ -387,8 +387,7 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
   if (g.second == GemmPlan::kLdsSuperHalves) {
     e = launch_lds_super_parts(o, p, g.n_split, (uint32_t)N, 2, parts, stream);
     if (e != hipSuccess) return e;
-    return launch_sum_parts(parts, 2, (uint32_t)M, (uint32_t)N - g.n_split, y, (uint32_t)ldy, g.n_split, out_f32,
-                            stream);
+    return launch_sum_parts(parts, o, p, 2, g.n_split, out_f32, stream);
   }
   return run_one(g.second, o, p, g.n_split, (uint32_t)N, out_f32, aligned, stream);
 }

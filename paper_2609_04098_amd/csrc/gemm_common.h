@@ -97,8 +97,8 @@ struct GemmParams {
   // when the next kernel's reads evict them).
   uint32_t y_stream;
   // K split across workgroups (LDS kernel, FP32 output only): every tile runs
-  // k_parts times, each on its own run of chunks, part j writing its partial
-  // sums at y + j * part_stride floats.
+  // k_parts times, each on its own run of chunks, part j writing its (unscaled)
+  // partial sums at y + j * part_stride floats.
   uint32_t k_parts, part_stride;
   // Run of tiles (in tile order) of a launch over part of the output (LDS
   // kernel): tiles [tile_begin, tile_begin + tile_count); tile_count = 0: all.
@@ -203,7 +203,9 @@ __device__ __forceinline__ void tile_of(const GemmParams& p, uint32_t& tm, uint3
 }
 
 // Epilogue: y = acc / (G_A * G_W[s]) for the segment s of each column, BF16
-// (round to nearest even) or FP32, rows/columns beyond M/N not stored.
+// (round to nearest even) or FP32, rows/columns beyond M/N not stored.  K parts
+// are stored as they are: 1 / (G_A * G_W[s]) belongs to their sum, a part times
+// it may be out of range where the sum is not.
 template <int FM, int FN, bool kF32Out>
 __device__ __forceinline__ void store_tile(const floatx16 (&acc)[FM][FN], const GemmParams& p,
                                            const float* __restrict__ a_g, const float* __restrict__ w_g,
@@ -218,7 +220,7 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[FM][FN], const 
 #pragma unroll
     for (int i = 1; i < NVFP4_SEG_TABLE - 1; ++i) s += (i < p.n_seg && col >= p.seg_off[i]) ? 1 : 0;
     const float prod = ga * w_g[s];
-    alpha[fb] = prod == 0.0f ? 0.0f : 1.0f / prod;
+    alpha[fb] = kF32Out && p.k_parts > 1 ? 1.0f : prod == 0.0f ? 0.0f : 1.0f / prod;
   }
   if (!kF32Out && p.y_pairs && m0 + FM * 32 <= p.M && n0 + FN * 32 <= p.N) {
     // Whole fragments in range, bf16 pairs aligned: lanes r and r ^ 1 trade
@@ -489,9 +491,10 @@ hipError_t launch_lds_super_tiles(const GemmOperands& o, const GemmParams& p, ui
                                   bool out_f32, hipStream_t stream);
 hipError_t launch_lds_super_tile_parts(const GemmOperands& o, const GemmParams& p, uint32_t tile_begin,
                                        uint32_t tile_end, uint32_t k_parts, float* parts, hipStream_t stream);
-hipError_t launch_sum_tiles(const float* parts, const GemmParams& p, uint32_t tile_begin, uint32_t tile_end,
-                            uint32_t k_parts, void* y, bool out_f32, hipStream_t stream);
-hipError_t launch_sum_parts(const float* parts, uint32_t k_parts, uint32_t M, uint32_t width, void* y, uint32_t ldy,
+hipError_t launch_sum_tiles(const float* parts, const GemmOperands& o, const GemmParams& p, uint32_t tile_begin,
+                            uint32_t tile_end, uint32_t k_parts, bool out_f32, hipStream_t stream);
+// Columns [col0, N) of Y.
+hipError_t launch_sum_parts(const float* parts, const GemmOperands& o, const GemmParams& p, uint32_t k_parts,
                             uint32_t col0, bool out_f32, hipStream_t stream);
 // 128 x 128 and 64 x 256 tiles over all columns, with scale super-stages
 // (K % 256 == 0) or without; k_parts > 1: partial sums to `parts`.

@@ -544,7 +544,7 @@ static hipError_t launch_lds_as(const GemmOperands& o, GemmParams p, uint32_t n_
 }
 
 // Output columns [n_begin, n_end) as k_parts runs of K per tile (whole groups
-// of 4 chunks with super-stages): segment-scaled FP32 partial sums into
+// of 4 chunks with super-stages): unscaled FP32 partial sums into
 // parts[k_parts][M][parts_row(n_end - n_begin)], for sum_parts_kernel.
 template <class C>
 static hipError_t launch_lds_parts(const GemmOperands& o, GemmParams p, uint32_t n_begin, uint32_t n_end,

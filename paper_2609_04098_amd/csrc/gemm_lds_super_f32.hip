@@ -14,21 +14,35 @@ hipError_t launch_lds_super_parts(const GemmOperands& o, const GemmParams& p, ui
   return launch_lds_parts<LdsSquareSuper>(o, p, n_begin, n_end, k_parts, parts, stream);
 }
 
-// Y[row, col0 + c] = part0[row, c] + part1[row, c] + ... for c < width (FP32
-// additions in part order, then RNE to bf16 for bf16 output); four columns
-// per thread (partial rows are parts_row(width) floats; the padding is never
-// stored).  The loads of four parts are in flight together; y_vec: bf16
-// outputs whose groups of four columns start on 8-byte boundaries are stored
-// 8 bytes at a time.
+// Scales of columns col .. col + 3 of Y (col + 3 may lie past N).
+__device__ __forceinline__ float4 column_scales(const GemmParams& p, const float* __restrict__ a_g,
+                                                const float* __restrict__ w_g, uint32_t col) {
+  int s[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) s[j] = segment_of(p, col + j);
+  const float first = segment_scale(a_g, w_g, s[0]);
+  if (s[0] == s[3]) return make_float4(first, first, first, first);
+  return make_float4(first, segment_scale(a_g, w_g, s[1]), segment_scale(a_g, w_g, s[2]), segment_scale(a_g, w_g, s[3]));
+}
+
+// Y[row, col0 + c] = (part0[row, c] + part1[row, c] + ...) * scale for c < width
+// (FP32 additions in part order, one multiplication, then RNE to bf16 for bf16
+// output); four columns per thread (partial rows are parts_row(width) floats;
+// the padding is never stored).  The loads of four parts are in flight together;
+// y_vec: bf16 outputs whose groups of four columns start on 8-byte boundaries are
+// stored 8 bytes at a time.
 template <bool kF32Out>
-__global__ __launch_bounds__(256) void sum_parts_kernel(const float4* __restrict__ parts, uint32_t k_parts, uint32_t n4,
-                                                        uint32_t w4, uint32_t width, void* __restrict__ y, uint32_t ldy,
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float4* __restrict__ parts, GemmParams p, uint32_t n4,
+                                                        uint32_t w4, uint32_t width, const float* __restrict__ a_g,
+                                                        const float* __restrict__ w_g, void* __restrict__ y,
                                                         uint32_t col0, bool y_vec) {
   for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n4; i += gridDim.x * 256u) {
+    const uint32_t row = i / w4, c = (i - row * w4) * 4u;
+    const float4 alpha = column_scales(p, a_g, w_g, col0 + c);
     const float4* q = parts + i;
     float4 a = *q;
 #pragma unroll 4
-    for (uint32_t j = 1; j < k_parts; ++j) {
+    for (uint32_t j = 1; j < p.k_parts; ++j) {
       q += n4;
       const float4 b = *q;
       a.x += b.x;
@@ -36,15 +50,14 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float4* __restrict
       a.z += b.z;
       a.w += b.w;
     }
-    const uint32_t row = i / w4, c = (i - row * w4) * 4u;
-    const float v[4] = {a.x, a.y, a.z, a.w};
+    const float v[4] = {a.x * alpha.x, a.y * alpha.y, a.z * alpha.z, a.w * alpha.w};
     if (kF32Out) {
-      float* d = static_cast<float*>(y) + (size_t)row * ldy + col0 + c;
+      float* d = static_cast<float*>(y) + (size_t)row * p.ldy + col0 + c;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         if (c + j < width) d[j] = v[j];
     } else {
-      uint16_t* d = static_cast<uint16_t*>(y) + (size_t)row * ldy + col0 + c;
+      uint16_t* d = static_cast<uint16_t*>(y) + (size_t)row * p.ldy + col0 + c;
       if (y_vec && c + 4 <= width) {
         *reinterpret_cast<uint2*>(d) = make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3]));
       } else {
@@ -71,6 +84,7 @@ hipError_t launch_lds_super_tile_parts(const GemmOperands& o, const GemmParams& 
 // The same sum over partial tiles [k_parts][tile_count][kSquareTile][kSquareTile].
 template <bool kF32Out>
 __global__ __launch_bounds__(256) void sum_tiles_kernel(const float4* __restrict__ parts, GemmParams p, uint32_t n4,
+                                                        const float* __restrict__ a_g, const float* __restrict__ w_g,
                                                         void* __restrict__ y, bool y_vec) {
   constexpr uint32_t kTile4 = kSquareTile * kSquareTile / 4, kRow4 = kSquareTile / 4;
   for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n4; i += gridDim.x * 256u) {
@@ -78,6 +92,7 @@ __global__ __launch_bounds__(256) void sum_tiles_kernel(const float4* __restrict
     tile_at<LdsSquareSuper::kGroupM>(p, p.tile_begin + i / kTile4, tm, tn);
     const uint32_t row = tm * kSquareTile + i % kTile4 / kRow4, col = tn * kSquareTile + i % kRow4 * 4u;
     if (row >= p.M || col >= p.N) continue;
+    const float4 alpha = column_scales(p, a_g, w_g, col);
     const float4* q = parts + i;
     float4 a = *q;
 #pragma unroll 4
@@ -89,7 +104,7 @@ __global__ __launch_bounds__(256) void sum_tiles_kernel(const float4* __restrict
       a.z += b.z;
       a.w += b.w;
     }
-    const float v[4] = {a.x, a.y, a.z, a.w};
+    const float v[4] = {a.x * alpha.x, a.y * alpha.y, a.z * alpha.z, a.w * alpha.w};
     if (kF32Out) {
       float* d = static_cast<float*>(y) + (size_t)row * p.ldy + col;
 #pragma unroll
@@ -108,8 +123,8 @@ __global__ __launch_bounds__(256) void sum_tiles_kernel(const float4* __restrict
   }
 }
 
-hipError_t launch_sum_tiles(const float* parts, const GemmParams& p, uint32_t tile_begin, uint32_t tile_end,
-                            uint32_t k_parts, void* y, bool out_f32, hipStream_t stream) {
+hipError_t launch_sum_tiles(const float* parts, const GemmOperands& o, const GemmParams& p, uint32_t tile_begin,
+                            uint32_t tile_end, uint32_t k_parts, bool out_f32, hipStream_t stream) {
   GemmParams q = p;
   q.tiles_m = (p.M + kSquareTile - 1) / kSquareTile;
   q.tiles_n = (p.N + kSquareTile - 1) / kSquareTile;
@@ -118,25 +133,29 @@ hipError_t launch_sum_tiles(const float* parts, const GemmParams& p, uint32_t ti
   const uint32_t n4 = (tile_end - tile_begin) * (kSquareTile * kSquareTile / 4);
   const dim3 grid(n4 / 256 < 2048 ? n4 / 256 : 2048), block(256);
   const float4* p4 = reinterpret_cast<const float4*>(parts);
-  const bool y_vec = p.ldy % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0;
+  const bool y_vec = p.ldy % 4 == 0 && reinterpret_cast<uintptr_t>(o.y) % 8 == 0;
   if (out_f32)
-    hipLaunchKernelGGL(sum_tiles_kernel<true>, grid, block, 0, stream, p4, q, n4, y, false);
+    hipLaunchKernelGGL(sum_tiles_kernel<true>, grid, block, 0, stream, p4, q, n4, o.a_g, o.w_g, o.y, false);
   else
-    hipLaunchKernelGGL(sum_tiles_kernel<false>, grid, block, 0, stream, p4, q, n4, y, y_vec);
+    hipLaunchKernelGGL(sum_tiles_kernel<false>, grid, block, 0, stream, p4, q, n4, o.a_g, o.w_g, o.y, y_vec);
   return hipGetLastError();
 }
 
-hipError_t launch_sum_parts(const float* parts, uint32_t k_parts, uint32_t M, uint32_t width, void* y, uint32_t ldy,
+hipError_t launch_sum_parts(const float* parts, const GemmOperands& o, const GemmParams& p, uint32_t k_parts,
                             uint32_t col0, bool out_f32, hipStream_t stream) {
-  const uint32_t w4 = parts_row(width) / 4, n4 = M * w4;
+  GemmParams q = p;
+  q.k_parts = k_parts;
+  const uint32_t width = p.N - col0, w4 = parts_row(width) / 4, n4 = p.M * w4;
   const uint32_t blocks = (n4 + 255) / 256;
   const dim3 grid(blocks < 2048 ? blocks : 2048), block(256);
   const float4* p4 = reinterpret_cast<const float4*>(parts);
-  const bool y_vec = ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(y) + col0 * 2u) % 8 == 0;
+  const bool y_vec = p.ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(o.y) + col0 * 2u) % 8 == 0;
   if (out_f32)
-    hipLaunchKernelGGL(sum_parts_kernel<true>, grid, block, 0, stream, p4, k_parts, n4, w4, width, y, ldy, col0, false);
+    hipLaunchKernelGGL(sum_parts_kernel<true>, grid, block, 0, stream, p4, q, n4, w4, width, o.a_g, o.w_g, o.y, col0,
+                       false);
   else
-    hipLaunchKernelGGL(sum_parts_kernel<false>, grid, block, 0, stream, p4, k_parts, n4, w4, width, y, ldy, col0, y_vec);
+    hipLaunchKernelGGL(sum_parts_kernel<false>, grid, block, 0, stream, p4, q, n4, w4, width, o.a_g, o.w_g, o.y, col0,
+                       y_vec);
   return hipGetLastError();
 }
 

@@ -121,3 +121,31 @@ def test_gemm_last_round_in_k_parts():
     at = torch.from_numpy(rows).cuda()
     check_gemm(y32[at].cpu().numpy().astype(np.float64), y_ref, r_ref, "last round in K parts")
     check_gemm(y_nows[at].cpu().numpy().astype(np.float64), y_ref, r_ref, "no workspace")
+
+
+@pytest.mark.parametrize("m,n,k,kernel", [
+    (200, 2600, 17408, "K parts"),           # the whole output in K parts
+    (8192, 2304, 512, "two K halves"),       # the last round in K halves
+    (7000, 5120, 17408, "last round"),       #   in K parts
+])
+def test_gemm_partial_sums_past_the_output_range(m, n, k, kernel):
+    """Activations near the top of the bf16 range against weights that are
+    positive in the first half of K and the same negated in the second: Y is
+    far inside FP32's range, the sum over the first half (or a part of it), in
+    Y's units, is not."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert any(kernel in name for name in L.gemm_kernels(m, n, k))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m)
+    half = 8e38 * (k / 512) ** 0.5            # sum over the first half, on average
+    x = (torch.rand((m, k), generator=gen, device="cuda") + 1.0).mul_(1.5e38).to(torch.bfloat16)
+    w = torch.rand((n, k // 2), generator=gen, device="cuda").add_(1.0).mul_(half / (0.5 * k * 2.25e38) / 1.5)
+    w = torch.cat([w, -w], 1)
+    aq, pw = L.quantize_act(x), L.pack_weight(w.to(torch.bfloat16))
+    y = L.gemm(aq, pw, out_dtype=torch.float32)
+    ref = L.gemm_no_workspace(aq, pw, out_dtype=torch.float32)
+    assert bool(torch.isfinite(ref).all()) and float(ref.abs().max()) < 1.7e38
+    # FP32 sums in another order: within 1e-4 of the sum of the magnitudes, as
+    # everywhere (here in units of 1e30, which keeps it inside FP32's range).
+    assert float((y * 1e-30 - ref * 1e-30).abs().max()) <= 1e-4 * 2.0 * half * 1e-30
+    assert torch.equal(L.gemm(aq, pw).view(torch.int16), y.to(torch.bfloat16).view(torch.int16))
