@@ -25,12 +25,37 @@ __device__ __forceinline__ float4 column_scales(const GemmParams& p, const float
   return make_float4(first, segment_scale(a_g, w_g, s[1]), segment_scale(a_g, w_g, s[2]), segment_scale(a_g, w_g, s[3]));
 }
 
+// The sum of a group of four columns over the parts (q: its part 0, n4 groups per
+// part), in part order, times the columns' scales.  The loads of the first four
+// parts are in flight while the scales are formed.
+__device__ __forceinline__ float4 scaled_sum(const float4* __restrict__ q, uint32_t n4, const GemmParams& p,
+                                             const float* __restrict__ a_g, const float* __restrict__ w_g,
+                                             uint32_t col) {
+  float4 first[4];
+#pragma unroll
+  for (uint32_t j = 0; j < 4; ++j)
+    if (j < p.k_parts) first[j] = q[(size_t)j * n4];
+  const float4 alpha = column_scales(p, a_g, w_g, col);
+  float4 a = first[0];
+  auto add = [&a](const float4& b) {
+    a.x += b.x;
+    a.y += b.y;
+    a.z += b.z;
+    a.w += b.w;
+  };
+#pragma unroll
+  for (uint32_t j = 1; j < 4; ++j)
+    if (j < p.k_parts) add(first[j]);
+#pragma unroll 4
+  for (uint32_t j = 4; j < p.k_parts; ++j) add(q[(size_t)j * n4]);
+  return make_float4(a.x * alpha.x, a.y * alpha.y, a.z * alpha.z, a.w * alpha.w);
+}
+
 // Y[row, col0 + c] = (part0[row, c] + part1[row, c] + ...) * scale for c < width
 // (FP32 additions in part order, one multiplication, then RNE to bf16 for bf16
 // output); four columns per thread (partial rows are parts_row(width) floats;
-// the padding is never stored).  The loads of four parts are in flight together;
-// y_vec: bf16 outputs whose groups of four columns start on 8-byte boundaries are
-// stored 8 bytes at a time.
+// the padding is never stored).  y_vec: bf16 outputs whose groups of four columns
+// start on 8-byte boundaries are stored 8 bytes at a time.
 template <bool kF32Out>
 __global__ __launch_bounds__(256) void sum_parts_kernel(const float4* __restrict__ parts, GemmParams p, uint32_t n4,
                                                         uint32_t w4, uint32_t width, const float* __restrict__ a_g,
@@ -38,19 +63,8 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float4* __restrict
                                                         uint32_t col0, bool y_vec) {
   for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n4; i += gridDim.x * 256u) {
     const uint32_t row = i / w4, c = (i - row * w4) * 4u;
-    const float4 alpha = column_scales(p, a_g, w_g, col0 + c);
-    const float4* q = parts + i;
-    float4 a = *q;
-#pragma unroll 4
-    for (uint32_t j = 1; j < p.k_parts; ++j) {
-      q += n4;
-      const float4 b = *q;
-      a.x += b.x;
-      a.y += b.y;
-      a.z += b.z;
-      a.w += b.w;
-    }
-    const float v[4] = {a.x * alpha.x, a.y * alpha.y, a.z * alpha.z, a.w * alpha.w};
+    const float4 sum = scaled_sum(parts + i, n4, p, a_g, w_g, col0 + c);
+    const float v[4] = {sum.x, sum.y, sum.z, sum.w};
     if (kF32Out) {
       float* d = static_cast<float*>(y) + (size_t)row * p.ldy + col0 + c;
 #pragma unroll
@@ -92,19 +106,8 @@ __global__ __launch_bounds__(256) void sum_tiles_kernel(const float4* __restrict
     tile_at<LdsSquareSuper::kGroupM>(p, p.tile_begin + i / kTile4, tm, tn);
     const uint32_t row = tm * kSquareTile + i % kTile4 / kRow4, col = tn * kSquareTile + i % kRow4 * 4u;
     if (row >= p.M || col >= p.N) continue;
-    const float4 alpha = column_scales(p, a_g, w_g, col);
-    const float4* q = parts + i;
-    float4 a = *q;
-#pragma unroll 4
-    for (uint32_t j = 1; j < p.k_parts; ++j) {
-      q += n4;
-      const float4 b = *q;
-      a.x += b.x;
-      a.y += b.y;
-      a.z += b.z;
-      a.w += b.w;
-    }
-    const float v[4] = {a.x * alpha.x, a.y * alpha.y, a.z * alpha.z, a.w * alpha.w};
+    const float4 sum = scaled_sum(parts + i, n4, p, a_g, w_g, col);
+    const float v[4] = {sum.x, sum.y, sum.z, sum.w};
     if (kF32Out) {
       float* d = static_cast<float*>(y) + (size_t)row * p.ldy + col;
 #pragma unroll
