@@ -95,13 +95,7 @@ __global__ __launch_bounds__(kThreads) void amax_partial_kernel(const uint16_t* 
   if (threadIdx.x == 0) partial[blockIdx.x] = __uint_as_float(mx << 16);
 }
 
-// Grid-strided loop over 16-element blocks: 32 bytes of bf16 in, 8 bytes of
-// packed codes and 1 scale byte out per block.  The next block's loads are
-// issued before the current block is quantized (two blocks in flight per
-// thread).  (Walking the blocks from the end of X to its start after the
-// amax pass, so as to meet the most recently read part of X in the MALL,
-// measured 2% slower on a 335 MB activation and is not done.)
-// d0, d1: the thread's first block.
+// Address of 16-element block b of X.
 template <bool kContig>
 __device__ __forceinline__ const uint4* block_ptr(const uint16_t* x, uint32_t b, uint32_t blocks_per_row,
                                                   uint32_t ldx) {
@@ -110,6 +104,13 @@ __device__ __forceinline__ const uint4* block_ptr(const uint16_t* x, uint32_t b,
   return reinterpret_cast<const uint4*>(x + (size_t)row * ldx) + 2 * col;
 }
 
+// Grid-strided loop over 16-element blocks: 32 bytes of bf16 in, 8 bytes of
+// packed codes and 1 scale byte out per block.  The next block's loads are
+// issued before the current block is quantized (two blocks in flight per
+// thread).  (Walking the blocks from the end of X to its start after the
+// amax pass, so as to meet the most recently read part of X in the MALL,
+// measured 2% slower on a 335 MB activation and is not done.)
+// d0, d1: the thread's first block.
 template <bool kContig, bool kExact>
 __device__ __forceinline__ void quantize_blocks(const uint16_t* __restrict__ x, uint32_t n_blocks,
                                                 uint32_t blocks_per_row, uint32_t ldx,

@@ -312,7 +312,7 @@ template <int KS, int FM, int FN, int kGroup, bool kF32Out, bool kGate>
 __device__ __forceinline__ void splitk_epilogue(const floatx16 (&acc)[FM][FN], float* part, const GemmParams& p,
                                                 const float (&alpha)[FN], void* __restrict__ y,
                                                 uint32_t m0, uint32_t n0, uint32_t wave, uint32_t lane) {
-  static_assert(KS == 4 || KS == 8 || KS == 16, "entries per wave");
+  static_assert(KS == 4 || KS == 8, "entries per wave");
   constexpr int kPer = 16 / KS, kFrags = FM * FN;
   typedef float entries __attribute__((ext_vector_type(kPer)));
   typedef float floatx4 __attribute__((ext_vector_type(4)));

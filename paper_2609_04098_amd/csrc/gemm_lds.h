@@ -51,12 +51,7 @@ struct LdsCfg {
   // columns, rows padded by 16 bytes.
   static constexpr int kEpiPitch = FN * 32 * 2 + 16;
   static constexpr int kEpiBytes = kWaves * 32 * kEpiPitch;
-  // Where that area would cost a workgroup per CU, the staging uses the ring
-  // instead (after a barrier, which the other workgroups cover).
-  static constexpr bool kEpiInRing = kOcc * (kLdsBytes + kEpiBytes) > 160 * 1024;
-  static constexpr int kEpiBase = kEpiInRing ? 0 : kLdsBytes;
-  static constexpr int kLdsTotal = kEpiInRing ? kLdsBytes : kLdsBytes + kEpiBytes;   // bf16 output
-  static_assert(!kEpiInRing || kEpiBytes <= kLdsBytes, "staging fits the ring");
+  static constexpr int kLdsTotal = kLdsBytes + kEpiBytes;     // bf16 output
   // DMA loads per chunk and wave (without the super-stage loads).
   static constexpr int kLoadsPerWave = kAPerWave + kBPerWave + (kSuper ? 0 : kSDmaA + kSDmaB);
   static constexpr int kSuperLoads = 2;          // per 4 chunks: one A pair, one W pair
@@ -521,9 +516,8 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   }
   if constexpr (kTransposed) {
     constexpr int kPitch = C::kEpiPitch;
-    if constexpr (C::kEpiInRing) __syncthreads();            // every wave has left the ring
     store_tile_t<FM, FN, kPitch>(acc, p, ep, a_g, w_g, yo, m0_wave, n0_wave, lane,
-                                 smem + C::kEpiBase + wave * 32 * kPitch);
+                                 smem + C::kLdsBytes + wave * 32 * kPitch);
   } else {
     store_tile<FM, FN, kF32Out>(acc, p, a_g, w_g, yo, m0_wave, n0_wave, r, h);
   }

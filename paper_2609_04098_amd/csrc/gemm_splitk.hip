@@ -477,8 +477,7 @@ hipError_t launch_decode_quant_gemm(const GemmOperands& o, GemmParams p, const D
                                     bool out_f32, hipStream_t stream) {
   if (p.M <= 16)
     return launch_rows16_quant(decode_shape(p.M, p.N, p.K, cu_count()), o, p, q, dynamic, out_f32, stream);
-  switch (decode_shape(p.M, p.N, p.K, cu_count())) {
-    case DecodeShape::k8Shared:
+  switch (decode_shape(p.M, p.N, p.K, cu_count())) {         // K < 1024 here: no k8Shared
     case DecodeShape::k8SharedPair:
     case DecodeShape::k8Shared3: return launch_decode_quant<8, 1, 4>(o, p, q, dynamic, out_f32, stream);
     default: return launch_decode_quant<4, 2, 4>(o, p, q, dynamic, out_f32, stream);
