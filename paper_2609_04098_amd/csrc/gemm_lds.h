@@ -48,9 +48,10 @@ struct LdsCfg {
   static constexpr int kLdsBytes = kSuperBase + (kSuper ? 2 * kSuperBytes : 0);
   // BF16 epilogue staging, beyond the ring (so that no wave waits for the
   // others to leave the ring): per wave 32 output rows of its FN fragment
-  // columns, rows padded by 16 bytes.
+  // columns, rows padded by 16 bytes, then a scale per column.
   static constexpr int kEpiPitch = FN * 32 * 2 + 16;
-  static constexpr int kEpiBytes = kWaves * 32 * kEpiPitch;
+  static constexpr int kEpiWave = 32 * kEpiPitch + FN * 32 * 4;
+  static constexpr int kEpiBytes = kWaves * kEpiWave;
   static constexpr int kLdsTotal = kLdsBytes + kEpiBytes;     // bf16 output
   // DMA loads per chunk and wave (without the super-stage loads).
   static constexpr int kLoadsPerWave = kAPerWave + kBPerWave + (kSuper ? 0 : kSDmaA + kSDmaB);
@@ -113,7 +114,8 @@ static_assert(LdsSquare::BM == kSquareTile && LdsSquare::BN == kSquareTile && Ld
 // per instruction took 3 times as long per tile in isolation, and the
 // epilogue 4.8 instead of 3.3 us per tile on mlp_gate_up).  Other blocks
 // (partial, unaligned, or with a segment boundary inside the wave's columns)
-// are stored element by element.  The staged stores are non-temporal when
+// are staged too, with a scale per column and narrower or fewer stores.  The
+// staged stores of whole blocks are non-temporal when
 // the output is at least as large as the MALL (p.y_stream), each
 // instruction then writing 4 whole rows of the wave block (256 bytes each):
 // with ordinary stores, the dirty lines of mlp_gate_up's 570 MB output were
@@ -157,9 +159,10 @@ __device__ __forceinline__ EpiPlan epi_plan(const GemmParams& p, const float* __
 template <int FM, int FN, int kPitch>
 __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], const GemmParams& p, EpiPlan ep,
                                              const float* __restrict__ a_g, const float* __restrict__ w_g,
-                                             void* __restrict__ y, uint32_t m0, uint32_t n0, uint32_t lane,
-                                             uint8_t* stage) {
+                                             void* __restrict__ y, uint32_t m0, uint32_t n0, uint8_t* stage) {
   constexpr uint32_t E = 2u;                      // bytes per output element
+  // The lane again (not from a register that would be kept through the K loop).
+  const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const uint32_t r = lane & 31u, h = lane >> 5;
   if (ep.whole) {
     const float alpha = ep.alpha;
@@ -213,22 +216,77 @@ __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], cons
     }
     return;
   }
+  // Blocks past M or N, of several segments, or in outputs whose rows allow no
+  // 16-byte stores: staged the same way, with a scale per column, and stored in
+  // pieces of 16 or 4 bytes (2 where a pair is not aligned or reaches past N).
+  // Element by element from the accumulators (64 lanes on 32 rows, a store per
+  // element) such a block took 20 to 30 us, most of a short-K call: 8000 x 1300 x
+  // 128 48.2 us on 256 x 256 tiles and 46.7 on 128 x 128, with this 16.6.
+  if (m0 >= p.M || n0 >= p.N) return;
+  float* scale = reinterpret_cast<float*>(stage + 32 * kPitch);
+  const uint32_t cols = p.N - n0 < FN * 32u ? p.N - n0 : FN * 32u;
 #pragma unroll
-  for (int fb = 0; fb < FN; ++fb)
+  for (uint32_t c = 0; c < FN * 32u; c += 64)
+    scale[c + lane] = c + lane < cols ? segment_scale(a_g, w_g, segment_of(p, n0 + c + lane)) : 0.0f;
+  const bool pieces = ((p.ldy * 2u) & 15u) == 0 && (reinterpret_cast<uintptr_t>(y) & 15u) == 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+  for (int fa = 0; fa < FM; ++fa) {
+    const uint32_t row0 = m0 + fa * 32u;
+    if (row0 >= p.M) return;
+    const uint32_t rows = p.M - row0 < 32u ? p.M - row0 : 32u;
+    // One fragment row at a time is copied out of the accumulators: all of them
+    // ahead of the branch need more registers than there are.
+    floatx16 part[FN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t col = n0 + fb * 32u + q * 8u + h * 4u + i;
-        if (col >= p.N) continue;
-        const float a = segment_scale(a_g, w_g, segment_of(p, col));
+    for (int fb = 0; fb < FN; ++fb) {
+      part[fb] = acc[fa][fb];
+      asm volatile("" : "+v"(part[fb]));
+    }
 #pragma unroll
-        for (int fa = 0; fa < FM; ++fa) {
-          const uint32_t row = m0 + fa * 32u + r;
-          if (row < p.M)
-            static_cast<uint16_t*>(y)[(size_t)row * p.ldy + col] = f32_to_bf16_rne(acc[fa][fb][4 * q + i] * a);
+    for (int fb = 0; fb < FN; ++fb)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const floatx16& v = part[fb];
+        const uint32_t c = fb * 32u + q * 8u + h * 4u;
+        const float4 a = *reinterpret_cast<const float4*>(scale + c);
+        const uint32_t lo = pack_bf16_rne(v[4 * q] * a.x, v[4 * q + 1] * a.y);
+        const uint32_t hi = pack_bf16_rne(v[4 * q + 2] * a.z, v[4 * q + 3] * a.w);
+        *reinterpret_cast<u32x2*>(stage + r * kPitch + c * E) = u32x2{lo, hi};
+      }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint16_t* y0 = static_cast<uint16_t*>(y) + (size_t)row0 * p.ldy + n0;
+    if (pieces) {
+      constexpr uint32_t kLanes = FN * 4u, kRows = 64u / kLanes;
+      const uint32_t c = lane % kLanes * 8u;
+#pragma unroll 1
+      for (uint32_t row = lane / kLanes; row < rows; row += kRows) {
+        const uint8_t* src = stage + row * kPitch + c * E;
+        uint16_t* dst = y0 + (size_t)row * p.ldy + c;
+        if (c + 8u <= cols) {
+          *reinterpret_cast<int4v*>(dst) = *reinterpret_cast<const int4v*>(src);
+        } else {
+          for (uint32_t i = 0; c + i < cols; ++i) dst[i] = reinterpret_cast<const uint16_t*>(src)[i];
         }
       }
+    } else {
+      constexpr uint32_t kLanes = FN * 16u < 64u ? FN * 16u : 64u, kRows = 64u / kLanes;
+      const uint32_t c = lane % kLanes * 2u;
+      static_assert(kLanes * 2u == FN * 32u, "a wave covers whole rows");
+#pragma unroll 1
+      for (uint32_t row = lane / kLanes; row < rows; row += kRows) {
+        const uint32_t v = *reinterpret_cast<const uint32_t*>(stage + row * kPitch + c * E);
+        uint16_t* dst = y0 + (size_t)row * p.ldy + c;
+        if (p.y_pairs && c + 2u <= cols) {
+          *reinterpret_cast<uint32_t*>(dst) = v;
+        } else {
+          if (c < cols) dst[0] = (uint16_t)v;
+          if (c + 1u < cols) dst[1] = (uint16_t)(v >> 16);
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
 }
 
 template <class C, bool kF32Out>
@@ -516,8 +574,8 @@ __global__ __launch_bounds__(C::kThreads, C::kOcc) void gemm_lds_kernel(const ui
   }
   if constexpr (kTransposed) {
     constexpr int kPitch = C::kEpiPitch;
-    store_tile_t<FM, FN, kPitch>(acc, p, ep, a_g, w_g, yo, m0_wave, n0_wave, lane,
-                                 smem + C::kLdsBytes + wave * 32 * kPitch);
+    store_tile_t<FM, FN, kPitch>(acc, p, ep, a_g, w_g, yo, m0_wave, n0_wave,
+                                 smem + C::kLdsBytes + wave * C::kEpiWave);
   } else {
     store_tile<FM, FN, kF32Out>(acc, p, a_g, w_g, yo, m0_wave, n0_wave, r, h);
   }

@@ -149,3 +149,31 @@ def test_gemm_partial_sums_past_the_output_range(m, n, k, kernel):
     # everywhere (here in units of 1e30, which keeps it inside FP32's range).
     assert float((y * 1e-30 - ref * 1e-30).abs().max()) <= 1e-4 * 2.0 * half * 1e-30
     assert torch.equal(L.gemm(aq, pw).view(torch.int16), y.to(torch.bfloat16).view(torch.int16))
+
+
+@pytest.mark.parametrize("m,n,k,offs", [
+    (1100, 2301, 2112, [0, 37, 1000, 2301]),     # 128 x 128 tiles: odd rows, segments inside a wave's 64 columns
+    (1100, 2304, 2048, [0, 2304]),               #   ragged rows only
+    (1153, 2298, 2112, [0, 1150, 2298]),         #   one row past a tile, N % 8 == 2
+    (131, 20793, 2816, [0, 9000, 9040, 20793]),  # 64 x 256 tiles
+    (4100, 8190, 320, [0, 100, 200, 300, 8190]), # 256 x 256 tiles, four segments in a wave's 128 columns
+    (4097, 4360, 320, [0, 4360]),                #   a last tile of one row
+])
+def test_bf16_tiles_past_the_edges(m, n, k, offs):
+    """bf16 blocks that reach past M or N, hold segment boundaries, or lie in
+    rows that allow 16-byte, 4-byte or only 2-byte stores: equal to RNE of the
+    FP32 output, and nothing around them written."""
+    assert "gemm_lds_kernel" in L.gemm_kernels(m, n, k, False)[0]
+    rng = np.random.default_rng(m + n)
+    xb = synth.f64_to_bf16_bits(rng.standard_normal((m, k)))
+    wb = synth.f64_to_bf16_bits(rng.standard_normal((n, k)) * 0.02)
+    aq, pw = L.quantize_act(to_dev_bf16(xb)), L.pack_weight(to_dev_bf16(wb), offs)
+    want = L.gemm_no_workspace(aq, pw, out_dtype=torch.float32).to(torch.bfloat16).view(torch.int16)
+    up8 = (n + 7) // 8 * 8
+    for ldy, shift in ((n, 0), (up8, 0), (up8 + 8, 1), (up8 + 2, 0), (up8 + 2, 2), (up8 + 8, 8)):
+        buf = torch.full(((m + 1) * ldy + shift + 8,), -7.0, dtype=torch.bfloat16, device="cuda")
+        y = buf[shift:shift + (m + 1) * ldy].view(m + 1, ldy)
+        L.gemm_no_workspace(aq, pw, out=y[:m, :n])
+        assert torch.equal(y[:m, :n].view(torch.int16), want), (ldy, shift)
+        assert bool((y[:m, n:] == -7.0).all()) and bool((y[m] == -7.0).all())
+        assert bool((buf[:shift] == -7.0).all()) and bool((buf[shift + (m + 1) * ldy:] == -7.0).all())
