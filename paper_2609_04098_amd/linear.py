@@ -53,6 +53,8 @@ def _scratch(nbytes, device, stream):
     freed block to the next allocation on the stream it was allocated on, in
     that stream's order: scratch that its call drops on return has to come from
     the stream that uses it."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
     with _on(stream, device):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
@@ -170,23 +172,19 @@ def gemm(aq: QuantizedAct, pw: PackedWeight, out_dtype=torch.bfloat16, out=None,
     dev = aq.codes.device
     y = out if out is not None else torch.empty((aq.m, pw.n), dtype=out_dtype, device=dev)
     kind = _c.NVFP4_F32 if y.dtype == torch.float32 else _c.NVFP4_BF16
-
-    def run(ws):
-        _c.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, kind,
-                                     ws, stream, M=aq.m, K=aq.k)
-
+    no_memory = False
     if workspace is None:
         try:
             workspace = gemm_workspace(aq.m, pw.n, aq.k, dev, stream)
         except torch.OutOfMemoryError:
-            try:
-                run(None)
-                return y
-            except _c.Nvfp4Error as e:
-                if e.status != _c.NVFP4_EWORKSPACE:
-                    raise
-            raise
-    run(workspace)
+            no_memory = True
+    try:
+        _c.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, kind,
+                                     workspace, stream, M=aq.m, K=aq.k)
+    except _c.Nvfp4Error as e:
+        if no_memory and e.status == _c.NVFP4_EWORKSPACE:
+            gemm_workspace(aq.m, pw.n, aq.k, dev, stream)      # what is missing
+        raise
     return y
 
 
