@@ -182,9 +182,9 @@ def gemm(aq: QuantizedAct, pw: PackedWeight, out_dtype=torch.bfloat16, out=None,
         _c.nvfp4_gemm_with_workspace(aq.codes, aq.scales, aq.g, pw.packed, pw.n, pw.seg_offsets, pw.g_seg, y, kind,
                                      workspace, stream, M=aq.m, K=aq.k)
     except _c.Nvfp4Error as e:
-        if no_memory and e.status == _c.NVFP4_EWORKSPACE:
-            gemm_workspace(aq.m, pw.n, aq.k, dev, stream)      # what is missing
-        raise
+        if not no_memory or e.status != _c.NVFP4_EWORKSPACE:
+            raise
+        return gemm(aq, pw, out=y, workspace=gemm_workspace(aq.m, pw.n, aq.k, dev, stream), stream=stream)
     return y
 
 
