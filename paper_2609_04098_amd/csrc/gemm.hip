@@ -32,12 +32,13 @@ uint32_t cu_count() {
 // partly filled last round of square tiles takes 0.74 to 0.8 of a full one (320
 // and 384 tiles at K = 5120, 400 at K = 17408: 240, 242 and 699 us against 138
 // and 389 for one round), a lone round of up to 0.85 of the CUs 0.9 (128 to 204
-// tiles).  Smaller tiles, several to a CU, gain less (`last`, `lone`), and
-// split-K tiles, whose waves wait more, need a second workgroup on the CU to
-// reach their rate (lone 1.1).
+// tiles); at K = 2048, where M and N reach no further than whole tiles, of up to
+// 0.6 of them 0.72 (64 to 160 tiles 41 to 45 us, 192 48, 256 57).  Smaller tiles,
+// several to a CU, gain less (`last`, `lone`), and split-K tiles, whose waves wait
+// more, need a second workgroup on the CU to reach their rate (lone 1.1).
 static float rounds_of(uint64_t workgroups, uint32_t n_cu, float last, float lone) {
-  const float frac = (float)(workgroups % n_cu) / (float)n_cu;
-  if (workgroups < n_cu) return lone >= 1.0f || frac <= 0.85f ? lone : lone + (1.0f - lone) * (frac - 0.85f) / 0.15f;
+  const float frac = (float)(workgroups % n_cu) / (float)n_cu, knee = lone < 0.8f ? 0.6f : 0.85f;
+  if (workgroups < n_cu) return lone >= 1.0f || frac <= knee ? lone : lone + (1.0f - lone) * (frac - knee) / (1.0f - knee);
   return (float)(workgroups / n_cu) + (frac == 0.0f ? 0.0f : frac > last ? frac : last);
 }
 
@@ -46,24 +47,35 @@ struct TileCost {
   uint32_t bm, bn;
   float chunk_us, chunk_us_super;   // one 64-deep chunk of a tile
   float fixed_us;                   // first loads, epilogue, launch
+  float round_us;                   // first loads and epilogue of a further round, at short K
   float last, lone;                 // see rounds_of
   uint32_t max_parts;               // K parts the launcher offers (with super-stages; square: only with them)
 };
-// Fitted, on one box, to M = 50 .. 1000 against N = 4352 .. 34816 at K = 5120,
-// to N = 5120 at K = 2176 .. 17408, and for the square tile to larger M.  The
+// Fitted to M = 50 .. 1000 against N = 4352 .. 34816 at K = 5120 and to N = 5120
+// at K = 2176 .. 17408, the square tile also to larger M, and checked at M = 64 ..
+// 3000, N = 256 .. 8192, K = 64 .. 5120 (below N of about 1000 and K of 2000 the
+// estimates order the tiles, their times are off by up to a third).  The
 // split-K tiles (four or eight waves share a tile's reduction and meet in LDS) have
 // the cheaper small tile, the LDS tiles the cheaper large one and K parts.
+// round_us: below kShortK the chunks of a split-K tile don't cover the first
+// loads and the epilogue of the next round's tile (1024 x 5120 with 64 x 64 tiles,
+// five rounds: 14.9 us at K = 64 and at K = 256; 128 x 128 tiles 7.2 and 9.5).
 constexpr TileCost kTileCosts[] = {
-    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 7.5f, 0.75f, 0.9f, 32},
-    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.53f, 0.465f, 6.5f, 0.92f, 0.95f, 32},
-    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.57f, 0.515f, 7.0f, 0.92f, 0.95f, 32},
-    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.175f, 0.175f, 6.5f, 1.0f, 1.1f, 1},
-    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.15f, 0.15f, 5.5f, 1.0f, 1.1f, 1},
-    {GemmPlan::kSplitk32x160, GemmPlan::kSplitk32x160, 32, 160, 0.185f, 0.185f, 6.0f, 1.0f, 1.1f, 1},
-    {GemmPlan::kSplitk32x96, GemmPlan::kSplitk32x96, 32, 96, 0.12f, 0.12f, 0.0f, 1.0f, 1.0f, 1},
-    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.08f, 0.08f, 5.5f, 1.0f, 1.1f, 1},
-    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 1.0f, 1.1f, 1},
+    {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 7.5f, 0.0f, 0.75f, 0.9f, 32},
+    {GemmPlan::kLdsMid, GemmPlan::kLdsMidSuper, 128, 128, 0.53f, 0.465f, 6.5f, 0.0f, 0.92f, 0.95f, 32},
+    {GemmPlan::kLdsLow, GemmPlan::kLdsLowSuper, 64, 256, 0.57f, 0.515f, 7.0f, 0.0f, 0.92f, 0.95f, 32},
+    {GemmPlan::kSplitk64x96, GemmPlan::kSplitk64x96, 64, 96, 0.175f, 0.175f, 6.5f, 1.8f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk64x64, GemmPlan::kSplitk64x64, 64, 64, 0.15f, 0.15f, 5.5f, 1.5f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x160, GemmPlan::kSplitk32x160, 32, 160, 0.185f, 0.185f, 6.0f, 1.5f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x96, GemmPlan::kSplitk32x96, 32, 96, 0.12f, 0.12f, 0.0f, 0.0f, 1.0f, 1.0f, 1},
+    {GemmPlan::kSplitk32x64, GemmPlan::kSplitk32x64, 32, 64, 0.08f, 0.08f, 5.5f, 0.5f, 1.0f, 1.1f, 1},
+    {GemmPlan::kSplitk32x32, GemmPlan::kSplitk32x32, 32, 32, 0.06f, 0.06f, 4.0f, 0.0f, 1.0f, 1.1f, 1},
 };
+constexpr int64_t kShortK = 2048;
+// The square tile at K <= kShortK.
+constexpr TileCost kSquareShort = {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 9.0f, 0.0f, 0.75f, 0.72f, 32};
+
+static const TileCost& square_cost(int64_t K) { return K <= kShortK ? kSquareShort : kTileCosts[0]; }
 // The summing pass: a launch, and every partial sum written and read once
 // (they stay in the last-level cache).
 constexpr float kSumLaunchUs = 2.5f, kPartBytesPerUs = 6.0e6f;
@@ -79,7 +91,6 @@ constexpr uint32_t kMinPartChunks = 4;   // one group of chunks with super-stage
 // each operand between their waves, are the better ones there), 5 below K =
 // 1024, where the estimates are mostly fixed cost.
 constexpr int64_t kSplitkMaxRows = 1024;
-constexpr int64_t kSplitkShortK = 2048;
 constexpr uint64_t kSplitkMaxRounds = 6, kSplitkMaxRoundsShort = 5;
 
 // Below this K the K-halves / tall-tile form of the last round is kept as
@@ -98,12 +109,13 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
   const uint32_t unit = super ? 4 : 1, units = (uint32_t)(K / 64) / unit;
   GemmPlan best{};
   *cost = 0.0f;
-  for (const TileCost& t : kTileCosts) {
-    const bool square = t.kind == GemmPlan::kLdsSquare;
+  for (const TileCost& row : kTileCosts) {
+    const bool square = row.kind == GemmPlan::kLdsSquare;
+    const TileCost& t = square ? square_cost(K) : row;
     const uint64_t tiles = (uint64_t)((M + t.bm - 1) / t.bm) * (uint64_t)((N + t.bn - 1) / t.bn);
     const bool splitk = t.kind == t.super_kind;
     const uint64_t max_rounds = K < 1024 ? kSplitkMaxRoundsShort : kSplitkMaxRounds;
-    if (splitk && ((M > kSplitkMaxRows && K >= kSplitkShortK) || tiles > max_rounds * n_cu)) continue;
+    if (splitk && ((M > kSplitkMaxRows && K >= kShortK) || tiles > max_rounds * n_cu)) continue;
     for (uint32_t parts = 1; parts <= t.max_parts; ++parts) {
       const uint64_t part_bytes = (uint64_t)parts * (uint64_t)M * parts_row((uint32_t)N) * sizeof(float);
       if (parts > 1 && (!with_ws || units * unit < parts * kMinPartChunks || part_bytes > kMaxPartBytes ||
@@ -112,9 +124,13 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
       // 32 x 96 tiles of eight waves fill a CU's LDS: a round's first loads and
       // epilogue (5 us, 42 chunks' worth) are not covered by another workgroup.
       const uint32_t chunks = (units + parts - 1) / parts * unit + (t.kind == GemmPlan::kSplitk32x96 ? 42 : 0);
-      const float c = rounds_of(tiles * parts, n_cu, t.last, t.lone) * (float)chunks *
-                          (super ? t.chunk_us_super : t.chunk_us) +
-                      t.fixed_us + (parts > 1 ? kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs : 0.0f);
+      const float rounds = rounds_of(tiles * parts, n_cu, t.last, t.lone);
+      float c = rounds * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us;
+      if (K < kShortK && rounds > 1.0f) {
+        const float fade = 2.0f - 2.0f * (float)K / (float)kShortK;      // from kShortK / 2 on
+        c += (rounds - 1.0f) * (fade < 1.0f ? fade : 1.0f) * t.round_us;
+      }
+      if (parts > 1) c += kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs;
       if (best.first == GemmPlan::kNone || c < *cost) {
         best.first = super ? t.super_kind : t.kind;
         best.k_parts = parts;
@@ -154,7 +170,7 @@ static GemmPlan plan_square(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool
 // then a summing pass.  K % 256 == 0.
 static GemmPlan plan_square_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, float* cost) {
   GemmPlan best{};
-  const TileCost& sq = kTileCosts[0];
+  const TileCost& sq = square_cost(K);
   const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
   const uint64_t rem = tiles % n_cu;
   const uint32_t units = (uint32_t)(K / 256);
@@ -196,7 +212,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
     g = plan_square(M, N, K, n_cu, with_ws);
     const bool tail = g.second != GemmPlan::kNone;
     if (n_cu != 0 && (!tail || K >= kTailMinK)) {
-      const TileCost& sq = kTileCosts[0];
+      const TileCost& sq = square_cost(K);
       const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
       const float last = g.second == GemmPlan::kLdsSuperHalves ? 0.55f : sq.last;
       const float rounds = tail ? (float)(tiles / n_cu) + last : rounds_of(tiles, n_cu, sq.last, sq.lone);
