@@ -259,7 +259,7 @@ __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], cons
     if (pieces) {
       constexpr uint32_t kLanes = FN * 4u, kRows = 64u / kLanes;
       const uint32_t c = lane % kLanes * 8u;
-#pragma unroll 1
+#pragma unroll 2
       for (uint32_t row = lane / kLanes; row < rows; row += kRows) {
         const uint8_t* src = stage + row * kPitch + c * E;
         uint16_t* dst = y0 + (size_t)row * p.ldy + c;
@@ -273,7 +273,7 @@ __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], cons
       constexpr uint32_t kLanes = FN * 16u < 64u ? FN * 16u : 64u, kRows = 64u / kLanes;
       const uint32_t c = lane % kLanes * 2u;
       static_assert(kLanes * 2u == FN * 32u, "a wave covers whole rows");
-#pragma unroll 1
+#pragma unroll 4
       for (uint32_t row = lane / kLanes; row < rows; row += kRows) {
         const uint32_t v = *reinterpret_cast<const uint32_t*>(stage + row * kPitch + c * E);
         uint16_t* dst = y0 + (size_t)row * p.ldy + c;
