@@ -218,7 +218,8 @@ __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], cons
   }
   // Blocks past M or N, of several segments, or in outputs whose rows allow no
   // 16-byte stores: staged the same way, with a scale per column, and stored in
-  // pieces of 16 or 4 bytes (2 where a pair is not aligned or reaches past N).
+  // pieces of 16, 8 or 4 bytes as the rows allow (a wave's store takes 16 cycles
+  // whatever its width: 5 us more per 256 x 256 tile with 8 bytes, 11 with 4).
   // Element by element from the accumulators (64 lanes on 32 rows, a store per
   // element) such a block took 20 to 30 us, most of a short-K call: 8000 x 1300 x
   // 128 48.2 us on 256 x 256 tiles and 46.7 on 128 x 128, with this 16.6.
@@ -228,7 +229,7 @@ __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], cons
 #pragma unroll
   for (uint32_t c = 0; c < FN * 32u; c += 64)
     scale[c + lane] = c + lane < cols ? segment_scale(a_g, w_g, segment_of(p, n0 + c + lane)) : 0.0f;
-  const bool pieces = ((p.ldy * 2u) & 15u) == 0 && (reinterpret_cast<uintptr_t>(y) & 15u) == 0;
+  const uint32_t align = (p.ldy * E | (uint32_t)reinterpret_cast<uintptr_t>(y)) & 15u;   // of the rows, 0: 16 bytes
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
   for (int fa = 0; fa < FM; ++fa) {
@@ -256,35 +257,34 @@ __device__ __forceinline__ void store_tile_t(const floatx16 (&acc)[FM][FN], cons
       }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     uint16_t* y0 = static_cast<uint16_t*>(y) + (size_t)row0 * p.ldy + n0;
-    if (pieces) {
-      constexpr uint32_t kLanes = FN * 4u, kRows = 64u / kLanes;
-      const uint32_t c = lane % kLanes * 8u;
-#pragma unroll 2
+    // Pieces of `bytes`; what reaches past N, and pieces that rows don't align,
+    // element by element.
+    auto store = [&](auto bytes_tag, bool aligned) {
+      constexpr uint32_t kBytes = decltype(bytes_tag)::value, kElems = kBytes / E;
+      typedef uint32_t piece __attribute__((ext_vector_type(kBytes / 4)));
+      constexpr uint32_t kLanes = FN * 32u / kElems, kRows = 64u / kLanes;
+      const uint32_t c = lane % kLanes * kElems;
+#pragma unroll 4
       for (uint32_t row = lane / kLanes; row < rows; row += kRows) {
         const uint8_t* src = stage + row * kPitch + c * E;
         uint16_t* dst = y0 + (size_t)row * p.ldy + c;
-        if (c + 8u <= cols) {
-          *reinterpret_cast<int4v*>(dst) = *reinterpret_cast<const int4v*>(src);
-        } else {
-          for (uint32_t i = 0; c + i < cols; ++i) dst[i] = reinterpret_cast<const uint16_t*>(src)[i];
-        }
-      }
-    } else {
-      constexpr uint32_t kLanes = FN * 16u < 64u ? FN * 16u : 64u, kRows = 64u / kLanes;
-      const uint32_t c = lane % kLanes * 2u;
-      static_assert(kLanes * 2u == FN * 32u, "a wave covers whole rows");
-#pragma unroll 4
-      for (uint32_t row = lane / kLanes; row < rows; row += kRows) {
-        const uint32_t v = *reinterpret_cast<const uint32_t*>(stage + row * kPitch + c * E);
-        uint16_t* dst = y0 + (size_t)row * p.ldy + c;
-        if (p.y_pairs && c + 2u <= cols) {
-          *reinterpret_cast<uint32_t*>(dst) = v;
-        } else {
+        if (aligned && c + kElems <= cols) {
+          *reinterpret_cast<piece*>(dst) = *reinterpret_cast<const piece*>(src);
+        } else if constexpr (kElems == 2) {
+          const uint32_t v = *reinterpret_cast<const uint32_t*>(src);
           if (c < cols) dst[0] = (uint16_t)v;
           if (c + 1u < cols) dst[1] = (uint16_t)(v >> 16);
+        } else {
+          for (uint32_t i = 0; i < kElems && c + i < cols; ++i) dst[i] = reinterpret_cast<const uint16_t*>(src)[i];
         }
       }
-    }
+    };
+    if (align == 0)
+      store(std::integral_constant<uint32_t, 16>{}, true);
+    else if ((align & 7u) == 0)
+      store(std::integral_constant<uint32_t, 8>{}, true);
+    else
+      store(std::integral_constant<uint32_t, 4>{}, (align & 3u) == 0);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
