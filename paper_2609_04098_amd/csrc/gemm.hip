@@ -237,6 +237,20 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
   return g;
 }
 
+// K % 64 != 0 with a workspace: the shapes that stay on the register path.  It
+// has no pass over the activation in front (2 us and a launch) and 256 x 256 tiles
+// of 2 us per chunk; rows that allow no 16-byte stores it stores as fast as the
+// tiled kernels.  It wins where the latter have to store such rows (bf16) of a
+// whole round of tiles and K is short.  Register path and padded: 8000 x 1300 (192
+// tiles) K = 16 13.5 and 15.8 us, 144 17.7 and 18.5, 528 29.5 and 31.8, 784 38 and
+// 39; 8000 x 4004 x 208 36.1 and 43; 8000 x 2601 x 80 35.6 and 41.6; but 1500 x 1300
+// x 16 (36 tiles) 13.2 and 9.0, and with 16-byte stores 3000 x 4000 x 144 17.7 and
+// 14.
+static bool keeps_register_path(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool wide_stores) {
+  const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * (uint64_t)((N + kSquareTile - 1) / kSquareTile);
+  return K % 64 != 0 && !wide_stores && K <= 9 * 64 && 5 * tiles >= 3 * (uint64_t)n_cu;
+}
+
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N) {
   const size_t pad = g.k_pad ? pad_bytes(M, g.k_pad) : 0;
   if (g.second == GemmPlan::kLdsSuperHalves)
@@ -311,7 +325,8 @@ static const char* narrow_kernel_name(int fragments) {
 const char* gemm_kernel_for(int64_t M, int64_t N, int64_t K, int part, bool with_ws) {
   const uint32_t n_cu = cu_count();
   if (n_cu == 0) return nullptr;
-  const GemmPlan g = plan_gemm(M, N, K, n_cu, with_ws);
+  // For bf16 rows of N columns.
+  const GemmPlan g = plan_gemm(M, N, K, n_cu, with_ws && !keeps_register_path(M, N, K, n_cu, N % 8 == 0));
   if (g.k_pad) K = g.k_pad;                  // after pad_act_kernel
   const int kind = part == 0 ? g.first : g.second;
   if (kind == GemmPlan::kSplitkDecode) return decode_kernel_name(decode_shape(M, N, K, n_cu));
@@ -364,6 +379,8 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
       if (h.second == GemmPlan::kLdsSuperHalves) g = h;
     }
   }
+  const bool wide_stores = out_f32 || (ldy % 8 == 0 && reinterpret_cast<uintptr_t>(y) % 16 == 0);
+  if (g.k_pad && keeps_register_path(M, N, K, cu_count(), wide_stores)) g = plan_gemm(M, N, K, cu_count(), false);
   float* parts = static_cast<float*>(workspace);
   if (g.k_pad) {
     uint8_t* pc = static_cast<uint8_t*>(workspace);
