@@ -256,7 +256,8 @@ int nvfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
  *     (e.g. 200 x 5120 x 17408), or the last round of its tiles has (e.g. 7000
  *     x 5120 x 17408); at most 128 MB;
  *   - a padded copy of the activation's codes and scales (K % 64 != 0), in
- *     front of either.
+ *     front of either (not used, though counted here, for short K with a bf16 Y
+ *     whose rows allow no 16-byte stores).
  */
 size_t nvfp4_gemm_workspace(int64_t M, int64_t N, int64_t K);
 

@@ -75,7 +75,13 @@ constexpr int64_t kShortK = 2048;
 // The square tile at K <= kShortK.
 constexpr TileCost kSquareShort = {GemmPlan::kLdsSquare, GemmPlan::kLdsSuper, 256, 256, 1.65f, 1.55f, 9.0f, 0.0f, 0.75f, 0.72f, 32};
 
-static const TileCost& square_cost(int64_t K) { return K <= kShortK ? kSquareShort : kTileCosts[0]; }
+// Where the costs of short K hold.  Rows that are no multiple of 16 bytes are
+// stored in narrower pieces, which costs the tiled kernels' staged stores 2 us a
+// tile and more but not the split-K tiles': with N % 8 != 0 their rounds go without
+// the extra cost (bf16, 1024 x 2601 x 1024 12.0 us on split-K tiles, 17.6 on 128 x
+// 128; 777 x 1998 x 128 6.9 and 9.2).
+static bool short_k(int64_t N, int64_t K) { return K <= kShortK && N % 8 == 0; }
+static const TileCost& square_cost(int64_t N, int64_t K) { return short_k(N, K) ? kSquareShort : kTileCosts[0]; }
 // The summing pass: a launch, and every partial sum written and read once
 // (they stay in the last-level cache).
 constexpr float kSumLaunchUs = 2.5f, kPartBytesPerUs = 6.0e6f;
@@ -107,11 +113,14 @@ constexpr float kPlanGain = 0.96f;
 static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws, float* cost) {
   const bool super = K % 256 == 0;
   const uint32_t unit = super ? 4 : 1, units = (uint32_t)(K / 64) / unit;
-  GemmPlan best{};
+  // Among the split-K tiles the plain costs decide, which fit their order; their
+  // extra cost per round (TileCost::round_us) counts against the tiled kernels.
+  GemmPlan best{}, best_splitk{};
+  float splitk_cost = 0.0f, splitk_round_cost = 0.0f;
   *cost = 0.0f;
   for (const TileCost& row : kTileCosts) {
     const bool square = row.kind == GemmPlan::kLdsSquare;
-    const TileCost& t = square ? square_cost(K) : row;
+    const TileCost& t = square ? square_cost(N, K) : row;
     const uint64_t tiles = (uint64_t)((M + t.bm - 1) / t.bm) * (uint64_t)((N + t.bn - 1) / t.bn);
     const bool splitk = t.kind == t.super_kind;
     const uint64_t max_rounds = K < 1024 ? kSplitkMaxRoundsShort : kSplitkMaxRounds;
@@ -126,16 +135,22 @@ static GemmPlan plan_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool 
       const uint32_t chunks = (units + parts - 1) / parts * unit + (t.kind == GemmPlan::kSplitk32x96 ? 42 : 0);
       const float rounds = rounds_of(tiles * parts, n_cu, t.last, t.lone);
       float c = rounds * (float)chunks * (super ? t.chunk_us_super : t.chunk_us) + t.fixed_us;
-      if (K < kShortK && rounds > 1.0f) {
-        const float fade = 2.0f - 2.0f * (float)K / (float)kShortK;      // from kShortK / 2 on
-        c += (rounds - 1.0f) * (fade < 1.0f ? fade : 1.0f) * t.round_us;
-      }
       if (parts > 1) c += kSumLaunchUs + 2.0f * (float)part_bytes / kPartBytesPerUs;
-      if (best.first == GemmPlan::kNone || c < *cost) {
-        best.first = super ? t.super_kind : t.kind;
-        best.k_parts = parts;
-        *cost = c;
-      }
+      GemmPlan& b = splitk ? best_splitk : best;
+      float& b_cost = splitk ? splitk_cost : *cost;
+      if (b.first != GemmPlan::kNone && c >= b_cost) continue;
+      b.first = super ? t.super_kind : t.kind;
+      b.k_parts = parts;
+      b_cost = c;
+      if (splitk) splitk_round_cost = rounds > 1.0f ? (rounds - 1.0f) * t.round_us : 0.0f;
+    }
+  }
+  if (best_splitk.first != GemmPlan::kNone) {
+    const float fade = 2.0f - 2.0f * (float)K / (float)kShortK;      // from kShortK / 2 on
+    if (short_k(N, K)) splitk_cost += (fade < 1.0f ? fade : 1.0f) * splitk_round_cost;
+    if (splitk_cost < *cost) {
+      best = best_splitk;
+      *cost = splitk_cost;
     }
   }
   best.n_split = (uint32_t)N;
@@ -170,7 +185,7 @@ static GemmPlan plan_square(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool
 // then a summing pass.  K % 256 == 0.
 static GemmPlan plan_square_tiles(int64_t M, int64_t N, int64_t K, uint32_t n_cu, float* cost) {
   GemmPlan best{};
-  const TileCost& sq = square_cost(K);
+  const TileCost& sq = square_cost(N, K);
   const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
   const uint64_t rem = tiles % n_cu;
   const uint32_t units = (uint32_t)(K / 256);
@@ -212,7 +227,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
     g = plan_square(M, N, K, n_cu, with_ws);
     const bool tail = g.second != GemmPlan::kNone;
     if (n_cu != 0 && (!tail || K >= kTailMinK)) {
-      const TileCost& sq = square_cost(K);
+      const TileCost& sq = square_cost(N, K);
       const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * ((N + kSquareTile - 1) / kSquareTile);
       const float last = g.second == GemmPlan::kLdsSuperHalves ? 0.55f : sq.last;
       const float rounds = tail ? (float)(tiles / n_cu) + last : rounds_of(tiles, n_cu, sq.last, sq.lone);
@@ -240,15 +255,19 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool with_ws)
 // K % 64 != 0 with a workspace: the shapes that stay on the register path.  It
 // has no pass over the activation in front (2 us and a launch) and 256 x 256 tiles
 // of 2 us per chunk; rows that allow no 16-byte stores it stores as fast as the
-// tiled kernels.  It wins where the latter have to store such rows (bf16) of a
-// whole round of tiles and K is short.  Register path and padded: 8000 x 1300 (192
-// tiles) K = 16 13.5 and 15.8 us, 144 17.7 and 18.5, 528 29.5 and 31.8, 784 38 and
-// 39; 8000 x 4004 x 208 36.1 and 43; 8000 x 2601 x 80 35.6 and 41.6; but 1500 x 1300
-// x 16 (36 tiles) 13.2 and 9.0, and with 16-byte stores 3000 x 4000 x 144 17.7 and
-// 14.
+// tiled kernels.  It wins where the latter have to store such rows (bf16) of half
+// a round of tiles or more and K is short, or of 0.4 of one up to three chunks, or
+// of a quarter up to two.  Register path and padded: 8000 x 1300 (192 tiles) K = 16
+// 13.5 and 15.8 us, 144 17.7 and 18.5, 528 29.5 and 31.8, 784 38 and 39; 8000 x
+// 4004 x 208 36.1 and 43; 2200 x 3998 (144 tiles) x 336 21.9 and 31.3; 2200 x 3004
+// (108) x 144 16.5 and 19.9; 1500 x 4004 (96 tiles) x 112 16.7 and 19, x 144 18.1
+// and 16.9; 777 x 4004 (64) x 48 12.3 and 13.5; but 1500 x 1300 (36) x 16 13.2 and
+// 9.0, and with 16-byte stores 3000 x 4000 x 144 17.7 and 14.
 static bool keeps_register_path(int64_t M, int64_t N, int64_t K, uint32_t n_cu, bool wide_stores) {
   const uint64_t tiles = (uint64_t)((M + kSquareTile - 1) / kSquareTile) * (uint64_t)((N + kSquareTile - 1) / kSquareTile);
-  return K % 64 != 0 && !wide_stores && K <= 9 * 64 && 5 * tiles >= 3 * (uint64_t)n_cu;
+  if (K % 64 == 0 || wide_stores) return false;
+  const uint64_t n = n_cu;
+  return (K <= 9 * 64 && 2 * tiles >= n) || (K <= 3 * 64 && 5 * tiles >= 2 * n) || (K <= 2 * 64 && 4 * tiles >= n);
 }
 
 size_t plan_workspace_bytes(const GemmPlan& g, int64_t M, int64_t N) {

@@ -49,9 +49,9 @@
 //    ring shared by 4 waves; the partial sums meet in LDS.
 //  * gemm_rows16_kernel (at most 16 rows): the same with per-wave rings and 16 x
 //    16 x 32 products.
-//  * gemm_reg_kernel (K % 64 != 0 without a workspace): operands go straight
-//    from global memory to registers one chunk ahead; per-block masking of the
-//    scales handles a K tail.
+//  * gemm_reg_kernel (K % 64 != 0 without a workspace, and with one the shapes
+//    of keeps_register_path): operands go straight from global memory to
+//    registers one chunk ahead; per-block masking of the scales handles a K tail.
 // All remap workgroups so that each XCD (its own L2) runs a contiguous,
 // M-grouped range of tiles; out-of-range rows/columns read zeros through the
 // buffer bounds and are not stored.

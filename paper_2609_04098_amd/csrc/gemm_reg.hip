@@ -1,4 +1,4 @@
-// Register-path NVFP4 GEMM (K % 64 != 0 without a workspace): operands go
+// Register-path NVFP4 GEMM (K % 64 != 0, see plan_gemm): operands go
 // global -> registers one chunk ahead; per-block masking of the scales handles
 // a K tail.  With a workspace the activation is padded instead (pad_act_kernel)
 // and the 64-aligned kernels run.
@@ -139,8 +139,8 @@ static hipError_t launch_reg(const GemmOperands& o, GemmParams p, bool out_f32, 
 // elements: one thread per 16-element block, 8 bytes of codes and the scale
 // (zero past K, so whatever the codes there, the products are zero).  The
 // 64-aligned kernels on the padded copy replace the register path wherever
-// there is a workspace: 777 x 1300 x 1040 53 us on the register path's 24
-// tiles.
+// there is a workspace, but for the shapes of keeps_register_path: 777 x 1300 x
+// 1040 53 us on the register path's 24 tiles.
 __global__ __launch_bounds__(256) void pad_act_kernel(const uint2* __restrict__ codes,
                                                       const uint8_t* __restrict__ scales, uint32_t n_blocks,
                                                       uint32_t bpr, uint32_t bpr_pad, uint2* __restrict__ pad_codes,

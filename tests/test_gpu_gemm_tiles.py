@@ -190,25 +190,29 @@ def test_short_k_keeps_off_many_rounds_of_small_tiles(m, n, k):
         assert "gemm_lds_kernel" in L.gemm_kernels(m, n, k, ws)[0]
 
 
-@pytest.mark.parametrize("n", [1300, 1304])
-def test_k_remainder_with_a_workspace(n):
-    """K % 64 != 0, short, over a round of tiles: rows that allow no 16-byte
-    stores stay on the register path also with a workspace, the others and FP32
-    outputs run on the padded copy (each bf16 output is RNE of its own path's FP32
-    sums)."""
-    m, k = 6500, 208
+@pytest.mark.parametrize("m,n,k,kept", [
+    (6500, 1300, 208, True),               # half a round of tiles or more
+    (6500, 1304, 208, False),
+    (2200, 3004, 144, True),               # 0.4 of one, three chunks
+    (1500, 4004, 112, True),               # a quarter, two chunks
+    (1500, 4004, 144, False),
+])
+def test_k_remainder_with_a_workspace(m, n, k, kept):
+    """K % 64 != 0, short, many tiles: rows that allow no 16-byte stores stay
+    on the register path also with a workspace, the others and FP32 outputs run on
+    the padded copy (each bf16 output is RNE of its own path's FP32 sums)."""
     rng = np.random.default_rng(n)
     xb = synth.f64_to_bf16_bits(rng.standard_normal((m, k)))
     wb = synth.f64_to_bf16_bits(rng.standard_normal((n, k)) * 0.02)
     aq, pw = L.quantize_act(to_dev_bf16(xb)), L.pack_weight(to_dev_bf16(wb))
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert ("gemm_reg" in L.gemm_kernels(m, n, k)[0]) == (n == 1300)
+        assert ("gemm_reg" in L.gemm_kernels(m, n, k)[0]) == kept
     y32, n32 = L.gemm(aq, pw, out_dtype=torch.float32), L.gemm_no_workspace(aq, pw, out_dtype=torch.float32)
-    # 208 exact products: sums in two orders differ by at most 2 * 208 * 2^-24 of
-    # the sum of magnitudes, here below 208 * |x| |w| of the largest.
+    # k exact products: sums in two orders differ by at most 2 k 2^-24 of the sum
+    # of magnitudes, here below k |x| |w| of the largest.
     bound = 2.0 * k * 2.0 ** -24 * k * 6.0 * 0.12
     assert float((y32 - n32).abs().max()) <= bound
     y16, n16 = L.gemm(aq, pw), L.gemm_no_workspace(aq, pw)
     assert torch.equal(n16.view(torch.int16), n32.to(torch.bfloat16).view(torch.int16))
-    want = n32 if n == 1300 else y32
+    want = n32 if kept else y32
     assert torch.equal(y16.view(torch.int16), want.to(torch.bfloat16).view(torch.int16))
