@@ -385,6 +385,7 @@ hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f3
   return gate ? launch_narrow<true>(o, p, out_f32, stream) : launch_narrow<false>(o, p, out_f32, stream);
 }
 
+constexpr int64_t kRowsMaxElems = 12 * 16384;
 // Decode shapes (M <= 32).  The order of an output column's sum follows from
 // the number of waves that share it, so the fused quantize + GEMM launch
 // (M * K <= 16 * kDecodeFuseMaxBlocks) takes the same form as the plain one.
@@ -393,11 +394,16 @@ hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f3
 //    waves (1 x 8192 x 5120 fused 9.1 us with 8-wave 32 x 32 tiles, 7.7 with
 //    this; 4 x 5120 x 17408 18.8 with 16-wave 32 x 32 tiles, 16.1).  More: 8
 //    waves and two tiles (1 x 8704 x 5120 fused 13.1 -> 10.1), three while that
-//    makes no more workgroups than CUs, and for the fused launch (every
-//    workgroup quantizes X) beyond: 1 x 17408 x 5120 fused 19.1 -> 13.5, 16 x
-//    17408 x 5120 18.2 -> 14.0, 1 x 34816 x 5120 fused 27.4 -> 22.7 (23.8 with
-//    4 waves and two tiles).  Else 4 waves and two tiles (4 and 16 x 34816 x
-//    5120 25.1 -> 22.0 and 28.6 -> 24.3; 23.9 and 26.1 with 8 waves and three).
+//    makes no more workgroups than CUs (1 x 17408 x 5120 fused 19.1 -> 13.5, 16 x
+//    17408 x 5120 18.2 -> 14.0).  Beyond, by how full the last round of workgroups
+//    is: up to four tiles per CU 8 waves and two (two full rounds; 1 x 24600 x 5120
+//    18.1 us, 21.9 with 4 waves and two), up to six 4 waves and two, or where every
+//    workgroup quantizes X (the fused launch) 8 waves and three (4 and 16 x 34816
+//    x 5120 25.1 -> 22.0 and 28.6 -> 24.3; 1 x 34816 x 5120 fused 27.4 -> 22.7, 23.8
+//    with 4 waves and two), more again 8 waves and two (1 x 50000 x 17408 96 us; 124
+//    with 4 waves and two).  With more X than kRowsMaxElems the 8-wave forms
+//    load it more slowly than the 32-row tiles of 4 waves (16 x 24600 x 17408 55
+//    us on those).
 //  * 17 to 32 rows, at most one tile per CU: 4 waves with per-wave rings
 //    (32 x 8192 x 5120: two tiles per workgroup and a shared activation ring
 //    13.7 us, this 9.7), for long K 8 waves with a shared ring (32 x 5120 x
@@ -407,19 +413,22 @@ hipError_t launch_splitk_narrow(const GemmOperands& o, GemmParams p, bool out_f3
 //    activation's decode and loads are shared by them (32 x 17408 x 5120, 8
 //    waves and three tiles: 15.1 us against 16.6 with 4 waves and three and
 //    18.1 with two; 32 x 34816 x 5120, 4 waves and five tiles: 22.3 against 25.8
-//    with three and 26.2 with two).
+//    with three and 26.2 with two).  Up to four tiles per CU two tiles make two
+//    full rounds (17 x 24600 x 17408 53.3 us; 59.1 with five).
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
   const uint64_t tiles = (uint64_t)((N + 31) / 32);
   if (M <= 16) {
     if (tiles <= n_cu) return DecodeShape::kRows16w1;
     if (5 * tiles < 9 * (uint64_t)n_cu) return DecodeShape::kRows8w2;        // three: under 0.6 of the CUs
-    if (tiles <= 3 * (uint64_t)n_cu || M * K <= 16 * (int64_t)kDecodeFuseMaxBlocks) return DecodeShape::kRows8w3;
-    return DecodeShape::kRows4w2;
+    if (tiles <= 3 * (uint64_t)n_cu) return DecodeShape::kRows8w3;
+    if (tiles <= 4 * (uint64_t)n_cu || tiles > 6 * (uint64_t)n_cu)
+      return M * K > kRowsMaxElems ? DecodeShape::k4SharedPair : DecodeShape::kRows8w2;
+    return M * K <= 16 * (int64_t)kDecodeFuseMaxBlocks ? DecodeShape::kRows8w3 : DecodeShape::kRows4w2;
   }
   if (tiles <= n_cu) return K >= 8192 ? DecodeShape::k8Shared : DecodeShape::k4Private;
   if (5 * tiles < 9 * (uint64_t)n_cu) return DecodeShape::k8SharedPair;
   if (tiles <= 3 * (uint64_t)n_cu) return DecodeShape::k8Shared3;
-  return tiles <= 5 * (uint64_t)n_cu ? DecodeShape::k4Shared5 : DecodeShape::k4SharedPair;
+  return tiles > 4 * (uint64_t)n_cu && tiles <= 5 * (uint64_t)n_cu ? DecodeShape::k4Shared5 : DecodeShape::k4SharedPair;
 }
 
 hipError_t launch_splitk_decode(const GemmOperands& o, GemmParams p, bool out_f32, hipStream_t stream) {

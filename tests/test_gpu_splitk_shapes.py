@@ -53,13 +53,18 @@ def _check(m, n, k, offs):
     (2, 14720, 320, [0, 14720]),           # 460 tiles: the most in twos, 5 chunks over 8 waves, one launch
     (9, 14721, 320, [0, 9999, 14721]),     # 461 tiles: the fewest in threes
     (16, 24576, 1088, [0, 24576]),         # 768 tiles: a workgroup of three per CU
-    (16, 24577, 1088, [0, 24577]),         # one more: two tiles for 4 waves
-    (15, 24609, 1088, [0, 24609]),         # ... and at the one-launch limit (M K = 16320): three for 8 waves
+    (16, 24577, 1088, [0, 24577]),         # one more: two tiles for 8 waves
+    (15, 24609, 1088, [0, 24609]),         # ... and at the one-launch limit (M K = 16320)
+    (16, 32769, 1088, [0, 9999, 32769]),   # past four per CU: two tiles for 4 waves
+    (15, 32800, 1088, [0, 32800]),         # ... in one launch three tiles for 8 waves
+    (2, 49153, 320, [0, 49153]),           # past six per CU: two tiles for 8 waves
     (17, 8193, 512, [0, 8193]),            # one tile past one per CU: two tiles for 8 waves, one launch
     (17, 14720, 1024, [0, 14720]),         # the most in twos
     (32, 14721, 192, [0, 9999, 14721]),    # the fewest in threes, 3 chunks over 8 waves
-    (18, 24577, 576, [0, 24577]),          # five tiles for 4 waves, one launch, ragged N
+    (18, 24577, 576, [0, 24577]),          # two tiles for 4 waves, one launch, ragged N
     (32, 24700, 1088, [0, 24700]),
+    (18, 32769, 576, [0, 32769]),          # past four tiles per CU: five tiles for 4 waves
+    (32, 32900, 320, [0, 30000, 32900]),
     (17, 40961, 128, [0, 40961]),          # past five tiles per CU: two tiles for 4 waves
     (1, 160, 8192, [0, 160]),              # long K, one launch
     (8, 170, 8256, [0, 85, 170]),          # long K: 129 chunks over 16 waves
@@ -68,6 +73,32 @@ def _check(m, n, k, offs):
 ])
 def test_decode_shapes(m, n, k, offs):
     _check(m, n, k, offs)
+
+
+@pytest.mark.parametrize("k,name", [
+    (12224, "gemm_rows16_kernel<8,2,2>"),  # M K = 195584
+    (12352, "gemm_splitk_kernel<4,1,2,3>"),  # 197632: 32-row tiles of 4 waves
+])
+def test_decode_shapes_wide_output_and_long_k(k, name):
+    """On either side of the length of X from which 32-row tiles are taken; Y at
+    a sample of the columns, the last ones among them."""
+    m, n = 16, 24579
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    w = torch.randn(n, k, generator=gen, device="cuda", dtype=torch.bfloat16) * 0.02
+    xb = _inputs(m, 16, k)[0]
+    pw = L.pack_weight(w)
+    cols = np.unique(np.concatenate([np.random.default_rng(k).choice(n, 90, replace=False), np.arange(n - 6, n)]))
+    wb = w[torch.from_numpy(cols).cuda()].view(torch.int16).cpu().numpy().view(np.uint16)
+    del w
+    y32, y16 = (L.gemm(L.quantize_act(to_dev_bf16(xb)), pw, out_dtype=t) for t in (torch.float32, torch.bfloat16))
+    xp, xs, gx = OQ.quantize_tensor(xb)
+    gw = pw.g_seg.cpu().numpy()
+    wp, ws, _ = OQ.quantize_tensor(wb, g=gw[0])
+    args = (xp, xs, gx, wp, ws, gw, [0, len(cols)])
+    check_gemm(y32.cpu().numpy().astype(np.float64)[:, cols], OG.gemm_f64(*args), OG.abs_bound(*args), "k=%d" % k)
+    np.testing.assert_array_equal(y16.view(torch.int16).cpu().numpy().view(np.uint16), bf16_rne_of(y32))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert L.gemm_kernels(m, n, k)[0].startswith(name)
 
 
 @pytest.mark.parametrize("m,n,k,offs", [
