@@ -340,7 +340,8 @@ size_t nvfp4_quantize_gemm_workspace(int64_t M, int64_t N, int64_t K);
  *     workspace.
  * The result equals nvfp4_quantize_act followed by nvfp4_gemm: the same
  * codes, scales and G_A, and the GEMM sums in the same order as nvfp4_gemm
- * at these shapes.
+ * at these shapes, but for M > 32 with 96 < N <= 128, where the two sum the same
+ * products in different orders.
  *
  *   x, M, K, ldx   bf16 activation, as for nvfp4_quantize_act.
  *   a_g_enc        one device float: G_A, written (NVFP4_DYNAMIC) or read

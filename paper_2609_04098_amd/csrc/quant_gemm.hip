@@ -337,6 +337,9 @@ hipError_t launch_quant_gemm(const void* x, int64_t M, int64_t K, int64_t ldx, f
       default: return launch_quant_gemm_fn<4, 2, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);
     }
   }
+  // M <= 32: the waves (and so the order of the sums) of the unfused GEMM's decode_shape.
+  if (M <= 32 && decode_shape(M, N, K, cu_count()) == DecodeShape::k8Shared)
+    return launch_quant_gemm_fn<8, 1, 1>(q, dynamic, wp, w_g, y, p, out_f32, stream);
   return launch_quant_gemm_fn<4, 1, 4>(q, dynamic, wp, w_g, y, p, out_f32, stream);
 }
 

@@ -226,7 +226,8 @@ def quantize_gemm_workspace(m, n, k, device, stream=None):
 def quantize_gemm(x, pw: PackedWeight, g=None, out_dtype=torch.bfloat16, out=None, act_out: QuantizedAct = None,
                   workspace=None, stream=None):
     """Act-quant fused into the GEMM (N <= 128, or M <= 32): y [M, N] equal to
-    gemm(quantize_act(x, g), pw).  Dynamic G unless ``g`` is given; the
+    gemm(quantize_act(x, g), pw) (up to the order of the sums for M > 32 with
+    96 < N <= 128).  Dynamic G unless ``g`` is given; the
     activation codes/scales/G are written to ``act_out`` when it is given.
     Returns (y, G as a device float32 [1])."""
     m, k = x.shape

@@ -75,6 +75,14 @@ def test_decode_shapes(m, n, k, offs):
     _check(m, n, k, offs)
 
 
+# The fused launch at these widths has 4 waves, or 8 from K = 2048 on.
+@pytest.mark.parametrize("k", [64, 1088, 1984, 2048, 5120, 8192])
+@pytest.mark.parametrize("n", [97, 128])
+@pytest.mark.parametrize("m", [1, 16, 17, 32])
+def test_decode_shapes_of_up_to_four_column_tiles(m, n, k):
+    _check(m, n, k, [0, 40, n])
+
+
 @pytest.mark.parametrize("k,name", [
     (12224, "gemm_rows16_kernel<8,2,2>"),  # M K = 195584
     (12352, "gemm_splitk_kernel<4,1,2,3>"),  # 197632: 32-row tiles of 4 waves
