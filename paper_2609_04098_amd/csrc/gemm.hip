@@ -349,7 +349,7 @@ const char* gemm_kernel_for(int64_t M, int64_t N, int64_t K, int part, bool with
   if (g.k_pad) K = g.k_pad;                  // after pad_act_kernel
   const int kind = part == 0 ? g.first : g.second;
   if (kind == GemmPlan::kSplitkDecode) return decode_kernel_name(decode_shape(M, N, K, n_cu));
-  if (kind == GemmPlan::kSplitkNarrow) return narrow_kernel_name(narrow_fragments(M, N, n_cu));
+  if (kind == GemmPlan::kSplitkNarrow) return narrow_kernel_name(narrow_fragments(M, N, K, n_cu, NarrowUse::kProduct));
   return kind == GemmPlan::kNone ? nullptr : gemm_kernel_name(kind, part == 0 && g.k_parts > 1);
 }
 

@@ -470,7 +470,8 @@ enum class DecodeShape { kRows16w1, kRows8w2, kRows8w3, kRows4w2, k4Private, k4S
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu);
 // Tiles of a tall-skinny output (N <= 96): 1..3: 32 rows x that many weight
 // fragments, 8 waves; 4: 32 x 96, 4 waves; 0: 64 x 96, 4 waves.
-int narrow_fragments(int64_t M, int64_t N, uint32_t n_cu);
+enum class NarrowUse { kProduct, kGates, kQuantize };
+int narrow_fragments(int64_t M, int64_t N, int64_t K, uint32_t n_cu, NarrowUse use);
 
 // Launchers of the kernel families (each in its own translation unit).
 // Prefill tiles over output columns [n_begin, n_end) (n_begin a multiple of 32).

@@ -359,20 +359,24 @@ static hipError_t launch_splitk(const GemmOperands& o, GemmParams p, bool out_f3
 // waves share the reduction of a 32-row tile of as few fragments as still
 // give every tile its own CU (gates at N = 96, K = 5120, same box: 1000 rows
 // 33.5 -> 10.4 us, 4000 rows 34.3 -> 14.8, 8000 rows 34.5 -> 20.6 against
-// 64 x 96 tiles of four waves, which keep 16 to 125 CUs busy); up to twice as
-// many rows 32 x 96 tiles of four waves (16000 rows 35.2 -> 31.4 us; fused
-// with the quantizer, 8300 rows 63 -> 49), beyond that 64 x 96 tiles (32768
-// rows: 53.8 us against 77.8 for 32 x 96 of eight waves).
-int narrow_fragments(int64_t M, int64_t N, uint32_t n_cu) {
+// 64 x 96 tiles of four waves, which keep 16 to 125 CUs busy).  Up to twice as
+// many rows 32 x 96 tiles of four waves where a workgroup has more to do than the
+// product: it quantizes X (8300 rows 63 -> 49 us), or computes the gates at the end
+// (16384 x 96 x 5120 33.9 -> 31.6), the latter while K is short (x 17408 71.6
+// against 75.5).  The plain product, and beyond: 64 x 96 tiles (16384 x 96 x 17408
+// 62.5 us and 70.6 with 32 x 96 of four waves; 32768 rows: 53.8 and 77.8 with 32 x
+// 96 of eight).  Four waves either way: the same order of the sums.
+int narrow_fragments(int64_t M, int64_t N, int64_t K, uint32_t n_cu, NarrowUse use) {
   const uint64_t rows = (uint64_t)((M + 31) / 32), frags = (uint64_t)((N + 31) / 32);
   for (uint64_t f = 1; f <= 3; ++f)
     if (rows * ((frags + f - 1) / f) <= n_cu) return (int)f;
-  return rows <= 2 * (uint64_t)n_cu ? 4 : 0;
+  const bool small = use == NarrowUse::kQuantize || (use == NarrowUse::kGates && K <= 8192);
+  return small && rows <= 2 * (uint64_t)n_cu ? 4 : 0;
 }
 
 template <bool kGate>
 static hipError_t launch_narrow(const GemmOperands& o, const GemmParams& p, bool out_f32, hipStream_t stream) {
-  switch (narrow_fragments(p.M, p.N, cu_count())) {
+  switch (narrow_fragments(p.M, p.N, p.K, cu_count(), kGate ? NarrowUse::kGates : NarrowUse::kProduct)) {
     case 1: return launch_splitk<8, 1, 1, 3, true, kGate>(o, p, out_f32, stream);
     case 2: return launch_splitk<8, 1, 2, 3, true, kGate>(o, p, out_f32, stream);
     case 3: return launch_splitk<8, 1, 3, 3, true, kGate>(o, p, out_f32, stream);

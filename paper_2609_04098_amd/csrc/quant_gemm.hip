@@ -328,8 +328,8 @@ hipError_t launch_quant_gemm(const void* x, int64_t M, int64_t K, int64_t ldx, f
     q.n_partial = (uint32_t)n_partial;
   }
   if (N <= 96) {
-    // The tiles (and so the order of the sums) of the unfused GEMM.
-    switch (narrow_fragments(M, N, cu_count())) {
+    // The waves per tile (and so the order of the sums) of the unfused GEMM.
+    switch (narrow_fragments(M, N, K, cu_count(), NarrowUse::kQuantize)) {
       case 1: return launch_quant_gemm_fn<8, 1, 1>(q, dynamic, wp, w_g, y, p, out_f32, stream);
       case 2: return launch_quant_gemm_fn<8, 1, 2>(q, dynamic, wp, w_g, y, p, out_f32, stream);
       case 3: return launch_quant_gemm_fn<8, 1, 3>(q, dynamic, wp, w_g, y, p, out_f32, stream);

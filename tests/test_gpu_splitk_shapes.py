@@ -116,17 +116,21 @@ def test_decode_shapes_wide_output_and_long_k(k, name):
     (2721, 90, 192, [0, 30, 90]),          # 86 x 3 tiles would not fit the CUs: two fragments
     (4097, 96, 128, [0, 48, 96]),          # three fragments
     (8192, 96, 64, [0, 48, 96]),           # one tile per CU
-    (8193, 96, 192, [0, 48, 96]),          # two 32 x 96 tiles of 4 waves per CU
+    (8193, 96, 192, [0, 48, 96]),          # 64 x 96 tiles; fused, two 32 x 96 tiles of 4 waves per CU
     (16384, 90, 64, [0, 90]),
-    (16385, 90, 64, [0, 90]),              # 64 x 96 tiles
+    (16385, 90, 64, [0, 90]),              # 64 x 96 tiles for both
 ])
 def test_narrow_shapes(m, n, k, offs):
     _check(m, n, k, offs)
 
 
-@pytest.mark.parametrize("m", [1, 70, 3000, 6000])
-def test_gate_epilogue_shapes(m):
-    h, k = 48, 576
+@pytest.mark.parametrize("m,k", [
+    (1, 576), (70, 576), (3000, 576), (6000, 576),
+    (8200, 576),                           # two 32 x 96 tiles of 4 waves per CU
+    (8200, 8256),                          # ... up to K = 8192
+])
+def test_gate_epilogue_shapes(m, k):
+    h = 48
     xb, wb = _inputs(m, 2 * h, k)
     rng = np.random.default_rng(m)
     a_log, dt = np.log(rng.uniform(1, 16, h)).astype(np.float32), rng.uniform(-4, 2, h).astype(np.float32)
