@@ -182,6 +182,36 @@ constexpr int kSmallThreads = 1024;
 constexpr int kSmallLoads = 4;           // 16-byte loads in flight per thread
 constexpr uint32_t kSmallMaxBlocks = 8192;
 
+// 16-byte vectors first, first + kSmallThreads, ... of X (past the end: vector 0
+// again).  Strided rows: row and column are carried along, two divisions for
+// the walk instead of one per vector (4 x 5120, ldx = 2 K: 5.0 us with those, 4.2).
+template <bool kContig>
+struct SmallWalk {
+  const uint16_t* x;
+  uint32_t v, n_vec, vec_per_row, ldx, row, col, d_row, d_col;
+  __device__ __forceinline__ SmallWalk(const uint16_t* x_, uint32_t first, uint32_t n_vec_, uint32_t vec_per_row_,
+                                       uint32_t ldx_)
+      : x(x_), v(first), n_vec(n_vec_), vec_per_row(vec_per_row_), ldx(ldx_), row(0), col(0), d_row(0), d_col(0) {
+    if (kContig) return;
+    row = first / vec_per_row, col = first - row * vec_per_row;
+    d_row = (uint32_t)kSmallThreads / vec_per_row, d_col = (uint32_t)kSmallThreads - d_row * vec_per_row;
+  }
+  __device__ __forceinline__ const uint4* next() {
+    const uint4* p;
+    if (kContig) {
+      p = reinterpret_cast<const uint4*>(x) + (v < n_vec ? v : 0);
+    } else {
+      const bool in = v < n_vec;
+      p = reinterpret_cast<const uint4*>(x + (size_t)(in ? row : 0) * ldx) + (in ? col : 0);
+      row += d_row;
+      col += d_col;
+      if (col >= vec_per_row) col -= vec_per_row, row += 1;
+    }
+    v += kSmallThreads;
+    return p;
+  }
+};
+
 template <bool kDynamic, bool kContig>
 __global__ __launch_bounds__(kSmallThreads) void act_quant_small_kernel(
     const uint16_t* __restrict__ x, uint32_t n_blocks, uint32_t blocks_per_row, uint32_t ldx,
@@ -189,8 +219,8 @@ __global__ __launch_bounds__(kSmallThreads) void act_quant_small_kernel(
   __shared__ uint32_t lds[kSmallThreads / 64];
   const uint32_t b = blockIdx.x * kSmallThreads + threadIdx.x;
   const uint32_t bq = b < n_blocks ? b : n_blocks - 1;
-  const uint4 d0 = *vec_ptr<kContig>(x, 2 * bq, 2 * blocks_per_row, ldx);
-  const uint4 d1 = *vec_ptr<kContig>(x, 2 * bq + 1, 2 * blocks_per_row, ldx);
+  const uint4* src = block_ptr<kContig>(x, bq, blocks_per_row, ldx);
+  const uint4 d0 = src[0], d1 = src[1];
   float g;
   if (kDynamic) {
     typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
@@ -202,14 +232,12 @@ __global__ __launch_bounds__(kSmallThreads) void act_quant_small_kernel(
     };
     // The thread's own block; in a single workgroup these are all of X.
     u16x2 mp = amax(amax(u16x2{0, 0}, d0), d1);
-    const uint32_t n_vec = gridDim.x == 1 ? 0 : 2 * n_blocks;
+    const uint32_t n_vec = gridDim.x == 1 ? 0 : 2 * n_blocks, vec_per_row = 2 * blocks_per_row;
+    SmallWalk<kContig> at(x, threadIdx.x, n_vec, vec_per_row, ldx);
     for (uint32_t v = threadIdx.x; v < n_vec; v += kSmallLoads * kSmallThreads) {
       uint4 d[kSmallLoads];
 #pragma unroll
-      for (int u = 0; u < kSmallLoads; ++u) {
-        const uint32_t vu = v + u * kSmallThreads;             // past the end: the last vector again
-        d[u] = *vec_ptr<kContig>(x, vu < n_vec ? vu : n_vec - 1, 2 * blocks_per_row, ldx);
-      }
+      for (int u = 0; u < kSmallLoads; ++u) d[u] = *at.next();
 #pragma unroll
       for (int u = 0; u < kSmallLoads; ++u) mp = amax(mp, d[u]);
     }

@@ -147,6 +147,9 @@ def test_gate_epilogue_shapes(m, k):
     (1, 16, None),                          # one block
     (64, 256, None),                        # 1024 blocks: one workgroup, its own blocks are all of X
     (41, 400, 416),                         # 1025 blocks, strided rows: two workgroups
+    (600, 32, 40),                          # strided: a step of the walk is whole rows
+    (3, 17408, 17424),                      # ... less than a row
+    (100, 1040, 1056),                      # ... and rows and a part, seven workgroups
     (32, 4096, None),                       # 8192 blocks: the largest one-launch activation
     (8193, 16, 24),                         # 8193 blocks: two launches
 ])
