@@ -111,7 +111,7 @@ __device__ __forceinline__ const uint4* block_ptr(const uint16_t* x, uint32_t b,
 // amax pass, so as to meet the most recently read part of X in the MALL,
 // measured 2% slower on a 335 MB activation and is not done.)
 // d0, d1: the thread's first block.
-template <bool kContig, bool kExact>
+template <bool kContig, QuantForm kForm>
 __device__ __forceinline__ void quantize_blocks(const uint16_t* __restrict__ x, uint32_t n_blocks,
                                                 uint32_t blocks_per_row, uint32_t ldx,
                                                 uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
@@ -128,7 +128,7 @@ __device__ __forceinline__ void quantize_blocks(const uint16_t* __restrict__ x, 
     }
     const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
     uint32_t c0, c1;
-    const uint32_t sc = quantize_block_as<kExact>(v, g, gd6, gf4, c0, c1);
+    const uint32_t sc = quantize_block_as<kForm>(v, g, gd6, gf4, c0, c1);
     reinterpret_cast<uint2*>(codes)[b] = make_uint2(c0, c1);
     scales[b] = (uint8_t)sc;
     d0 = e0;
@@ -161,10 +161,10 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(
   }
   // The form is chosen per tensor, uniformly across the launch.
   const QuantMode q = quant_mode(g);
-  if (q.exact)
-    quantize_blocks<kContig, true>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.0f, d0, d1);
-  else
-    quantize_blocks<kContig, false>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.25f * q.gf, d0, d1);
+  with_quant_form(q, [&](auto form) {
+    quantize_blocks<kContig, decltype(form)::value>(x, n_blocks, blocks_per_row, ldx, codes, scales, g, 0.25f * q.gf,
+                                                    d0, d1);
+  });
 }
 
 __global__ void write_zero_scale_kernel(float* g_enc) { *g_enc = 0.0f; }
@@ -257,10 +257,9 @@ __global__ __launch_bounds__(kSmallThreads) void act_quant_small_kernel(
   if (b >= n_blocks) return;
   const uint32_t v[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
   uint32_t c0, c1, sc;
-  if (q.exact)
-    sc = quantize_block_as<true>(v, g, g * (1.0f / 6.0f), 0.0f, c0, c1);
-  else
-    sc = quantize_block_as<false>(v, g, g * (1.0f / 6.0f), 0.25f * q.gf, c0, c1);
+  with_quant_form(q, [&](auto form) {
+    sc = quantize_block_as<decltype(form)::value>(v, g, g * (1.0f / 6.0f), 0.25f * q.gf, c0, c1);
+  });
   reinterpret_cast<uint2*>(codes)[b] = make_uint2(c0, c1);
   scales[b] = (uint8_t)sc;
 }

@@ -106,16 +106,12 @@ __device__ float quantize_into_lds(const DecodeQuantArgs& q, const GemmParams& p
   // weight ring's direct-to-LDS loads issued before it (the compiler cannot
   // tell the addresses apart), so the quantization runs before that wait.
   uint32_t c[kSlots][3];
+  with_quant_form(qm, [&](auto form) {
 #pragma unroll
-  for (int t = 0; t < kSlots; ++t) {
-    const uint32_t b = threadIdx.x + t * kThreads;
-    if (b < n_blocks) {
-      if (qm.exact)
-        c[t][2] = quantize_block_as<true>(v[t], g, gd6, 0.0f, c[t][0], c[t][1]);
-      else
-        c[t][2] = quantize_block_as<false>(v[t], g, gd6, 0.25f * qm.gf, c[t][0], c[t][1]);
-    }
-  }
+    for (int t = 0; t < kSlots; ++t)
+      if (threadIdx.x + t * kThreads < n_blocks)
+        c[t][2] = quantize_block_as<decltype(form)::value>(v[t], g, gd6, 0.25f * qm.gf, c[t][0], c[t][1]);
+  });
 #pragma unroll
   for (int t = 0; t < kSlots; ++t) {
     const uint32_t b = threadIdx.x + t * kThreads;

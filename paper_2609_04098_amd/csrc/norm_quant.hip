@@ -39,7 +39,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 
 // Normalize, round to bf16 and quantize block b of one row (d0, d1: its
 // 16 bf16 values).
-template <bool kExact>
+template <QuantForm kForm>
 __device__ __forceinline__ void norm_quant_block(uint4 d0, uint4 d1, uint32_t b, const uint4* __restrict__ gr,
                                                  float r, float g, float gd6, float gf4, uint2* __restrict__ codes_row,
                                                  uint8_t* __restrict__ scales_row, uint4* __restrict__ y_row) {
@@ -55,7 +55,7 @@ __device__ __forceinline__ void norm_quant_block(uint4 d0, uint4 d1, uint32_t b,
     y_row[2 * b + 1] = make_uint4(v[4], v[5], v[6], v[7]);
   }
   uint32_t c0, c1;
-  const uint32_t sc = quantize_block_as<kExact>(v, g, gd6, gf4, c0, c1);
+  const uint32_t sc = quantize_block_as<kForm>(v, g, gd6, gf4, c0, c1);
   codes_row[b] = make_uint2(c0, c1);
   scales_row[b] = (uint8_t)sc;
 }
@@ -90,6 +90,8 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_kernel(
   if (row >= M) return;                                     // the whole wave
   const uint32_t nb = K >> 4;
   const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * ldx);
+  const float g = *g_enc;
+  const QuantMode qm = quant_mode(g);
 
   float ss = 0.0f;
   uint4 d[kPerLane > 0 ? kPerLane : 1][2];
@@ -119,32 +121,26 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_kernel(
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
   const float r = 1.0f / __builtin_sqrtf(ss / (float)K + eps);
 
-  const float g = *g_enc;
   const uint4* gr = reinterpret_cast<const uint4*>(gamma);
   uint2* codes_row = reinterpret_cast<uint2*>(codes + (size_t)row * (K >> 1));
   uint8_t* scales_row = scales + (size_t)row * nb;
   uint4* y_row = y == nullptr ? nullptr : reinterpret_cast<uint4*>(y + (size_t)row * ldy);
-  const float gd6 = g * (1.0f / 6.0f);
-  const QuantMode qm = quant_mode(g);
-  const float gf4 = 0.25f * qm.gf;
-  auto pass2 = [&](auto exact_tag) {
-    constexpr bool kExact = decltype(exact_tag)::value;
+  const float gd6 = g * (1.0f / 6.0f), gf4 = 0.25f * qm.gf;
+  auto pass2 = [&](auto form) {
+    constexpr QuantForm kForm = decltype(form)::value;
     if constexpr (kPerLane > 0) {
       // From the registers of pass 1: X is read from memory once.
 #pragma unroll
       for (int j = 0; j < kPerLane; ++j) {
         const uint32_t b = lane + 64u * j;
-        if (b < nb) norm_quant_block<kExact>(d[j][0], d[j][1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
+        if (b < nb) norm_quant_block<kForm>(d[j][0], d[j][1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
       }
     } else {
       for (uint32_t b = lane; b < nb; b += 64)
-        norm_quant_block<kExact>(xr[2 * b], xr[2 * b + 1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
+        norm_quant_block<kForm>(xr[2 * b], xr[2 * b + 1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
     }
   };
-  if (qm.exact)
-    pass2(std::integral_constant<bool, true>{});
-  else
-    pass2(std::integral_constant<bool, false>{});
+  with_quant_form(qm, pass2);
 }
 
 // Two waves per row (rows of at most 128 * kPerLane blocks): wave half hw
@@ -158,11 +154,13 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_pair_kernel(
     float eps, const float* __restrict__ g_enc, uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
     uint16_t* __restrict__ y, uint32_t ldy) {
   __shared__ float half_sum[kNormThreads / 64];
+  __shared__ QuantMode mode;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hw = wave & 1u;
   const uint32_t row = blockIdx.x * (kNormThreads / 128) + (wave >> 1);
   const bool live = row < M;                                // both waves of the pair; no early exit (barrier)
   const uint32_t nb = K >> 4;
   const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)(live ? row : 0) * ldx);
+  const float g = *g_enc;
   uint4 d[kPerLane][2];
   float ss = 0.0f;
 #pragma unroll
@@ -174,6 +172,12 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_pair_kernel(
       d[j][1] = xr[2 * b + 1];
     }
   }
+  // Once per workgroup, while X is on its way.  (By every wave it was 0.5 us of
+  // 8.3 at 8192 rows of 1024, where a wave has half a block per lane.)
+  if (wave == 0) {
+    const QuantMode m = quant_mode(g);
+    if (lane == 0) mode = m;
+  }
 #pragma unroll
   for (int j = 0; j < kPerLane; ++j) {
     const uint32_t v[8] = {d[j][0].x, d[j][0].y, d[j][0].z, d[j][0].w, d[j][1].x, d[j][1].y, d[j][1].z, d[j][1].w};
@@ -184,28 +188,23 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_quant_pair_kernel(
   if (lane == 0) half_sum[wave] = ss;
   __syncthreads();
   if (!live) return;
+  const QuantMode qm{(QuantForm)__builtin_amdgcn_readfirstlane((int)mode.form), mode.gf};
   ss = half_sum[wave & ~1u] + half_sum[wave | 1u];
   const float r = 1.0f / __builtin_sqrtf(ss / (float)K + eps);
-  const float g = *g_enc;
   const uint4* gr = reinterpret_cast<const uint4*>(gamma);
   uint2* codes_row = reinterpret_cast<uint2*>(codes + (size_t)row * (K >> 1));
   uint8_t* scales_row = scales + (size_t)row * nb;
   uint4* y_row = y == nullptr ? nullptr : reinterpret_cast<uint4*>(y + (size_t)row * ldy);
-  const float gd6 = g * (1.0f / 6.0f);
-  const QuantMode qm = quant_mode(g);
-  const float gf4 = 0.25f * qm.gf;
-  auto pass2 = [&](auto exact_tag) {
-    constexpr bool kExact = decltype(exact_tag)::value;
+  const float gd6 = g * (1.0f / 6.0f), gf4 = 0.25f * qm.gf;
+  auto pass2 = [&](auto form) {
+    constexpr QuantForm kForm = decltype(form)::value;
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
       const uint32_t b = 64u * hw + lane + 128u * j;
-      if (b < nb) norm_quant_block<kExact>(d[j][0], d[j][1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
+      if (b < nb) norm_quant_block<kForm>(d[j][0], d[j][1], b, gr, r, g, gd6, gf4, codes_row, scales_row, y_row);
     }
   };
-  if (qm.exact)
-    pass2(std::integral_constant<bool, true>{});
-  else
-    pass2(std::integral_constant<bool, false>{});
+  with_quant_form(qm, pass2);
 }
 
 hipError_t launch_rmsnorm_quant(const void* x, int64_t M, int64_t K, int64_t ldx, const void* gamma,

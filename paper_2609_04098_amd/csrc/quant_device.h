@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace nvfp4 {
 
 constexpr float kRange = 2688.0f;             // 6 (E2M1 max) * 448 (E4M3 max)
@@ -235,13 +237,15 @@ __device__ __forceinline__ uint32_t quantize_block(const uint32_t v[8], float g,
 // many products are a midpoint but for the rounding of G) is on one known side
 // of it; scaling G by 1 +- 2^-21 moves the product past the error to that
 // side, and no further threshold than 2^-20 with it.  quant_mode decides once
-// per wave: `exact` if the sides differ or an exact tie exists (G = 2688 /
-// amax exact), or for G outside [2^-100, 2^100].
+// per wave: the exact decision if the sides differ or an exact tie exists (G =
+// 2688 / amax exact), with the two-multiply q for G outside [2^-100, 2^100],
+// where G * 4 / S could overflow or lose bits.
 //
 // Per element: widening, the product, half a conversion (2.5 instructions
 // against 7.5 of the exact decision).
+enum class QuantForm { kFast, kExact, kExactTwoMul };
 struct QuantMode {
-  bool exact;
+  QuantForm form;
   float gf;     // G, or G (1 +- 2^-21)
 };
 
@@ -251,7 +255,7 @@ __device__ __forceinline__ QuantMode quant_mode(float g) {
   const uint32_t gb = __float_as_uint(g);
   const float gm = __uint_as_float((gb & 0x007FFFFFu) | 0x3F800000u);        // significand of G, [1, 2)
   const float mu = (float)((2u * (lane & 3u) + 1u) * (8u + (lane >> 2)));
-  const float t = mu / gm;
+  const float t = mu * __builtin_amdgcn_rcpf(gm);                            // to 2^-22: x below is that of mu / gm where near
   // Power of two that brings t to [128, 256).
   const float p = __uint_as_float((127u + 7u + 127u - (__float_as_uint(t) >> 23)) << 23);
   const float x = __builtin_rintf(t * p);                                    // the only bf16 significand near it
@@ -261,12 +265,14 @@ __device__ __forceinline__ QuantMode quant_mode(float g) {
   const uint64_t above = __ballot(near && e > 0.0f), below = __ballot(near && e < 0.0f);
   const uint64_t tie = __ballot(near && e == 0.0f);
   QuantMode q;
-  q.exact = tie != 0 || (above != 0 && below != 0) || !(g >= 0x1p-100f && g <= 0x1p100f);
+  q.form = !(g >= 1.0f / kHugeScale && g <= kHugeScale) ? QuantForm::kExactTwoMul
+           : tie != 0 || (above != 0 && below != 0)     ? QuantForm::kExact
+                                                        : QuantForm::kFast;
   q.gf = __builtin_fmaf(g, above ? 0x1p-21f : below ? -0x1p-21f : 0.0f, g);
   return q;
 }
 
-// quantize_block for a tensor whose quant_mode is not exact (gf4 = gf / 4).
+// quantize_block for a tensor whose quant_mode is the fast form (gf4 = gf / 4).
 template <bool kBranch = true>
 __device__ __forceinline__ uint32_t quantize_block_fast(const uint32_t v[8], float g, float gd6, float gf4,
                                                         uint32_t& c0, uint32_t& c1) {
@@ -296,16 +302,25 @@ __device__ __forceinline__ uint32_t quantize_block_fast(const uint32_t v[8], flo
   return bs.code;
 }
 
-// One block in the form `kExact` of a tensor's quant_mode (gf4: gf / 4 of the
-// fast form, unused in the exact one, which takes the two-multiply q: it holds
-// for every G).
-template <bool kExact, bool kBranch = true>
+// One block in the form of a tensor's quant_mode (gf4: gf / 4 of the fast form,
+// unused in the exact ones).
+template <QuantForm kForm, bool kBranch = true>
 __device__ __forceinline__ uint32_t quantize_block_as(const uint32_t v[8], float g, float gd6, float gf4,
                                                       uint32_t& c0, uint32_t& c1) {
-  if constexpr (kExact)
-    return quantize_block<true, kBranch>(v, g, gd6, c0, c1);
-  else
+  if constexpr (kForm == QuantForm::kFast)
     return quantize_block_fast<kBranch>(v, g, gd6, gf4, c0, c1);
+  else
+    return quantize_block<kForm == QuantForm::kExactTwoMul, kBranch>(v, g, gd6, c0, c1);
+}
+
+// run(form as an integral constant) for the form of `q`, uniform over a launch.
+template <class Run>
+__device__ __forceinline__ void with_quant_form(const QuantMode& q, Run run) {
+  switch (q.form) {
+    case QuantForm::kFast: run(std::integral_constant<QuantForm, QuantForm::kFast>{}); break;
+    case QuantForm::kExact: run(std::integral_constant<QuantForm, QuantForm::kExact>{}); break;
+    default: run(std::integral_constant<QuantForm, QuantForm::kExactTwoMul>{});
+  }
 }
 
 }  // namespace nvfp4

@@ -148,8 +148,8 @@ __global__ __launch_bounds__(KS * 64, 2) void quant_gemm_kernel(QuantGemmArgs q,
 #pragma unroll
     for (int fb = 0; fb < FN; ++fb) acc[fa][fb] = floatx16{};
 
-  auto run = [&](auto exact_tag) {
-    constexpr bool kExact = decltype(exact_tag)::value;
+  auto run = [&](auto form) {
+    constexpr QuantForm kForm = decltype(form)::value;
     auto compute = [&](const Chunk& c, uint32_t i) {
       const uint32_t kc = wave + KS * i;
       uint32_t cd[FM][4];
@@ -162,8 +162,8 @@ __global__ __launch_bounds__(KS * 64, 2) void quant_gemm_kernel(QuantGemmArgs q,
         const uint32_t v1[8] = {(uint32_t)c.x[f][2][0], (uint32_t)c.x[f][2][1], (uint32_t)c.x[f][2][2],
                                 (uint32_t)c.x[f][2][3], (uint32_t)c.x[f][3][0], (uint32_t)c.x[f][3][1],
                                 (uint32_t)c.x[f][3][2], (uint32_t)c.x[f][3][3]};
-        const uint32_t s0 = quantize_block_as<kExact, false>(v0, g, gd6, gf4, cd[f][0], cd[f][1]);
-        const uint32_t s1 = quantize_block_as<kExact, false>(v1, g, gd6, gf4, cd[f][2], cd[f][3]);
+        const uint32_t s0 = quantize_block_as<kForm, false>(v0, g, gd6, gf4, cd[f][0], cd[f][1]);
+        const uint32_t s1 = quantize_block_as<kForm, false>(v1, g, gd6, gf4, cd[f][2], cd[f][3]);
         if (kCodes) {
           // Buffer stores: the lane's offset is fixed, the chunk goes in the
           // scalar offset; rows >= M have offsets past the buffers (dropped).
@@ -226,10 +226,7 @@ __global__ __launch_bounds__(KS * 64, 2) void quant_gemm_kernel(QuantGemmArgs q,
       }
     }
   };
-  if (qm.exact)
-    run(std::integral_constant<bool, true>{});
-  else
-    run(std::integral_constant<bool, false>{});
+  with_quant_form(qm, run);
   // The partial sums reuse the X slots (every load has landed: the last
   // chunk waited for all of them).
   __syncthreads();

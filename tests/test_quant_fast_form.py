@@ -12,13 +12,15 @@ f32 = np.float32
 MU = np.array([m * s for s in range(8, 16) for m in (1, 3, 5, 7)], dtype=np.float64)
 
 
-def _mode(g):
-    """quant_mode of csrc/quant_device.h: (exact, gf)."""
+def _mode(g, rcp_ulps=0):
+    """quant_mode of csrc/quant_device.h: (exact, gf), with a reciprocal that is
+    off by rcp_ulps."""
     g = f32(g)
     gm = np.frexp(np.float64(g))[0] * 2.0
     if g == 0:
         return True, g
-    t = (MU.astype(f32) / f32(gm)).astype(np.float64)
+    rcp = (f32(1.0) / f32(gm)).view(np.int32) + rcp_ulps
+    t = (MU.astype(f32) * rcp.astype(np.int32).view(f32)).astype(np.float64)
     p = 2.0 ** (8 - np.frexp(t)[1])
     x = np.rint(t * p)
     e = x * gm - MU * p                       # exact in float64 (33 bits less 15)
@@ -72,6 +74,11 @@ def test_fast_form_matches_the_exact_decision():
     assert fast > 600
 
 
+def test_the_form_does_not_hang_on_the_reciprocal():
+    for g in _scales():
+        assert _mode(g, -1) == _mode(g) == _mode(g, 1), float(g)
+
+
 def test_exact_form_is_kept_where_it_is_needed():
     # 2688 / amax without rounding: exact ties exist
     for a in (128, 168, 192, 224):
@@ -115,3 +122,58 @@ def test_quantizer_near_thresholds_and_far_out_of_range():
         xp, xs, _ = OQ.quantize_tensor(bits, g=g)
         aq = L.quantize_act(x, g=float(g))
         assert np.array_equal(aq.scales.cpu().numpy(), xs) and np.array_equal(aq.codes.cpu().numpy(), xp), float(g)
+
+
+FORMS = [
+    (f32(2688.0) / f32(201.0), False),       # fast
+    (f32(4.0), True),                        # exact ties, one multiplication for q
+    (f32(1.7 * 2.0 ** 100), True),           # two: q's factor could overflow
+    (f32(2.0 ** -101), True),                # ... or lose bits
+]
+
+
+def _form_input(rng, m, k, g):
+    """Blocks over the scales' whole range under G = g: saturating, normal,
+    subnormal and zero scales, the last with elements of both signs."""
+    v = rng.integers(128, 256, (m, k)) * rng.choice([-1.0, 1.0], (m, k)) * 2.0 ** rng.integers(-6, 1, (m, k))
+    e = np.floor(-np.log2(np.float64(g)))
+    v *= 2.0 ** np.repeat(rng.integers(-17, 7, (m, k // 16)), 16, axis=1) * 2.0 ** np.clip(e, -100, 100)
+    v[0, :16] *= 2.0 ** -20                  # S = 0
+    return v
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("g,exact", FORMS)
+@pytest.mark.parametrize("path,m,k", [
+    ("small", 20, 512), ("large", 272, 512), ("norm", 33, 512), ("norm", 5, 8208), ("narrow", 40, 512),
+    ("narrow", 300, 512), ("decode", 3, 512), ("decode", 20, 512)])
+def test_every_form_in_every_kernel(path, m, k, g, exact):
+    """Codes and scales of the quantizer's kernels, of the normalizing ones and of
+    both fused products, in each form, against the oracle."""
+    import torch
+    from paper_2609_04098_amd import linear as L
+    from paper_2609_04098_amd import synth
+    from tests.gpu_common import np_u8, to_dev_bf16
+    assert _mode(g)[0] == exact
+    rng = np.random.default_rng(m + k)
+    bits = synth.f64_to_bf16_bits(_form_input(rng, m, k, g))
+    x = to_dev_bf16(bits)
+    if path == "norm":
+        # gamma spreads the normalized rows (all of about 1) over the scales' range
+        gamma = to_dev_bf16(synth.f64_to_bf16_bits(_form_input(rng, 1, k, g))).reshape(-1)
+        x = to_dev_bf16(synth.f64_to_bf16_bits(rng.standard_normal((m, k))))
+        y = torch.empty_like(x)
+        aq = L.rmsnorm_quantize_act(x, gamma, 1e-6, float(g), y=y)
+        bits = y.view(torch.int16).cpu().numpy().view(np.uint16)
+    elif path in ("narrow", "decode"):
+        n = 96 if path == "narrow" else 200
+        pw = L.pack_weight(to_dev_bf16(synth.f64_to_bf16_bits(rng.standard_normal((n, k)))))
+        aq = L.alloc_act(m, k, x.device)
+        L.quantize_gemm(x, pw, g=float(g), act_out=aq)
+    else:
+        aq = L.quantize_act(x, g=float(g))
+    xp, xs, _ = OQ.quantize_tensor(bits, g=g)
+    s = np.unique(xs)
+    assert s.min() == 0 and (s == 126).any() and ((s > 0) & (s < 8)).any()
+    np.testing.assert_array_equal(np_u8(aq.scales), xs)
+    np.testing.assert_array_equal(np_u8(aq.codes), xp)
