@@ -186,17 +186,21 @@ def test_gemm_strided_output():
     check_small(x, w, [0, 64, 136], ldy=256, what="ldy")
 
 
-@pytest.mark.parametrize("ldy,col0", [(768, 0), (771, 0), (776, 1), (776, 8)])
-def test_gemm_bf16_rows_staged_or_not(ldy, col0):
-    # The prefill kernel's bf16 epilogue stages whole wave blocks through
-    # LDS and stores 16 bytes of a row per lane when every output row starts
-    # on a 16-byte boundary (ldy = 768, or 776 at an 8-column offset), and
-    # stores element by element otherwise (ldy = 771; or the output shifted
-    # by one column).  Segment boundaries on multiples of 256 keep every
-    # wave block in one segment.  Every bf16 value must be RNE of the FP32
-    # output, and nothing outside the output may be written.
+@pytest.mark.parametrize("pad,col0", [(0, 0), (3, 0), (8, 1), (8, 8), (2, 0)])
+@pytest.mark.parametrize("m,n,k,kernel", [(512, 768, 256, "gemm_splitk_kernel"), (777, 2560, 256, "128x128"),
+                                          (3000, 4104, 192, "256x256")])
+def test_gemm_bf16_rows_staged_or_not(m, n, k, kernel, pad, col0):
+    # The tiled kernels' bf16 epilogue stages wave blocks through LDS and
+    # stores 16, 8 or 4 bytes of a row per lane, as the output's rows allow
+    # (pad 0 or 8: 16, at an 8-column offset as well; pad 2: 4), and element by
+    # element where a row starts on an odd column (pad 3, or the output shifted
+    # by one).  Segment boundaries on multiples of 256 keep every wave block in
+    # one segment.  Every bf16 value must be RNE of the FP32 output, and nothing
+    # outside the output may be written.
     rng = np.random.default_rng(307)
-    m, n, k = 512, 768, 256
+    ldy = n + pad
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert kernel in L.gemm_kernels(m, n, k)[0]
     x, w = _xw(rng, m, n, k)
     offs = [0, 256, n]
     aq = L.quantize_act(to_dev_bf16(x))

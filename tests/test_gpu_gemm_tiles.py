@@ -75,6 +75,31 @@ def test_gemm_tiles_and_k_parts(m, n, k, offs, ldy):
     log("%dx%dx%d: %s, workspace %d" % (m, n, k, L.gemm_kernels(m, n, k), need))
 
 
+@pytest.mark.parametrize("m,n,k,offs,ldy,name", [
+    (33, 97, 64, [0, 97], 97, "gemm_splitk_kernel<4,1,1,3>"),
+    (300, 4104, 64, [0, 1000, 4104], 4104, "gemm_splitk_kernel<4,1,2,3>"),
+    (777, 1999, 64, [0, 1999], 1999, "gemm_splitk_kernel<4,2,2,3>"),
+    (3000, 1999, 192, [0, 700, 1999], 2000, "gemm_splitk_kernel<4,2,3,2>"),
+    (100, 4104, 1280, [0, 4104], 4112, "gemm_splitk_kernel<8,1,3,3>"),
+    (3000, 1999, 64, [0, 1999], 1999, "gemm_splitk_kernel<4,1,5,2>"),
+    (300, 5064, 64, [0, 2000, 5064], 5064, "gemm_lds_kernel<LdsMid> (128x128 tiles)"),
+    (1030, 97, 2112, [0, 97], 97, "gemm_lds_kernel<LdsMid> (128x128 tiles, K parts)"),
+    (777, 2600, 256, [0, 1300, 2600], 2601, "gemm_lds_kernel<LdsMidSuper> (128x128 tiles, scale super-stages)"),
+    (33, 97, 8704, [0, 97], 97, "gemm_lds_kernel<LdsMidSuper> (128x128 tiles, scale super-stages, K parts)"),
+    (900, 4104, 128, [0, 4104], 4104, "gemm_lds_kernel<LdsLow> (64x256 tiles)"),
+    (900, 4104, 256, [0, 333, 4104], 4106, "gemm_lds_kernel<LdsLowSuper> (64x256 tiles, scale super-stages)"),
+    (33, 1999, 17408, [0, 1999], 1999, "gemm_lds_kernel<LdsLowSuper> (64x256 tiles, scale super-stages, K parts)"),
+    (3000, 4104, 192, [0, 4104], 4104, "gemm_lds_kernel<LdsSquare> (256x256 tiles)"),
+    (3000, 4104, 256, [0, 1000, 4104], 4108, "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, scale super-stages)"),
+    (3000, 1300, 4352, [0, 1300], 1300,
+     "gemm_lds_kernel<LdsSquareSuper> (256x256 tiles, scale super-stages, K parts)"),
+])
+def test_gemm_every_tile_kind(m, n, k, offs, ldy, name):
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert L.gemm_kernels(m, n, k)[0].startswith(name)
+    _case(m, n, k, offs, ldy)
+
+
 def test_gemm_k_parts_without_their_workspace():
     """A workspace short of the K parts' (or none) gives the nvfp4_gemm result."""
     # Long K on few tiles: the shape stays on K parts whatever the small

@@ -19,10 +19,14 @@ pytestmark = pytest.mark.gpu
 
 # (m, n, k, segment offsets): each case takes a different GEMM path.
 CASES = [
-    (513, 520, 1024, [0, 100, 520]),       # 256 x 256 tiles with scale super-stages
-    (777, 1300, 384, [0, 500, 1300]),      # 256 x 256 tiles, K % 256 != 0, ragged M and N
+    (513, 520, 1024, [0, 100, 520]),       # small split-K tiles
+    (777, 1300, 384, [0, 500, 1300]),      # ... K % 256 != 0, ragged M and N
     (300, 96, 5184, [0, 48, 96]),          # tall-skinny split-K
     (7, 4100, 1024, [0, 4000, 4100]),      # decode split-K; also the fused quantize + GEMM
+    (3000, 4104, 256, [0, 1000, 4104]),    # 256 x 256 tiles with scale super-stages
+    (1030, 770, 4352, [0, 770]),           # 128 x 128 tiles in K parts (workspace) and their sum
+    (3000, 1304, 208, [0, 1304]),          # K % 64 != 0: padded activation in the workspace
+    (1500, 4004, 112, [0, 2000, 4004]),    # ... and rows that stay on the register path
 ]
 REPS = 3
 
