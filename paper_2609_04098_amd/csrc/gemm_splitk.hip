@@ -360,17 +360,19 @@ static hipError_t launch_splitk(const GemmOperands& o, GemmParams p, bool out_f3
 // give every tile its own CU (gates at N = 96, K = 5120, same box: 1000 rows
 // 33.5 -> 10.4 us, 4000 rows 34.3 -> 14.8, 8000 rows 34.5 -> 20.6 against
 // 64 x 96 tiles of four waves, which keep 16 to 125 CUs busy).  Up to twice as
-// many rows 32 x 96 tiles of four waves where a workgroup has more to do than the
-// product: it quantizes X (8300 rows 63 -> 49 us), or computes the gates at the end
-// (16384 x 96 x 5120 33.9 -> 31.6), the latter while K is short (x 17408 71.6
-// against 75.5).  The plain product, and beyond: 64 x 96 tiles (16384 x 96 x 17408
-// 62.5 us and 70.6 with 32 x 96 of four waves; 32768 rows: 53.8 and 77.8 with 32 x
-// 96 of eight).  Four waves either way: the same order of the sums.
+// many rows 32 x 96 tiles of four waves where a tile's first loads and epilogue
+// weigh more than the weight's decode, which two row fragments share: with the
+// quantizer in the workgroup (8300 rows 63 -> 49 us), with the gates at its end up
+// to K = 8192 (16384 x 96 x 5120 33.9 -> 31.6; x 17408 71.6 against 75.5), in the
+// plain product below 2048 (8300 x 96 x 64 6.7 -> 5.8, x 320 7.5 -> 6.9, x 2560 14.1
+// against 14.2, 16384 x 96 x 17408 62.5 against 70.6).  Else, and beyond: 64 x 96
+// tiles (32768 rows: 53.8 us, 77.8 with 32 x 96 of eight waves).  Four waves either
+// way: the same order of the sums.
 int narrow_fragments(int64_t M, int64_t N, int64_t K, uint32_t n_cu, NarrowUse use) {
   const uint64_t rows = (uint64_t)((M + 31) / 32), frags = (uint64_t)((N + 31) / 32);
   for (uint64_t f = 1; f <= 3; ++f)
     if (rows * ((frags + f - 1) / f) <= n_cu) return (int)f;
-  const bool small = use == NarrowUse::kQuantize || (use == NarrowUse::kGates && K <= 8192);
+  const bool small = use == NarrowUse::kQuantize || K <= (use == NarrowUse::kGates ? 8192 : 2047);
   return small && rows <= 2 * (uint64_t)n_cu ? 4 : 0;
 }
 

@@ -116,7 +116,8 @@ def test_decode_shapes_wide_output_and_long_k(k, name):
     (2721, 90, 192, [0, 30, 90]),          # 86 x 3 tiles would not fit the CUs: two fragments
     (4097, 96, 128, [0, 48, 96]),          # three fragments
     (8192, 96, 64, [0, 48, 96]),           # one tile per CU
-    (8193, 96, 192, [0, 48, 96]),          # 64 x 96 tiles; fused, two 32 x 96 tiles of 4 waves per CU
+    (8193, 96, 192, [0, 48, 96]),          # two 32 x 96 tiles of 4 waves per CU
+    (8200, 70, 2048, [0, 70]),             # ... long K: 64 x 96 tiles; fused, 32 x 96
     (16384, 90, 64, [0, 90]),
     (16385, 90, 64, [0, 90]),              # 64 x 96 tiles for both
 ])
