@@ -332,12 +332,12 @@ size_t nvfp4_quantize_gemm_workspace(int64_t M, int64_t N, int64_t K);
  *   - narrow outputs, N <= 128 (the tall-skinny gate projections), any M:
  *     X is quantized in registers inside the GEMM (read once with a given
  *     G; dynamic mode adds the amax pass in front);
- *   - decode shapes, M <= 32 (any N): for M * K <= 16384 (up to 3 tokens
+ *   - decode shapes, M <= 32 (N > 96): for M * K <= 16384 (up to 3 tokens
  *     of width 5120) one launch in which every workgroup quantizes all of
  *     X into its LDS (and takes the dynamic G itself) and the GEMM reads
- *     the activation from there; larger activations take two launches (the
- *     quantizer, then the GEMM), with the codes in a_codes or in the
- *     workspace.
+ *     the activation from there; larger activations with N > 128 take two
+ *     launches (the quantizer, then the GEMM), with the codes in a_codes or in
+ *     the workspace.
  * The result equals nvfp4_quantize_act followed by nvfp4_gemm: the same
  * codes, scales and G_A, and the GEMM sums in the same order as nvfp4_gemm
  * at these shapes, but for M > 32 with 96 < N <= 128, where the two sum the same

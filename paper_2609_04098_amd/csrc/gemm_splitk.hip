@@ -421,13 +421,14 @@ constexpr int64_t kRowsMaxElems = 12 * 16384, kLongNarrowK = 2048;
 //    18.1 with two; 32 x 34816 x 5120, 4 waves and five tiles: 22.3 against 25.8
 //    with three and 26.2 with two).  Up to four tiles per CU two tiles make two
 //    full rounds (17 x 24600 x 17408 53.3 us; 59.1 with five).
-//  * N <= 128 (97 .. 128 here): the waves of the fused launch at these widths,
-//    quant_gemm_kernel, which has no 16-row form: eight from K = kLongNarrowK on (1 x
-//    128 x 5120 8 waves 7.5 us, 4 waves 8.6; x 17408 17.9 and 23.5; 16 waves of the
-//    16-row form would take 6.1 and 13.1).
+//  * N <= 128 (97 .. 128 here) with M * K past the one-launch limit: the waves of
+//    the fused launch at these sizes, quant_gemm_kernel, which has no 16-row form:
+//    eight from K = kLongNarrowK on (7 x 128 x 5120 8 waves 7.9 us, 4 waves 8.6; x
+//    17408 18.3 and 23.5; 16 waves of the 16-row form would take 6.4 and 12.9).
 DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
   const uint64_t tiles = (uint64_t)((N + 31) / 32);
-  if (N <= 128) return K >= kLongNarrowK ? DecodeShape::k8Shared : DecodeShape::k4Private;
+  if (N <= 128 && M * K > 16 * (int64_t)kDecodeFuseMaxBlocks)
+    return K >= kLongNarrowK ? DecodeShape::k8Shared : DecodeShape::k4Private;
   if (M <= 16) {
     if (tiles <= n_cu) return DecodeShape::kRows16w1;
     if (5 * tiles < 9 * (uint64_t)n_cu) return DecodeShape::kRows8w2;        // three: under 0.6 of the CUs

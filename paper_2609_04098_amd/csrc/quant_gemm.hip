@@ -293,13 +293,13 @@ hipError_t launch_quant_gemm(const void* x, int64_t M, int64_t K, int64_t ldx, f
   }
   GemmParams p = gemm_params(M, K, N, seg_offsets, n_seg, ldy);
   const uint8_t* wp = static_cast<const uint8_t*>(w_packed);
+  if (M <= 32 && N > 96 && M * K <= kDecodeFuseMaxElems) {
+    // One launch: every workgroup quantizes X into its LDS.
+    const DecodeQuantArgs dq{static_cast<const uint16_t*>(x), (uint32_t)ldx, g_enc, codes, scales};
+    const GemmOperands o{codes, scales, g_enc, wp, w_g, y};
+    return launch_decode_quant_gemm(o, p, dq, dynamic, out_f32, stream);
+  }
   if (quant_gemm_uses_decode_path(M, N)) {
-    if (M * K <= kDecodeFuseMaxElems) {
-      // One launch: every workgroup quantizes X into its LDS.
-      const DecodeQuantArgs dq{static_cast<const uint16_t*>(x), (uint32_t)ldx, g_enc, codes, scales};
-      const GemmOperands o{codes, scales, g_enc, wp, w_g, y};
-      return launch_decode_quant_gemm(o, p, dq, dynamic, out_f32, stream);
-    }
     // Larger activations: the quantizer, then the same GEMM kernel reading
     // the codes from memory (the caller's buffers or the workspace).
     uint8_t* ws = static_cast<uint8_t*>(workspace) + kActScratchBytes;

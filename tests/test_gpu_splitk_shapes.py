@@ -75,8 +75,9 @@ def test_decode_shapes(m, n, k, offs):
     _check(m, n, k, offs)
 
 
-# The fused launch at these widths has 4 waves, or 8 from K = 2048 on.
-@pytest.mark.parametrize("k", [64, 1088, 1984, 2048, 5120, 8192])
+# Up to M K = 16384 one launch of the plain decode kernel's form; past it the fused
+# launch has 4 waves, or 8 from K = 2048 on.
+@pytest.mark.parametrize("k", [64, 960, 1088, 1984, 2048, 5120, 8192])
 @pytest.mark.parametrize("n", [97, 128])
 @pytest.mark.parametrize("m", [1, 16, 17, 32])
 def test_decode_shapes_of_up_to_four_column_tiles(m, n, k):
