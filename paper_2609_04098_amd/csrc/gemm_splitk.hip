@@ -407,9 +407,10 @@ constexpr int64_t kRowsMaxElems = 12 * 16384, kLongNarrowK = 2048;
 //    workgroup quantizes X (the fused launch) 8 waves and three (4 and 16 x 34816
 //    x 5120 25.1 -> 22.0 and 28.6 -> 24.3; 1 x 34816 x 5120 fused 27.4 -> 22.7, 23.8
 //    with 4 waves and two), more again 8 waves and two (1 x 50000 x 17408 96 us; 124
-//    with 4 waves and two).  With more X than kRowsMaxElems the 8-wave forms
-//    load it more slowly than the 32-row tiles of 4 waves (16 x 24600 x 17408 55
-//    us on those).
+//    with 4 waves and two).  With more X than kRowsMaxElems every 8-wave form
+//    loads it more slowly: 4 waves and two tiles up to six tiles per CU (16 x 24600
+//    x 17408 56.5 us; 49.7 with W in the last-level cache on 32-row tiles, 40.6
+//    with this), 32-row tiles past it (16 x 50000 x 17408 123 -> 115).
 //  * 17 to 32 rows, at most one tile per CU: 4 waves with per-wave rings
 //    (32 x 8192 x 5120: two tiles per workgroup and a shared activation ring
 //    13.7 us, this 9.7), for long K 8 waves with a shared ring (32 x 5120 x
@@ -433,8 +434,9 @@ DecodeShape decode_shape(int64_t M, int64_t N, int64_t K, uint32_t n_cu) {
     if (tiles <= n_cu) return DecodeShape::kRows16w1;
     if (5 * tiles < 9 * (uint64_t)n_cu) return DecodeShape::kRows8w2;        // three: under 0.6 of the CUs
     if (tiles <= 3 * (uint64_t)n_cu) return DecodeShape::kRows8w3;
-    if (tiles <= 4 * (uint64_t)n_cu || tiles > 6 * (uint64_t)n_cu)
-      return M * K > kRowsMaxElems ? DecodeShape::k4SharedPair : DecodeShape::kRows8w2;
+    const bool past_six = tiles > 6 * (uint64_t)n_cu;
+    if (M * K > kRowsMaxElems) return past_six ? DecodeShape::k4SharedPair : DecodeShape::kRows4w2;
+    if (past_six || tiles <= 4 * (uint64_t)n_cu) return DecodeShape::kRows8w2;
     return M * K <= 16 * (int64_t)kDecodeFuseMaxBlocks ? DecodeShape::kRows8w3 : DecodeShape::kRows4w2;
   }
   if (tiles <= n_cu) return K >= 8192 ? DecodeShape::k8Shared : DecodeShape::k4Private;

@@ -84,14 +84,16 @@ def test_decode_shapes_of_up_to_four_column_tiles(m, n, k):
     _check(m, n, k, [0, 40, n])
 
 
-@pytest.mark.parametrize("k,name", [
-    (12224, "gemm_rows16_kernel<8,2,2>"),  # M K = 195584
-    (12352, "gemm_splitk_kernel<4,1,2,3>"),  # 197632: 32-row tiles of 4 waves
+@pytest.mark.parametrize("n,k,name", [
+    (24579, 12224, "gemm_rows16_kernel<8,2,2>"),    # M K = 195584
+    (24579, 12352, "gemm_rows16_kernel<4,2,3>"),    # 197632
+    (49155, 12224, "gemm_rows16_kernel<8,2,2>"),    # past six tiles per CU
+    (49155, 12352, "gemm_splitk_kernel<4,1,2,3>"),  # ... 32-row tiles
 ])
-def test_decode_shapes_wide_output_and_long_k(k, name):
-    """On either side of the length of X from which 32-row tiles are taken; Y at
-    a sample of the columns, the last ones among them."""
-    m, n = 16, 24579
+def test_decode_shapes_wide_output_and_long_k(n, k, name):
+    """On either side of the length of X from which the 8-wave forms are left; Y
+    at a sample of the columns, the last ones among them."""
+    m = 16
     gen = torch.Generator(device="cuda").manual_seed(k)
     w = torch.randn(n, k, generator=gen, device="cuda", dtype=torch.bfloat16) * 0.02
     xb = _inputs(m, 16, k)[0]
