@@ -62,8 +62,12 @@ def _scratch(nbytes, device, stream):
 def _copy_on(dst, src, stream):
     """``dst.copy_(src)`` in the order of ``stream``, whose next kernel reads it.
     No gradient flows through a scale: a learned one leaves dst a plain buffer."""
+    if src.requires_grad:
+        src = src.detach()
+    if stream is None:
+        return dst.copy_(src)
     with _on(stream, dst.device):
-        return dst.copy_(src.detach())
+        return dst.copy_(src)
 
 
 def pack_weight(w, seg_offsets=None, g_seg=None, stream=None) -> PackedWeight:
